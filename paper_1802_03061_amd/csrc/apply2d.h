@@ -11,7 +11,7 @@ struct ChanScale {
     double s[2 * RTE_MAX_L + 1];   // per-channel factor applied in pass A (D for operator A, 1 for K~)
 };
 
-// The coarse correction added in pass B instead of pass A (FP32 fused pass B, L <= 8).  Pass A
+// The coarse correction added in pass B instead of pass A (FP32, L <= 8).  Pass A
 // has transformed the vector alone; pass B adds, to every column before its y-FFT, the
 // x-spectrum of the correction cs P y scaled as pass A scales its input.  P is separable (an
 // x- then a y-interpolation), so the x-spectrum of row yy of P y_c is (1 - a) G_c[r0] + a G_c[r1],
@@ -29,19 +29,17 @@ template <typename T>
 struct Apply2DArgs {
     int nx, ny, PX, PY, L, C;
     cx<T>* work;               // work buffer [nbatch][C][NKS][ny], NKS = pack ? PX/2 : PX/2+1
-    cx<T>* work2;              // split pass B only: [nbatch][C][NKS][PY] (may be null otherwise)
+    cx<T>* work2;              // L > 8 only: [nbatch][C][NKS][PY] (may be null otherwise)
     const cx<T>* Q;            // quarter spectra [2L+1][PX/2+1][PY/2+1], scaled by 1/(PX PY)
     const cx<T>* twx;          // exp(-2 pi i q/PX), q < PX
     const cx<T>* twy;          // exp(-2 pi i q/PY), q < PY
     hipStream_t stream;
     const cx<T>* twm = nullptr;   // L > 8: stage twiddles of the mode-axis FFT (length mode_fft_len(L))
-    const cx<T>* twy1 = nullptr;  // y twiddles in the radix-32 schedule (fft.h, schedule 1)
-    const cx<T>* twyh = nullptr;  // stage twiddles of length PY/2 (pass B split in halves)
+    const cx<T>* twyh = nullptr;  // pass B in two halves: see half_twiddles
     int pack = 0;              // 1: x-frequencies 0 and PX/2 share column 0 of the work buffer
     int var[3] = {0, 0, 0};    // kernel variant of passes A, B, C (see apply2d_variant_count)
     // The input's channels other than channel 0 are zero and pass A ran for channel 0 alone, so
-    // pass B reads channel 0 only (split form: forward y-FFTs of channel 0 only; fused form: the
-    // other channels' spectra start as zeros without loads).  The right-hand side K~ f.
+    // pass B takes channel 0 only (the other channels' spectra are zero).  The right-hand side K~ f.
     int single_in = 0;
     // Optional coarse correction (operator A, one batch entry): the input of the apply is taken as
     // x + cs P y, y = corr[C][ny/cF][nx/cF] (FP32), P = bilinear interpolation from the coarse
@@ -56,16 +54,15 @@ struct Apply2DArgs {
 
 // Kernel variants (same arithmetic, different tiling; results agree up to rounding):
 //   passes A and C (PX >= 128): row tiles of 16, 8, 32 or 4 rows (FP32) / 8, 4, 16 or 2 rows (FP64)
-//   pass B, fused form (PY >= 128): default threads and FFT grouping, 1024 threads with groups of
-//   4 transforms (FP32 only), 256 threads, the register-resident form (FP32, 5+ channels), the
-//   radix-32 schedule (PY >= 256), and all of a block's transforms in one FFT stage group where
-//   the default grouping splits them (FP32, PY = 1024, L >= 6)
-//   pass B, split form (FP64 with L > 4): three kernels through the full-length buffer, the
-//   column split in halves, or the coupling fused with the inverse y-FFTs by channel groups
+//   pass B, L <= 8: one kernel per shape (passb_wave.h).  The variant numbers of the forms it
+//   replaced stay valid and select it.
 //   pass B, L > 8: the coupling as a mode-axis FFT or as a register-blocked direct sum
-// Number of variants of `pass` (0 = A, 1 = B, 2 = C) for this shape and precision.
+// Number of variants of `pass` (0 = A, 1 = B, 2 = C) for this shape and precision, and how many of
+// them are kernels of their own (the tuner times those).
 template <typename T>
 int apply2d_variant_count(int pass, int L, int PX, int PY);
+template <typename T>
+int apply2d_tuned_variants(int pass, int L, int PX);
 
 // One isotropic problem (C = 1) of a batched apply.  Pass A reads in (+ j * stride when jin is
 // set, j read from the device), pass C writes out (+ (j + 1) * stride when jout is set) and reads
@@ -121,20 +118,16 @@ template <typename T, typename TV>
 int apply2d_pass_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, int nbatch);
 template <typename T>
 int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch);
-// True when pass B for (L, PY) in precision T needs the work2 buffer.
+// True when pass B needs the work2 buffer, and when it takes the work buffer unpacked
+// (x-frequencies 0 and PX/2 in columns of their own instead of sharing column 0): L > 8.
+bool apply2d_needs_work2(int L);
+bool apply2d_unpacked(int L);
+// Whether pass B runs the y-transforms in two halves (twyh needed).
 template <typename T>
-bool apply2d_needs_work2(int L, int PY);
-// Whether the 2D work buffer must be unpacked (x-frequencies 0 and PX/2 in columns of their own
-// instead of sharing column 0) for pass B of this (precision, L, PY) and pass-B variant.
-template <typename T>
-bool apply2d_unpacked(int L, int PY, int var_b);
+bool apply2d_b_halves(int L, int PY);
 template <typename T, typename TV>
 int apply2d_pass_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                    int nbatch);
-// Whether pass B of this (precision, L, PY, pass-B variant) can add the coarse correction
-// (CorrB): the FP32 fused form in LDS, not the register-resident variant.
-template <typename T>
-bool apply2d_b_corr_ok(int L, int PY, int var_b);
 // Passes B and C of y = A (x + cs P y) for one batch entry, pass A having already written the
 // x-spectrum of the scaled x alone into a.work; a.bcorr and a.corr describe the correction.
 template <typename T, typename TV>

@@ -30,6 +30,8 @@
 #include "apply2d_tile.h"
 #include "fft.h"
 
+#include <algorithm>
+
 namespace rte {
 
 // ---------------------------------------------------------------------------- pass A --------
@@ -285,25 +287,45 @@ static void launch_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* 
         default: return -1;                       \
     }
 
+// Pass-B variant numbers that rte_set_variant takes for L <= 8: those of the tilings that existed
+// before the wave-private form replaced them all (default, 1024 and 256 threads, register-resident,
+// radix 32, one FFT group; in FP64 beyond LDS: split, halves, fused inverse), which now select it.
+static int pass_b_numbers(bool f64, int L, int PY) {
+    const int C = 2 * L + 1, ncol = C >= 4 ? 1 : (C == 3 ? 2 : 4), nf = ncol * C, n8 = nf * PY / 8;
+    const int nthr = n8 >= 512 ? 512 : (n8 >= 256 ? 256 : (n8 >= 128 ? 128 : 64));
+    const int group = std::max(1, std::min(nf, 3 * nthr * 8 / PY));
+    const long es = f64 ? 16 : 8, budget = 160 * 1024;
+    if ((nf * (long)padded(PY) + PY + 2 * C) * es <= budget && (!f64 || L <= 4)) {
+        const int base = PY < 128 ? 1 : (!f64 && L >= 2 ? 4 : (!f64 && n8 >= 1024 ? 3 : 2));
+        return base + (PY >= 256 ? 1 : 0) + (group < nf ? 1 : 0);
+    }
+    const bool half = PY >= 64 && (C * (long)padded(PY / 2) + PY / 2) * es <= budget;
+    return (half ? 2 : 1) + (L >= 1 ? 1 : 0);
+}
 template <typename T>
 int apply2d_variant_count(int pass, int L, int PX, int PY) {
     if (pass == 0 || pass == 2) return PX >= 128 ? 4 : 1;
     if (pass != 1) return 0;
-    switch (L) {
-        case 0: return pass_b_variants_L0<T>(PY);
-        case 1: return pass_b_variants_L1<T>(PY);
-        case 2: return pass_b_variants_L2<T>(PY);
-        case 3: return pass_b_variants_L3<T>(PY);
-        case 4: return pass_b_variants_L4<T>(PY);
-        case 5: return pass_b_variants_L5<T>(PY);
-        case 6: return pass_b_variants_L6<T>(PY);
-        case 7: return pass_b_variants_L7<T>(PY);
-        case 8: return pass_b_variants_L8<T>(PY);
-    }
+    if (L <= PASSB_FUSED_MAX_L) return pass_b_numbers(sizeof(T) == 8, L, PY);
     return L <= RTE_MAX_L ? 2 : 0;   // mode-axis FFT or direct coupling
 }
 template int apply2d_variant_count<float>(int, int, int, int);
 template int apply2d_variant_count<double>(int, int, int, int);
+template <typename T>
+int apply2d_tuned_variants(int pass, int L, int PX) {
+    return pass == 1 && L <= PASSB_FUSED_MAX_L ? 1 : apply2d_variant_count<T>(pass, L, PX, 16);
+}
+template int apply2d_tuned_variants<float>(int, int, int);
+template int apply2d_tuned_variants<double>(int, int, int);
+
+bool apply2d_needs_work2(int L) { return L > PASSB_FUSED_MAX_L; }
+bool apply2d_unpacked(int L) { return L > PASSB_FUSED_MAX_L; }
+template <typename T>
+bool apply2d_b_halves(int L, int PY) {
+    return L <= PASSB_FUSED_MAX_L && L >= 2 && (2 * L + 1) * (long)padded(PY) * (long)sizeof(cx<T>) > 160 * 1024;
+}
+template bool apply2d_b_halves<float>(int, int);
+template bool apply2d_b_halves<double>(int, int);
 
 template <typename T, typename TV>
 int apply2d_pass_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, int nbatch) {
@@ -325,57 +347,6 @@ int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch) {
     }
     return pass_b_large<T>(a, nbatch);
 }
-template <typename T>
-bool apply2d_needs_work2(int L, int PY) {
-    switch (L) {
-        case 0: return pass_b_split_L0<T>(PY);
-        case 1: return pass_b_split_L1<T>(PY);
-        case 2: return pass_b_split_L2<T>(PY);
-        case 3: return pass_b_split_L3<T>(PY);
-        case 4: return pass_b_split_L4<T>(PY);
-        case 5: return pass_b_split_L5<T>(PY);
-        case 6: return pass_b_split_L6<T>(PY);
-        case 7: return pass_b_split_L7<T>(PY);
-        case 8: return pass_b_split_L8<T>(PY);
-    }
-    return true;   // L > 8: split form
-}
-template bool apply2d_needs_work2<float>(int, int);
-template bool apply2d_needs_work2<double>(int, int);
-template <typename T>
-bool apply2d_unpacked(int L, int PY, int var_b) {
-    switch (L) {
-        case 0: return pass_b_unpacked_L0<T>(PY, var_b);
-        case 1: return pass_b_unpacked_L1<T>(PY, var_b);
-        case 2: return pass_b_unpacked_L2<T>(PY, var_b);
-        case 3: return pass_b_unpacked_L3<T>(PY, var_b);
-        case 4: return pass_b_unpacked_L4<T>(PY, var_b);
-        case 5: return pass_b_unpacked_L5<T>(PY, var_b);
-        case 6: return pass_b_unpacked_L6<T>(PY, var_b);
-        case 7: return pass_b_unpacked_L7<T>(PY, var_b);
-        case 8: return pass_b_unpacked_L8<T>(PY, var_b);
-    }
-    return true;   // L > 8: split form over unpacked columns
-}
-template bool apply2d_unpacked<float>(int, int, int);
-template bool apply2d_unpacked<double>(int, int, int);
-template <typename T>
-bool apply2d_b_corr_ok(int L, int PY, int var_b) {
-    switch (L) {
-        case 0: return pass_b_corr_ok_L0<T>(PY, var_b);
-        case 1: return pass_b_corr_ok_L1<T>(PY, var_b);
-        case 2: return pass_b_corr_ok_L2<T>(PY, var_b);
-        case 3: return pass_b_corr_ok_L3<T>(PY, var_b);
-        case 4: return pass_b_corr_ok_L4<T>(PY, var_b);
-        case 5: return pass_b_corr_ok_L5<T>(PY, var_b);
-        case 6: return pass_b_corr_ok_L6<T>(PY, var_b);
-        case 7: return pass_b_corr_ok_L7<T>(PY, var_b);
-        case 8: return pass_b_corr_ok_L8<T>(PY, var_b);
-    }
-    return false;
-}
-template bool apply2d_b_corr_ok<float>(int, int, int);
-template bool apply2d_b_corr_ok<double>(int, int, int);
 template <typename T, typename TV>
 int apply2d_pass_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                    int nbatch) {

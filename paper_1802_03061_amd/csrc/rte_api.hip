@@ -109,9 +109,6 @@ static void free_ctx(rte_ctx* c) {
     }
     dfree(c->twmf);
     dfree(c->twmd);
-    dfree(c->twy1f);
-    dfree(c->twy1d);
-    dfree(c->twyhf);
     dfree(c->twyhd);
     dfree(c->wf);
     dfree(c->wf2);
@@ -175,10 +172,10 @@ static int ensure_work(rte_ctx* c, int nb) {
         const size_t nt = (size_t)nb * c->C * NK * c->ny;
         const size_t nt2 = (size_t)nb * c->C * NK * c->PY;
         if ((rc = dalloc(&c->wd, nt))) return rc;
-        if (apply2d_needs_work2<double>(c->L, c->PY) && (rc = dalloc(&c->wd2, nt2))) return rc;
+        if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wd2, nt2))) return rc;
         if (f32) {
             if ((rc = dalloc(&c->wf, nt))) return rc;
-            if (apply2d_needs_work2<float>(c->L, c->PY) && (rc = dalloc(&c->wf2, nt2))) return rc;
+            if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wf2, nt2))) return rc;
         }
     } else {
         const size_t n1 = (size_t)nb * c->C * c->nz * NK * c->ny;
@@ -212,9 +209,9 @@ static ChanScale3 channel_scale3(const rte_ctx* c, int mode) {
 }
 
 // Column 0 of the 2D work buffer packs the x-frequencies 0 and PX/2 (two real sequences) except
-// with the register-resident pass B, which takes them as columns of their own.
+// with more than 17 modes, whose pass B takes them as columns of their own.
 template <typename T>
-static int pack_for(const Apply2DArgs<T>& a) { return apply2d_unpacked<T>(a.L, a.PY, a.var[1]) ? 0 : 1; }
+static int pack_for(const Apply2DArgs<T>& a) { return apply2d_unpacked(a.L) ? 0 : 1; }
 
 template <typename T>
 static Apply2DArgs<T> args2d(const rte_ctx* c);
@@ -222,8 +219,6 @@ template <>
 Apply2DArgs<float> args2d<float>(const rte_ctx* c) {
     Apply2DArgs<float> a{c->nx, c->ny, c->PX, c->PY, c->L, c->C, c->wf, c->wf2, c->Qf, c->twf[0], c->twf[1], c->stream};
     a.twm = c->twmf;
-    a.twy1 = c->twy1f;
-    a.twyh = c->twyhf;
     for (int p = 0; p < 3; ++p) a.var[p] = c->varf[p];
     return a;
 }
@@ -231,7 +226,6 @@ template <>
 Apply2DArgs<double> args2d<double>(const rte_ctx* c) {
     Apply2DArgs<double> a{c->nx, c->ny, c->PX, c->PY, c->L, c->C, c->wd, c->wd2, c->Qd, c->twd[0], c->twd[1], c->stream};
     a.twm = c->twmd;
-    a.twy1 = c->twy1d;
     a.twyh = c->twyhd;
     for (int p = 0; p < 3; ++p) a.var[p] = c->vard[p];
     return a;
@@ -386,7 +380,6 @@ static bool early_a_ok(rte_ctx* c) {
     if (env && env[0] == '0') return false;
     if (!pc_rescale_net_pa_ok(c)) return false;
     const Apply2DArgs<float> a = args2d<float>(c);
-    if (!apply2d_b_corr_ok<float>(c->L, c->PY, a.var[1])) return false;
     if (pc_phi_prepare(c, pack_for(a)) != RTE_OK) return false;
     // the per-channel factors, uploaded again only when the medium changed
     const ChanScale sc = channel_scale(c, APPLY_A);
@@ -450,7 +443,11 @@ static int tune_t(rte_ctx* c, int* var, int reps, bool use_cache) {
     RTE_HIP_TRY(hipEventCreate(&e1));
     int rc = RTE_OK;
     for (int pass = 0; pass < 3 && !rc; ++pass) {
-        const int nv = apply2d_variant_count<T>(pass, c->L, c->PX, c->PY);
+        const int nv = apply2d_tuned_variants<T>(pass, c->L, c->PX);
+        if (nv == 1) {
+            var[pass] = 0;
+            continue;
+        }
         int best = 0;
         float best_ms = 1e30f;
         for (int v = 0; v < nv && !rc; ++v) {
@@ -1003,24 +1000,31 @@ int rte_setup(rte_ctx** out, const rte_grid* g, double mu_a, double mu_s, const 
 
     // twiddles of the grid axes, and of the mode axis when pass B couples the modes by an FFT
     const bool mode_fft = c->dim == 2 && c->L > PASSB_FUSED_MAX_L;
-    // (index 4: the y axis in the radix-32 schedule, for the pass-B variant that uses it; index 5:
-    // length PY/2, for pass B split in halves)
-    const int Ps[6] = {c->PX, c->PY, c->PZ, mode_fft ? mode_fft_len(c->L) : 0, c->PY, c->PY / 2};
-    for (int a = 0; a < 6; ++a) {
-        if (a >= c->dim && !(a == 3 && mode_fft) && !(a >= 4 && c->dim == 2)) continue;
+    const int Ps[4] = {c->PX, c->PY, c->PZ, mode_fft ? mode_fft_len(c->L) : 0};
+    for (int a = 0; a < 4; ++a) {
+        if (a >= c->dim && !(a == 3 && mode_fft)) continue;
         std::vector<double> re, im;
-        twiddles(Ps[a], re, im, a == 4 ? 1 : 0);
+        twiddles(Ps[a], re, im);
         std::vector<cx<double>> td(Ps[a]);
         std::vector<cx<float>> tf(Ps[a]);
         for (int q = 0; q < Ps[a]; ++q) {
             td[q] = mk(re[q], im[q]);
             tf[q] = mk((float)re[q], (float)im[q]);
         }
-        cx<double>*& dd = a < 3 ? c->twd[a] : (a == 3 ? c->twmd : (a == 4 ? c->twy1d : c->twyhd));
-        cx<float>*& ff = a < 3 ? c->twf[a] : (a == 3 ? c->twmf : (a == 4 ? c->twy1f : c->twyhf));
+        cx<double>*& dd = a < 3 ? c->twd[a] : c->twmd;
+        cx<float>*& ff = a < 3 ? c->twf[a] : c->twmf;
         if ((rc = dalloc(&dd, Ps[a])) || (rc = dalloc(&ff, Ps[a]))) { free_ctx(c); return rc; }
         e = hipMemcpy(dd, td.data(), Ps[a] * sizeof(cx<double>), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(ff, tf.data(), Ps[a] * sizeof(cx<float>), hipMemcpyHostToDevice);
+        if (e != hipSuccess) { free_ctx(c); return set_hip_error(e, "twiddle upload", __FILE__, __LINE__); }
+    }
+    if (c->dim == 2 && apply2d_b_halves<double>(c->L, c->PY)) {
+        std::vector<double> re, im;
+        half_twiddles(c->PY, re, im);
+        std::vector<cx<double>> td(c->PY);
+        for (int q = 0; q < c->PY; ++q) td[q] = mk(re[q], im[q]);
+        if ((rc = dalloc(&c->twyhd, c->PY))) { free_ctx(c); return rc; }
+        e = hipMemcpy(c->twyhd, td.data(), c->PY * sizeof(cx<double>), hipMemcpyHostToDevice);
         if (e != hipSuccess) { free_ctx(c); return set_hip_error(e, "twiddle upload", __FILE__, __LINE__); }
     }
     const bool f32 = prec == RTE_PREC_FP32;
@@ -1055,10 +1059,10 @@ int rte_setup(rte_ctx** out, const rte_grid* g, double mu_a, double mu_s, const 
         const size_t nt = (size_t)nb * c->C * NK * c->ny;
         const size_t nt2 = (size_t)nb * c->C * NK * c->PY;
         if ((rc = dalloc(&c->wd, nt))) { free_ctx(c); return rc; }
-        if (apply2d_needs_work2<double>(c->L, c->PY) && (rc = dalloc(&c->wd2, nt2))) { free_ctx(c); return rc; }
+        if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wd2, nt2))) { free_ctx(c); return rc; }
         if (f32) {
             if ((rc = dalloc(&c->wf, nt))) { free_ctx(c); return rc; }
-            if (apply2d_needs_work2<float>(c->L, c->PY) && (rc = dalloc(&c->wf2, nt2))) { free_ctx(c); return rc; }
+            if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wf2, nt2))) { free_ctx(c); return rc; }
         }
     } else {
         const size_t n1 = (size_t)nb * c->C * c->nz * NK * c->ny;

@@ -8,7 +8,8 @@ namespace rte {
 
 double self_cell_2d(int m, double h, double mu_t);
 double self_cell_3d(double h, double mu_t);
-void twiddles(int P, std::vector<double>& re, std::vector<double>& im, int sched = 0);
+void twiddles(int P, std::vector<double>& re, std::vector<double>& im);
+void half_twiddles(int P, std::vector<double>& re, std::vector<double>& im);
 
 struct SpectraArgs2D {
     int nx, ny, PX, PY, L;

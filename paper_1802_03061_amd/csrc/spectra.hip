@@ -127,33 +127,36 @@ void self_cell_3d_pairs(int L, double h, double mu_t, std::vector<double>& c) {
                 }
 }
 
-// The twiddle table of the length-P LDS FFT (fft.h) with radix schedule `sched`, in its per-stage
-// layout: for every Stockham stage after the first (sub-transform length NS, radix R), the factors
-// exp(-2 pi i k r / (NS R)) for k < NS, r = 1..R-1 at stage_tw_offset(P, NS, sched) + k (R - 1) + (r - 1).  The angle is computed
-// in long double from the exact integer fraction (k r mod NS R) / (NS R), rounded to FP64, with
+// exp(-2 pi i q / S), q in 0 .. S - 1.
+static void unit_root(int q, int S, double& cr, double& ci) {
+    const long double pi = 3.141592653589793238462643383279502884L;
+    if (q == 0) { cr = 1; ci = 0; }
+    else if (4 * q == S) { cr = 0; ci = -1; }
+    else if (2 * q == S) { cr = -1; ci = 0; }
+    else if (4 * q == 3 * S) { cr = 0; ci = 1; }
+    else {
+        const long double ang = -2.0L * pi * (long double)q / (long double)S;
+        cr = (double)std::cos(ang);
+        ci = (double)std::sin(ang);
+    }
+}
+
+// The twiddle table of the length-P LDS FFT (fft.h), in its per-stage layout: for every Stockham stage after the first (sub-transform length NS, radix R), the factors
+// exp(-2 pi i k r / (NS R)) for k < NS, r = 1..R-1 at stage_tw_offset(P, NS) + k (R - 1) + (r - 1).  The angle is computed in long double from the exact integer fraction (k r mod NS R) / (NS R), rounded to FP64, with
 // the quarter points exact.
-void twiddles(int P, std::vector<double>& re, std::vector<double>& im, int sched) {
+void twiddles(int P, std::vector<double>& re, std::vector<double>& im) {
     re.assign(P, 0.0);
     im.assign(P, 0.0);
-    const long double pi = 3.141592653589793238462643383279502884L;
     int ns = 1, off = 0;
     while (ns < P) {
-        const int R = fft_radix(P, ns, sched);
+        const int R = fft_radix(P, ns);
         if (ns > 1) {
             const int S = ns * R;
             for (int k = 0; k < ns; ++k)
                 for (int r = 1; r < R; ++r) {
                     const int q = (k * r) % S;
                     double cr, ci;
-                    if (4 * q == 0) { cr = 1; ci = 0; }
-                    else if (4 * q == S) { cr = 0; ci = -1; }
-                    else if (4 * q == 2 * S) { cr = -1; ci = 0; }
-                    else if (4 * q == 3 * S) { cr = 0; ci = 1; }
-                    else {
-                        const long double ang = -2.0L * pi * (long double)q / (long double)S;
-                        cr = (double)std::cos(ang);
-                        ci = (double)std::sin(ang);
-                    }
+                    unit_root(q, S, cr, ci);
                     re[off + k * (R - 1) + (r - 1)] = cr;
                     im[off + k * (R - 1) + (r - 1)] = ci;
                 }
@@ -161,6 +164,15 @@ void twiddles(int P, std::vector<double>& re, std::vector<double>& im, int sched
         }
         ns *= R;
     }
+}
+
+// For a transform of length P run in two halves: the stage twiddles of length P/2, then
+// exp(-2 pi i n / P) for n < P/2.
+void half_twiddles(int P, std::vector<double>& re, std::vector<double>& im) {
+    twiddles(P / 2, re, im);
+    re.resize(P);
+    im.resize(P);
+    for (int n = 0; n < P / 2; ++n) unit_root(n, P, re[P / 2 + n], im[P / 2 + n]);
 }
 
 // ------------------------------------------------------------------ device kernels -------------
