@@ -3,7 +3,7 @@
     python -m paper_1802_03061_amd.build [-j N]
 
 Every translation unit is compiled in parallel into _build/, then linked into
-paper_1802_03061_amd/librte.so.  Pass B is compiled once per L = 0..8.
+paper_1802_03061_amd/librte.so.  Pass B is compiled once per L = 0..16.
 """
 from __future__ import annotations
 
@@ -30,10 +30,10 @@ SOURCES = ["apply2d.hip", "apply2d_bm.hip", "apply3d.hip", "spectra.hip", "krylo
 
 
 def units():
-    out = [(s, os.path.splitext(s)[0] + ".o", []) for s in SOURCES]
-    for L in range(9):
+    out = []
+    for L in reversed(range(17)):   # the longest first
         out.append(("apply2d_b.hip", f"apply2d_b_L{L}.o", [f"-DRTE_PASSB_L={L}"]))
-    return out
+    return out + [(s, os.path.splitext(s)[0] + ".o", []) for s in SOURCES]
 
 
 def compile_one(src, obj, extra):

@@ -29,7 +29,7 @@ template <typename T>
 struct Apply2DArgs {
     int nx, ny, PX, PY, L, C;
     cx<T>* work;               // work buffer [nbatch][C][NKS][ny], NKS = pack ? PX/2 : PX/2+1
-    cx<T>* work2;              // L > 8 only: [nbatch][C][NKS][PY] (may be null otherwise)
+    cx<T>* work2;              // split form only: [nbatch][C][NKS][PY] (may be null otherwise)
     const cx<T>* Q;            // quarter spectra [2L+1][PX/2+1][PY/2+1], scaled by 1/(PX PY)
     const cx<T>* twx;          // exp(-2 pi i q/PX), q < PX
     const cx<T>* twy;          // exp(-2 pi i q/PY), q < PY
@@ -54,15 +54,15 @@ struct Apply2DArgs {
 
 // Kernel variants (same arithmetic, different tiling; results agree up to rounding):
 //   passes A and C (PX >= 128): row tiles of 16, 8, 32 or 4 rows (FP32) / 8, 4, 16 or 2 rows (FP64)
-//   pass B, L <= 8: one kernel per shape (passb_wave.h).  The variant numbers of the forms it
-//   replaced stay valid and select it.
-//   pass B, L > 8: the coupling as a mode-axis FFT or as a register-blocked direct sum
+//   pass B: one kernel per shape (passb_wave.h).  The variant numbers of the forms it replaced stay
+//   valid and select it.
+//   pass B in split form: the coupling as a mode-axis FFT or as a register-blocked direct sum
 // Number of variants of `pass` (0 = A, 1 = B, 2 = C) for this shape and precision, and how many of
 // them are kernels of their own (the tuner times those).
 template <typename T>
 int apply2d_variant_count(int pass, int L, int PX, int PY);
 template <typename T>
-int apply2d_tuned_variants(int pass, int L, int PX);
+int apply2d_tuned_variants(int pass, int L, int PX, int PY);
 
 // One isotropic problem (C = 1) of a batched apply.  Pass A reads in (+ j * stride when jin is
 // set, j read from the device), pass C writes out (+ (j + 1) * stride when jout is set) and reads
@@ -118,10 +118,12 @@ template <typename T, typename TV>
 int apply2d_pass_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, int nbatch);
 template <typename T>
 int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch);
-// True when pass B needs the work2 buffer, and when it takes the work buffer unpacked
-// (x-frequencies 0 and PX/2 in columns of their own instead of sharing column 0): L > 8.
-bool apply2d_needs_work2(int L);
-bool apply2d_unpacked(int L);
+// Whether pass B runs in split form (a full-length buffer, work2, between its transforms and its
+// coupling, and the work buffer unpacked: x-frequencies 0 and PX/2 in columns of their own instead
+// of sharing column 0): more than 17 modes, except in FP32 up to 33 modes at padded y <= 512, whose
+// column spectra fit LDS.  At 256^2, L = 16 in FP32 the split form took 83 us, the other 31 us.
+template <typename T>
+bool apply2d_split(int L, int PY);
 // Whether pass B runs the y-transforms in two halves (twyh needed).
 template <typename T>
 bool apply2d_b_halves(int L, int PY);

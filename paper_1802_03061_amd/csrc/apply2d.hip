@@ -312,14 +312,19 @@ int apply2d_variant_count(int pass, int L, int PX, int PY) {
 template int apply2d_variant_count<float>(int, int, int, int);
 template int apply2d_variant_count<double>(int, int, int, int);
 template <typename T>
-int apply2d_tuned_variants(int pass, int L, int PX) {
-    return pass == 1 && L <= PASSB_FUSED_MAX_L ? 1 : apply2d_variant_count<T>(pass, L, PX, 16);
+int apply2d_tuned_variants(int pass, int L, int PX, int PY) {
+    return pass == 1 && !apply2d_split<T>(L, PY) ? 1 : apply2d_variant_count<T>(pass, L, PX, PY);
 }
-template int apply2d_tuned_variants<float>(int, int, int);
-template int apply2d_tuned_variants<double>(int, int, int);
+template int apply2d_tuned_variants<float>(int, int, int, int);
+template int apply2d_tuned_variants<double>(int, int, int, int);
 
-bool apply2d_needs_work2(int L) { return L > PASSB_FUSED_MAX_L; }
-bool apply2d_unpacked(int L) { return L > PASSB_FUSED_MAX_L; }
+template <typename T>
+bool apply2d_split(int L, int PY) {
+    if (L <= PASSB_FUSED_MAX_L) return false;
+    return !(sizeof(T) == 4 && L <= PASSB_FUSED_MAX_L_F32 && PY <= PASSB_FUSED_MAX_PY);
+}
+template bool apply2d_split<float>(int, int);
+template bool apply2d_split<double>(int, int);
 template <typename T>
 bool apply2d_b_halves(int L, int PY) {
     return L <= PASSB_FUSED_MAX_L && L >= 2 && (2 * L + 1) * (long)padded(PY) * (long)sizeof(cx<T>) > 160 * 1024;
@@ -344,6 +349,20 @@ int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch) {
         case 6: return pass_b_L6<T>(a, nbatch);
         case 7: return pass_b_L7<T>(a, nbatch);
         case 8: return pass_b_L8<T>(a, nbatch);
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (!apply2d_split<T>(a.L, a.PY)) {
+            switch (a.L) {
+                case 9: return pass_b_L9<T>(a, nbatch);
+                case 10: return pass_b_L10<T>(a, nbatch);
+                case 11: return pass_b_L11<T>(a, nbatch);
+                case 12: return pass_b_L12<T>(a, nbatch);
+                case 13: return pass_b_L13<T>(a, nbatch);
+                case 14: return pass_b_L14<T>(a, nbatch);
+                case 15: return pass_b_L15<T>(a, nbatch);
+                case 16: return pass_b_L16<T>(a, nbatch);
+            }
+        }
     }
     return pass_b_large<T>(a, nbatch);
 }

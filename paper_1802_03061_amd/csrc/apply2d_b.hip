@@ -1,4 +1,4 @@
-// Pass B of the 2D apply for one value of L (this file is compiled once per L = 0..8 with
+// Pass B of the 2D apply for one value of L (this file is compiled once per L = 0..16 with
 // -DRTE_PASSB_L=<L>): FFT along y of every channel, per-frequency mode coupling with the kernel
 // spectra, inverse FFT along y (Sec. 3.3.1: the kernel depends on x - y and on k' - k only, so
 // the convolution over y and the sum over k' meet at each frequency).  The kernels are in
@@ -22,7 +22,8 @@
 namespace rte {
 
 // A block keeps the spectra of its columns in LDS (k_pass_b_wave) wherever they fit 160 KB; FP64
-// with L > 4 at padded y = 1024 runs each column in two halves (k_pass_b_half).  Pass B at 512^2,
+// with L > 4 at padded y = 1024 runs each column in two halves (k_pass_b_half).  L = 9..16 come here in FP32
+// up to padded y = 512 (apply2d_split).  Pass B at 512^2,
 // L = 8: FP32 38.5 us, where the form it replaces (block-wide FFT stages, complex coupling) took
 // 57-60 us; FP64 see k_pass_b_half.
 template <typename T, int PY>
@@ -32,11 +33,14 @@ static int launch_py(const Apply2DArgs<T>& a, int nbatch) {
     const int nkq = a.PX / 2 + 1, nkx = a.PX / 2;
     if constexpr (wave_fits<T, PY, L>()) {
         launch_wave<T, PY, L>(a, nbatch, nkx, nkq);
-    } else {
+        return 0;
+    } else if constexpr (L <= 8) {
         if (!a.twyh) return -5;
         launch_half<T, PY, L, 8>(a, nbatch, nkx, nkq);
+        return 0;
+    } else {
+        return -1;   // apply2d_split: not routed here
     }
-    return 0;
 }
 
 template <typename T>
@@ -59,10 +63,12 @@ template <>
 int RTE_CAT(pass_b_L, RTE_PASSB_L)<float>(const Apply2DArgs<float>& a, int nbatch) {
     return launch_pass_b_impl<float>(a, nbatch);
 }
+#if RTE_PASSB_L <= 8
 template <>
 int RTE_CAT(pass_b_L, RTE_PASSB_L)<double>(const Apply2DArgs<double>& a, int nbatch) {
     return launch_pass_b_impl<double>(a, nbatch);
 }
+#endif
 
 #if RTE_PASSB_L == 0
 // ---- batched isotropic form: one block per (problem, group of NCOL columns) ----

@@ -20,7 +20,9 @@
 // units busy 58 % of the time; this one takes 39 us with 15.9M (the column traffic alone: 13 us).
 // Of a column's time at a CU about 40 % is the coupling and 40 % the transforms.  Twiddles are read
 // from memory (L1-resident): staging them in LDS cost each block a memory latency and took 0.5 us
-// longer at 256^2.  At 256^2, L = 8 the FP64 apply went from 72 to 42 us.
+// longer at 256^2.  At 256^2, L = 8 the FP64 apply went from 72 to 42 us.  With 33 modes at
+// 256^2 in FP32 pass B takes 31 us, where forward transforms, a register-blocked complex coupling and
+// inverse transforms through a full-length buffer took 83 us.
 #pragma once
 #include "apply2d.h"
 #include "fft.h"
@@ -748,15 +750,16 @@ constexpr bool wave_fits() {
 // Waves per block: one per sequence, and enough (up to 8) that a thread couples one frequency: at
 // 32^2, L = 0 in FP64 the launch with one wave took 3 us longer than with four, each of a thread's
 // four frequencies waiting for its kernel entry.  At most 16; the coupling's live values set lower
-// limits: 17 channels in FP32 take 137 registers (12 waves leave 168), 11 and more in FP64 up to 244
-// (8 waves leave 256).
+// limits: 17 to 21 channels in FP32 take 137 to 150 registers (12 waves leave 168), more up to 230, and
+// 11 and more in FP64 up to 244 (8 waves leave 256).
 template <typename T, int PY, int L>
 constexpr int wave_count() {
     constexpr int SPW = 64 / wave_lanes(PY);
     constexpr int W = (wave_ncol<L>() * (2 * L + 1) + SPW - 1) / SPW;
     constexpr int F = wave_ncol<L>() * PY / 64, F8 = F > 8 ? 8 : (F < 1 ? 1 : F);
     constexpr int N = W > F8 ? W : F8;
-    return sizeof(T) == 8 && L > 4 ? (N > 8 ? 8 : N) : (N > 16 ? 12 : N);
+    constexpr int top = (sizeof(T) == 8 && L > 4) || L > 10 ? 8 : (L >= 8 ? 12 : 16);
+    return N > top ? top : N;
 }
 
 // Grid of a looping kernel: as many blocks as the device holds at once, at most one per item.
@@ -784,7 +787,7 @@ inline void launch_wave_nw(const Apply2DArgs<T>& a, int nbatch, int nkx, int nkq
 template <typename T, int PY, int L>
 inline void launch_wave(const Apply2DArgs<T>& a, int nbatch, int nkx, int nkq) {
     constexpr int NW = wave_count<T, PY, L>();
-    if constexpr (sizeof(T) == 4) {
+    if constexpr (sizeof(T) == 4 && L <= 8) {   // the preconditioner takes up to 17 modes
         if (a.bcorr.y) return launch_wave_nw<T, PY, L, NW, true>(a, nbatch, nkx, nkq);
     }
     launch_wave_nw<T, PY, L, NW, false>(a, nbatch, nkx, nkq);

@@ -172,10 +172,10 @@ static int ensure_work(rte_ctx* c, int nb) {
         const size_t nt = (size_t)nb * c->C * NK * c->ny;
         const size_t nt2 = (size_t)nb * c->C * NK * c->PY;
         if ((rc = dalloc(&c->wd, nt))) return rc;
-        if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wd2, nt2))) return rc;
+        if (apply2d_split<double>(c->L, c->PY) && (rc = dalloc(&c->wd2, nt2))) return rc;
         if (f32) {
             if ((rc = dalloc(&c->wf, nt))) return rc;
-            if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wf2, nt2))) return rc;
+            if (apply2d_split<float>(c->L, c->PY) && (rc = dalloc(&c->wf2, nt2))) return rc;
         }
     } else {
         const size_t n1 = (size_t)nb * c->C * c->nz * NK * c->ny;
@@ -208,10 +208,10 @@ static ChanScale3 channel_scale3(const rte_ctx* c, int mode) {
     return s;
 }
 
-// Column 0 of the 2D work buffer packs the x-frequencies 0 and PX/2 (two real sequences) except
-// with more than 17 modes, whose pass B takes them as columns of their own.
+// Column 0 of the 2D work buffer packs the x-frequencies 0 and PX/2 (two real sequences) except in
+// pass B's split form.
 template <typename T>
-static int pack_for(const Apply2DArgs<T>& a) { return apply2d_unpacked(a.L) ? 0 : 1; }
+static int pack_for(const Apply2DArgs<T>& a) { return apply2d_split<T>(a.L, a.PY) ? 0 : 1; }
 
 template <typename T>
 static Apply2DArgs<T> args2d(const rte_ctx* c);
@@ -443,7 +443,7 @@ static int tune_t(rte_ctx* c, int* var, int reps, bool use_cache) {
     RTE_HIP_TRY(hipEventCreate(&e1));
     int rc = RTE_OK;
     for (int pass = 0; pass < 3 && !rc; ++pass) {
-        const int nv = apply2d_tuned_variants<T>(pass, c->L, c->PX);
+        const int nv = apply2d_tuned_variants<T>(pass, c->L, c->PX, c->PY);
         if (nv == 1) {
             var[pass] = 0;
             continue;
@@ -1059,10 +1059,10 @@ int rte_setup(rte_ctx** out, const rte_grid* g, double mu_a, double mu_s, const 
         const size_t nt = (size_t)nb * c->C * NK * c->ny;
         const size_t nt2 = (size_t)nb * c->C * NK * c->PY;
         if ((rc = dalloc(&c->wd, nt))) { free_ctx(c); return rc; }
-        if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wd2, nt2))) { free_ctx(c); return rc; }
+        if (apply2d_split<double>(c->L, c->PY) && (rc = dalloc(&c->wd2, nt2))) { free_ctx(c); return rc; }
         if (f32) {
             if ((rc = dalloc(&c->wf, nt))) { free_ctx(c); return rc; }
-            if (apply2d_needs_work2(c->L) && (rc = dalloc(&c->wf2, nt2))) { free_ctx(c); return rc; }
+            if (apply2d_split<float>(c->L, c->PY) && (rc = dalloc(&c->wf2, nt2))) { free_ctx(c); return rc; }
         }
     } else {
         const size_t n1 = (size_t)nb * c->C * c->nz * NK * c->ny;

@@ -1,5 +1,5 @@
 """Pass B with wave-private transforms and the real coupling: every padded y-length 16..1024 (whole and
-ragged), L = 0..8, column groups with a dead column, columns in two halves (FP64, padded y = 1024,
+ragged), L = 0..17 (FP32 up to 16 here, the others in split form), column groups with a dead column, columns in two halves (FP64, padded y = 1024,
 L >= 5), more columns than blocks on the chip, and the single-channel right-hand side, against the
 oracle's FP64 FFT apply.  Tolerances are the apply's: 1e-6 (FP32, a factor of about 5 over the
 rounding of the transforms' stages) and 1e-12 (FP64)."""
@@ -24,7 +24,8 @@ def rte():
 
 CASES = [(5, 2, 0), (9, 8, 3), (3, 9, 1), (13, 16, 8), (7, 17, 2), (17, 32, 5), (6, 33, 7), (11, 64, 1), (5, 65, 8),
          (9, 128, 4), (6, 129, 6), (7, 256, 8), (4, 257, 5), (9, 300, 8), (6, 511, 6), (5, 512, 7), (3, 512, 8),
-         (5, 400, 4), (3, 512, 0), (512, 20, 8), (300, 257, 5)]
+         (5, 400, 4), (3, 512, 0), (512, 20, 8), (300, 257, 5),
+         (6, 256, 16), (5, 130, 16), (9, 40, 9), (4, 200, 12), (300, 10, 13), (7, 8, 11), (3, 257, 16), (5, 64, 17)]
 
 
 @pytest.mark.timeout(300)
