@@ -14,8 +14,10 @@
 //   E  inverse x-FFT (complex-to-real), crop, y = u - v / v / residual           (2D pass C)
 // Each pass reads and writes HBM in 128-byte runs: B and D move tiles of TZ consecutive z.
 #include "apply3d.h"
-#include "fft.h"
+#include "fft_wave.h"
 #include "sh3d.h"
+
+#include <algorithm>
 
 namespace rte {
 
@@ -45,54 +47,63 @@ __global__ __launch_bounds__(NTHR) void k_pass3_b(const cx<T>* __restrict__ T1, 
     }
 }
 
-template <typename T, int PZ, int NC, int NTHR>
-__global__ __launch_bounds__(NTHR) void k_pass3_c(cx<T>* __restrict__ T2, const T* __restrict__ Q3,
-                                                  const cx<T>* __restrict__ tw, int nz, int PY, size_t ncol) {
-    constexpr int LD = padded(PZ) + 1;
-    __shared__ cx<T> buf[NC * LD];
-    __shared__ cx<T> tws[PZ];
-    const int tid = threadIdx.x;
-    const size_t c0 = (size_t)blockIdx.x * NC;
+// Isotropic pass C.  Every column is transformed by part of one wave, from its loads to its stores,
+// in an LDS row of its own: no block barrier anywhere.  The spectrum multiplies the last forward
+// stage's registers; its values and the wave's next columns are loaded ahead of the transforms.
+// Bound: HBM.  Between events in FP32 it takes 23.2 us at 128^3 (76 MB) and 121 us at 200^3, where
+// block-wide stages over 8 columns with the multiply between two barriers took 28.2 and 168 us.  (The
+// same transforms in the spherical-harmonic z-pass below, whose coupling needs the barriers anyway,
+// did not change its time.)
+template <typename T, int PZ>
+__global__ __launch_bounds__(384) void k_pass3_c(cx<T>* __restrict__ T2, const T* __restrict__ Q3,
+                                                 const cx<T>* __restrict__ tw, int nz, int PY, int ncol) {
+    constexpr int LN = wave_lanes(PZ);
+    constexpr int SPW = 64 / LN;            // columns a wave runs side by side
+    constexpr int LD = padded(PZ);
+    constexpr int NSL = fft_last_ns(PZ), RL = PZ / NSL, R0 = fft_radix(PZ, 1);
+    using Last = WaveStage<T, PZ, LN, RL, NSL, false>;
+    extern __shared__ __align__(16) double smem_c[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = (threadIdx.x & 63) % LN, sub = (threadIdx.x & 63) / LN;
+    cx<T>* buf = reinterpret_cast<cx<T>*>(smem_c) + (wave * SPW + sub) * LD;
     const int HY = PY / 2 + 1, HZ = PZ / 2 + 1;
-    stage_twiddles<T, PZ, NTHR>(tws, tw, tid);
-    __syncthreads();
-    // entries z >= nz are zero padding; only z < nz are kept after the inverse transform
-    fft_forward_padded<T, PZ, NC, LD, NTHR>(buf, tws, tid, [&](int c, int z) {
-        const size_t col = c0 + c;
-        return (col < ncol && z < nz) ? T2[col * nz + z] : mk((T)0, (T)0);
-    });
-    // spectrum row of each of the block's columns, decoded once (col = kx PY + ky)
-    __shared__ int qrow[NC];
-    if (tid < NC) {
-        const int col = (int)(c0 + tid);
-        const int kx = col / PY, ky = col % PY;
-        const int fy = ky <= PY / 2 ? ky : PY - ky;
-        qrow[tid] = (col < (int)ncol) ? (kx * HY + fy) * HZ : -1;
-    }
-    __syncthreads();
-    // the spectrum values of the thread's entries are loaded first, all in flight together
-    constexpr int PERQ = (NC * PZ + NTHR - 1) / NTHR;
-    T qv[PERQ];
+    const int step = gridDim.x * (blockDim.x / 64) * SPW;
+    int col = (blockIdx.x * (blockDim.x / 64) + wave) * SPW + sub;
+    WaveIn<T, PZ, LN> in;
+    in.load(T2 + (size_t)min(col, ncol - 1) * nz, nz, l);
+    // every lane of a wave runs the same number of rounds: columns past the last are not stored
+    for (int base = col - sub; base < ncol; base += step, col += step) {
+        const int cc = min(col, ncol - 1), kx = cc / PY, ky = cc % PY;
+        const T* q = Q3 + ((size_t)kx * HY + (ky <= PY / 2 ? ky : PY - ky)) * HZ;
+        T qv[Last::ITEMS][RL];
 #pragma unroll
-    for (int u = 0; u < PERQ; ++u) {
-        const int idx = tid + u * NTHR;
-        const int c = idx / PZ, kz = idx % PZ;
-        const int q = ((NC * PZ) % NTHR == 0 || idx < NC * PZ) ? qrow[c] : -1;
-        const int fz = kz <= PZ / 2 ? kz : PZ - kz;
-        qv[u] = q >= 0 ? Q3[(size_t)q + fz] : (T)0;
-    }
+        for (int it = 0; it < Last::ITEMS; ++it)
 #pragma unroll
-    for (int u = 0; u < PERQ; ++u) {
-        const int idx = tid + u * NTHR;
-        const int c = idx / PZ, kz = idx % PZ;
-        if (((NC * PZ) % NTHR == 0 || idx < NC * PZ) && qrow[c] >= 0)
-            buf[c * LD + sw(kz)] = scale(buf[c * LD + sw(kz)], qv[u]);
+            for (int r = 0; r < RL; ++r) {
+                const int kz = (l + it * LN + r * NSL) & (PZ - 1);
+                qv[it][r] = q[kz <= PZ / 2 ? kz : PZ - kz];
+            }
+        in.first_stage(buf, nz, true, l);
+        wave_sync();
+        if constexpr (NSL > 1) {
+            wave_stages<T, PZ, LN, false, R0, NSL>(buf, tw, l);
+            cx<T> v[Last::ITEMS][RL];
+            Last::compute(v, buf, tw, l);
+            wave_sync();
+#pragma unroll
+            for (int it = 0; it < Last::ITEMS; ++it)
+#pragma unroll
+                for (int r = 0; r < RL; ++r) v[it][r] = scale(v[it][r], qv[it][r]);
+            Last::store(v, buf, l);
+        } else if (l == 0) {   // a single stage: lane 0 holds the whole spectrum
+#pragma unroll
+            for (int r = 0; r < RL; ++r) buf[r] = scale(buf[r], qv[0][r]);
+        }
+        wave_sync();
+        if (base + step < ncol) in.load(T2 + (size_t)min(col + step, ncol - 1) * nz, nz, l);
+        wave_inverse<T, PZ, LN>(buf, tw, T2 + (size_t)cc * nz, nz, col < ncol, l);
+        wave_sync();
     }
-    __syncthreads();
-    fft_inverse_cropped<T, PZ, NC, LD, NTHR>(buf, tws, tid, [&](int c, int z, cx<T> v) {
-        const size_t col = c0 + c;
-        if (col < ncol && z < nz) T2[col * nz + z] = v;
-    });
 }
 
 // Degree and reflection parities of the first 16 modes, as compile-time tables (sh3d.h).
@@ -245,20 +256,25 @@ static void launch3_bd(const Apply3DArgs<T>& a, bool inverse) {
     else launch3_bd_tz<T, PY, 8>(a, inverse);
 }
 
-template <typename T, int PZ, int NC>
-static void launch3_c_iso(const Apply3DArgs<T>& a, size_t ncol) {
-    dim3 grid((unsigned)((ncol + NC - 1) / NC));
-    hipLaunchKernelGGL((k_pass3_c<T, PZ, NC, 256>), grid, dim3(256), 0, a.stream, a.T2, a.Q3, a.twz, a.nz, a.PY, ncol);
+// Isotropic pass C with `waves` (2, 4 or 6) waves per block, as many blocks as the device holds at
+// once.
+template <typename T, int PZ>
+static void launch3_c_iso(const Apply3DArgs<T>& a, int ncol, int waves) {
+    constexpr int SPW = 64 / wave_lanes(PZ);
+    const size_t lds = (size_t)waves * SPW * padded(PZ) * sizeof(cx<T>);
+    static const unsigned cap[3] = {resident_blocks(k_pass3_c<T, PZ>, 256, 4 * (lds / waves)),
+                                    resident_blocks(k_pass3_c<T, PZ>, 128, 2 * (lds / waves)),
+                                    resident_blocks(k_pass3_c<T, PZ>, 384, 6 * (lds / waves))};
+    const unsigned need = (unsigned)((ncol + waves * SPW - 1) / (waves * SPW));
+    const unsigned nb = std::min(need, cap[waves == 4 ? 0 : (waves == 2 ? 1 : 2)]);
+    hipLaunchKernelGGL((k_pass3_c<T, PZ>), dim3(nb), dim3(64 * waves), lds, a.stream, a.T2, a.Q3, a.twz, a.nz, a.PY, ncol);
 }
 
 template <typename T, int PZ>
 static int launch3_c(const Apply3DArgs<T>& a) {
     const size_t ncol = (size_t)(a.PX / 2 + 1) * a.PY;
     if (a.C == 1) {
-        constexpr int NC = PZ >= 2048 ? 1 : 2048 / PZ;
-        if (a.var[1] == 1) launch3_c_iso<T, PZ, (NC > 1 ? NC / 2 : 1)>(a, ncol);
-        else if (a.var[1] == 2) launch3_c_iso<T, PZ, 2 * NC>(a, ncol);
-        else launch3_c_iso<T, PZ, NC>(a, ncol);
+        launch3_c_iso<T, PZ>(a, (int)ncol, a.var[1] == 1 ? 2 : (a.var[1] == 2 ? 6 : 4));
         return 0;
     }
     if constexpr (PZ > 256) {
