@@ -44,16 +44,26 @@ constexpr int kpad(int cin) { return (cin * 9 + 7) / 8 * 8; }
 // ------------------------------------------------------------------ convolution (MFMA) --------
 // in [B][CIN][H][W] (times *in_scale if given); Wp [32][KP] bf16; out/preact [B][Cout][H][W].
 // mask (optional, same shape as out): the output is zeroed where mask <= 0.
-template <int CIN>
+// A wave's 32 pixels are one row of 32 or, for images up to 16 wide, two rows of 16 (TW), so that no
+// column of the tile is idle there.  Both operands come from LDS: the weights with a row pitch of
+// KP + 4 (conflict-free 8-byte reads), the input through a table of the K offsets k -> (channel, tap)
+// read 4 at a time.  Every global load of the block (weights, input, mask) is issued before the
+// first use.  Bound by those load latencies: 32 images of 16^2, 32 -> 32 channels took 21 us with the
+// weights read from memory per step, the offsets divided out per value and half the tile idle.
+template <int CIN, int TW>
 __global__ __launch_bounds__(256) void k_conv3x3(const float* __restrict__ in, const unsigned short* __restrict__ Wp,
                                                  const float* __restrict__ bias, int Cout, float* __restrict__ out,
                                                  float* __restrict__ preact, const float* __restrict__ mask, int relu,
                                                  const float* __restrict__ in_scale, int B, int H, int W) {
     constexpr int K = CIN * 9;
     constexpr int KP = kpad(CIN);
-    constexpr int ROWS = 4, TW = 32;
-    __shared__ unsigned short patch[CIN][ROWS + 2][TW + 2];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int RPW = 32 / TW, ROWS = 4 * RPW, PW = TW + 2, PR = ROWS + 2;
+    constexpr int NP = CIN * PR * PW, NL = (NP + 255) / 256;
+    constexpr int WPITCH = KP + 4, NW8 = 32 * KP / 8, NWL = (NW8 + 255) / 256;
+    __shared__ unsigned short patch[NP];
+    __shared__ __align__(16) unsigned short ws[32 * WPITCH];
+    __shared__ __align__(8) unsigned short koff[KP];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + ROWS - 1) / ROWS;
     int bid = blockIdx.x;
     const int tx = bid % tiles_x;
@@ -62,61 +72,86 @@ __global__ __launch_bounds__(256) void k_conv3x3(const float* __restrict__ in, c
     const int b = bid / tiles_y;
     const int x0 = tx * TW, y0 = ty * ROWS;
     const float sc = in_scale ? *in_scale : 1.0f;
-    constexpr int NP = CIN * (ROWS + 2) * (TW + 2);
-    unsigned short* pf = &patch[0][0][0];
-    // loads in batches of 8 so that their latencies overlap, then the conversions
-    for (int base = 0; base < NP; base += 8 * 256) {
-        float v[8];
+    uint4 wv[NWL];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = base + u * 256 + threadIdx.x;
-            const int c = idx / ((ROWS + 2) * (TW + 2));
-            const int rem = idx % ((ROWS + 2) * (TW + 2));
-            const int y = y0 + rem / (TW + 2) - 1, x = x0 + rem % (TW + 2) - 1;
-            const bool in_img = idx < NP && y >= 0 && y < H && x >= 0 && x < W;
-            v[u] = in_img ? in[((size_t)(b * CIN + c) * H + y) * W + x] * sc : 0.f;
-        }
+    for (int u = 0; u < NWL; ++u) {
+        const int q = tid + u * 256;
+        wv[u] = reinterpret_cast<const uint4*>(Wp)[q < NW8 ? q : 0];
+    }
+    float v[NL];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = base + u * 256 + threadIdx.x;
-            if (idx < NP) pf[idx] = f2bf(v[u]);
+    for (int u = 0; u < NL; ++u) {
+        const int idx = u * 256 + tid;
+        const int c = idx / (PR * PW), rem = idx % (PR * PW);
+        const int y = y0 + rem / PW - 1, x = x0 + rem % PW - 1;
+        const bool ok = idx < NP && y >= 0 && y < H && x >= 0 && x < W;
+        v[u] = in[ok ? ((size_t)(b * CIN + c) * H + y) * W + x : 0];
+    }
+    const int j = lane & 31;           // pixel of the tile
+    const int yl = wave * RPW + j / TW, xl = j % TW;
+    const int x = x0 + xl, y = y0 + yl;
+    const bool inside = x < W && y < H;
+    auto chan = [&](int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };   // output channel of acc[r]
+    float mk[16], bs[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = chan(r);
+        mk[r] = mask ? mask[inside && i < Cout ? ((size_t)(b * Cout + i) * H + y) * W + x : 0] : 1.f;
+        bs[r] = bias ? bias[i < Cout ? i : 0] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < NWL; ++u) {
+        const int q = tid + u * 256;
+        if (q < NW8) {
+            unsigned short* d = ws + (q / (KP / 8)) * WPITCH + (q % (KP / 8)) * 8;   // 8-byte aligned
+            *reinterpret_cast<uint2*>(d) = make_uint2(wv[u].x, wv[u].y);
+            *reinterpret_cast<uint2*>(d + 4) = make_uint2(wv[u].z, wv[u].w);
         }
+    }
+    for (int k = tid; k < KP; k += 256)
+        koff[k] = k < K ? (unsigned short)((k / 9) * PR * PW + ((k % 9) / 3) * PW + k % 3) : 0;
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+        const int idx = u * 256 + tid;
+        const int rem = idx % (PR * PW);
+        const int yy = y0 + rem / PW - 1, xx = x0 + rem % PW - 1;
+        const bool ok = yy >= 0 && yy < H && xx >= 0 && xx < W;
+        if (idx < NP) patch[idx] = f2bf(ok ? v[u] * sc : 0.f);
     }
     __syncthreads();
     f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const int ai = lane & 31;          // A row (output channel) held by this lane
     const int kq = (lane >> 5) * 4;    // K offset of this lane within a step of 8
-    const int j = lane & 31;           // pixel column within the tile
-#pragma unroll 4
+    const unsigned short* wa = ws + (lane & 31) * WPITCH + kq;   // A row: output channel lane & 31
+    const unsigned short* px = patch + yl * PW + xl;
+#pragma unroll 6
     for (int kb = 0; kb < KP / 8; ++kb) {
-        const bf16x4 a = *reinterpret_cast<const bf16x4*>(Wp + (size_t)ai * KP + kb * 8 + kq);
+        const bf16x4 a = *reinterpret_cast<const bf16x4*>(wa + kb * 8);
+        const ushort4 o = *reinterpret_cast<const ushort4*>(koff + kb * 8 + kq);
         bf16x4 bv;
+        bv[0] = (short)px[o.x];
+        bv[1] = (short)px[o.y];
+        bv[2] = (short)px[o.z];
+        bv[3] = (short)px[o.w];
+        if (K % 8 != 0 && kb == KP / 8 - 1) {   // past K: zero (the weights there are zero too)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int k = kb * 8 + kq + r;
-            unsigned short val = 0;
-            if (k < K) {
-                const int c = k / 9, t = k % 9;
-                val = patch[c][wave + t / 3][j + t % 3];
-            }
-            bv[r] = (short)val;
+            for (int r = 0; r < 4; ++r)
+                if (kb * 8 + kq + r >= K) bv[r] = 0;
         }
         acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, bv, acc, 0, 0, 0);
     }
-    const int x = x0 + j, y = y0 + wave;
-    if (x < W && y < H) {
+    if (inside) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);   // output channel of acc[r]
+            const int i = chan(r);
             if (i < Cout) {
                 const size_t o = ((size_t)(b * Cout + i) * H + y) * W + x;
-                float v = acc[r] + (bias ? bias[i] : 0.f);
-                if (preact) preact[o] = v;
-                if (mask && !(mask[o] > 0.f)) v = 0.f;
-                if (relu) v = fmaxf(v, 0.f);
-                out[o] = v;
+                float z = acc[r] + bs[r];
+                if (preact) preact[o] = z;
+                if (!(mk[r] > 0.f)) z = 0.f;
+                if (relu) z = fmaxf(z, 0.f);
+                out[o] = z;
             }
         }
     }
@@ -129,7 +164,10 @@ __global__ __launch_bounds__(256) void k_conv3x3(const float* __restrict__ in, c
 // stages the tile's input with its halo and the output gradient in LDS as BF16, and its wave w
 // accumulates the 32-column tile kt = 4 group + w of G over the tile's pixels, 8 at a time.  Each
 // block writes its 32 x 32 sums to part[tile][32][NKT*32]; k_wgrad_reduce adds the tiles in order.
-// The staging loads are issued in batches of 8 so that their latencies overlap.
+// The staging loads are issued in batches of 16 so that their latencies overlap; the staged output
+// gradient has a row pitch of 260 (its 8-byte reads over 32 rows hit different banks; with 256 all
+// of them hit one).  Small batches launch every layer at once (blockIdx.z): 32 images of 16^2, 5
+// layers took 5 x (19.6 + 4.8) us one layer after another, most of it those bank conflicts.
 constexpr int WG_ROWS = 8, WG_TW = 32, WG_MAXCIN = 32;
 
 __host__ __device__ constexpr int wgrad_ktiles(int cin) { return (cin * 9 + 1 + 31) / 32; }
@@ -139,11 +177,23 @@ __host__ __device__ inline int wgrad_tiles(int B, int H, int W) {
     return B * ((H + rows - 1) / rows) * ((W + tw - 1) / tw);
 }
 
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(const float* __restrict__ x, const float* __restrict__ gy,
-                                                       float* __restrict__ part, int B, int Cin, int Cout, int H,
-                                                       int W) {
+constexpr int NN_MAXL = 8;   // layers of a network
+struct WgradArgs {           // per layer: input, output gradient, shape, offsets into part and g
+    const float* x[NN_MAXL];
+    const float* gy[NN_MAXL];
+    int cin[NN_MAXL], cout[NN_MAXL];
+    size_t part[NN_MAXL], woff[NN_MAXL], boff[NN_MAXL];
+};
+constexpr int WG_GP = 260;
+
+__global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgradArgs A, float* __restrict__ partb, int B, int H, int W) {
     __shared__ unsigned short xs[WG_MAXCIN * (WG_ROWS + 2) * (WG_TW + 2)];
-    __shared__ __align__(16) unsigned short gs[32 * 256];
+    __shared__ __align__(16) unsigned short gs[32 * WG_GP];
+    const int Cin = A.cin[blockIdx.z], Cout = A.cout[blockIdx.z];
+    const float* __restrict__ x = A.x[blockIdx.z];
+    const float* __restrict__ gy = A.gy[blockIdx.z];
+    float* __restrict__ part = partb + A.part[blockIdx.z];
+    if ((int)blockIdx.y * 4 >= wgrad_ktiles(Cin)) return;   // the whole block
     const int TW = wgrad_tw(W), ROWS = 256 / TW, PW = TW + 2, PH = ROWS + 2;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int NKT = wgrad_ktiles(Cin), K = Cin * 9;
@@ -152,35 +202,39 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(const float* __restrict__
     const int tile = blockIdx.x;
     const int tx = tile % tiles_x, ty = (tile / tiles_x) % tiles_y, b = tile / (tiles_x * tiles_y);
     const int x0 = tx * TW, y0 = ty * ROWS;
-    const int NX = Cin * PH * PW, NG = 32 * 256;
-    for (int base = 0; base < NX; base += 8 * 256) {
-        float v[8];
+    const int NX = Cin * PH * PW;
+    constexpr int U = 16;
+    for (int base = 0; base < NX; base += U * 256) {
+        float v[U];
+        bool in[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int idx = base + u * 256 + threadIdx.x;
             const int c = idx / (PH * PW), rem = idx % (PH * PW);
             const int yy = y0 + rem / PW - 1, xx = x0 + rem % PW - 1;
-            const bool in = idx < NX && yy >= 0 && yy < H && xx >= 0 && xx < W;
-            v[u] = in ? x[((size_t)(b * Cin + c) * H + yy) * W + xx] : 0.f;
+            in[u] = idx < NX && yy >= 0 && yy < H && xx >= 0 && xx < W;
+            v[u] = x[in[u] ? ((size_t)(b * Cin + c) * H + yy) * W + xx : 0];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int idx = base + u * 256 + threadIdx.x;
-            if (idx < NX) xs[idx] = f2bf(v[u]);
+            if (idx < NX) xs[idx] = f2bf(in[u] ? v[u] : 0.f);
         }
     }
+    {
+        const int pr = threadIdx.x, yy = y0 + pr / TW, xx = x0 + pr % TW;
+        const bool px = yy < H && xx < W;
 #pragma unroll
-    for (int base = 0; base < NG; base += 8 * 256) {
-        float v[8];
+        for (int base = 0; base < 32; base += U) {
+            float v[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = base + u * 256 + threadIdx.x;
-            const int o = idx / 256, pr = idx % 256;
-            const int yy = y0 + pr / TW, xx = x0 + pr % TW;
-            v[u] = (o < Cout && yy < H && xx < W) ? gy[((size_t)(b * Cout + o) * H + yy) * W + xx] : 0.f;
+            for (int u = 0; u < U; ++u) {
+                const int o = base + u;
+                v[u] = gy[px && o < Cout ? ((size_t)(b * Cout + o) * H + yy) * W + xx : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) gs[(base + u) * WG_GP + pr] = f2bf(px && base + u < Cout ? v[u] : 0.f);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) gs[base + u * 256 + threadIdx.x] = f2bf(v[u]);
     }
     __syncthreads();
     if (kt >= NKT) return;
@@ -196,7 +250,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(const float* __restrict__
 #pragma unroll 4
     for (int step = 0; step < 32; ++step) {
         const int row = step / spr, cg = (step % spr) * 8 + 4 * h;
-        const bf16x4 a = *reinterpret_cast<const bf16x4*>(gs + li * 256 + row * TW + cg);
+        const bf16x4 a = *reinterpret_cast<const bf16x4*>(gs + li * WG_GP + row * TW + cg);
         bf16x4 bv;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -212,14 +266,16 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(const float* __restrict__
 }
 
 // gW[o][k] = sum over tiles of part[tile][o][k] (k < Cin*9, the layout of W[o][c][t]); gb[o] from
-// the ones column k = Cin*9.  Eight independent loads per step, added in tile order.
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int ntiles, int Cin, int Cout,
-                                                      float* __restrict__ gW, float* __restrict__ gb) {
+// the ones column k = Cin*9, zero for a network without biases; layer blockIdx.y, into g and, if
+// given, into a second copy.  Eight independent loads per step, added in tile order.
+__global__ __launch_bounds__(256) void k_wgrad_reduce(WgradArgs A, const float* __restrict__ partb, int ntiles,
+                                                      int use_bias, float* __restrict__ grad, float* __restrict__ copy) {
+    const int Cin = A.cin[blockIdx.y], Cout = A.cout[blockIdx.y];
     const int K = Cin * 9, KT32 = wgrad_ktiles(Cin) * 32;
     const int idx = blockIdx.x * 256 + threadIdx.x;
     if (idx >= Cout * (K + 1)) return;
     const int o = idx / (K + 1), k = idx % (K + 1);
-    const float* p = part + (size_t)o * KT32 + k;
+    const float* p = partb + A.part[blockIdx.y] + (size_t)o * KT32 + k;
     const size_t st = (size_t)32 * KT32;
     float s = 0.f;
     int g = 0;
@@ -231,8 +287,10 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
         for (int u = 0; u < 8; ++u) s += v[u];
     }
     for (; g < ntiles; ++g) s += p[(size_t)g * st];
-    if (k < K) gW[(size_t)o * K + k] = s;
-    else if (gb) gb[o] = s;
+    if (k == K && !use_bias) s = 0.f;
+    const size_t at = k < K ? A.woff[blockIdx.y] + (size_t)o * K + k : A.boff[blockIdx.y] + o;
+    grad[at] = s;
+    if (copy) copy[at] = s;
 }
 
 // diff = y - t; gout = 2 w_b diff / B; lossb[b] = w_b ||diff||^2 / B.  One block per sample.
@@ -243,11 +301,24 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ y, const
     const int b = blockIdx.x;
     const float wb = w[b];
     double s = 0.0;
-    for (int i = threadIdx.x; i < per; i += 256) {
-        const size_t o = (size_t)b * per + i;
-        const float d = y[o] - t[o];
-        s += (double)d * d;
-        gout[o] = 2.f * wb * d / (float)B;
+    for (int i0 = threadIdx.x; i0 < per; i0 += 8 * 256) {   // 8 elements a step, their loads first
+        float yv[8], tv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * 256;
+            const size_t o = (size_t)b * per + (i < per ? i : 0);
+            yv[u] = y[o];
+            tv[u] = t[o];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * 256;
+            if (i < per) {
+                const float d = yv[u] - tv[u];
+                s += (double)d * d;
+                gout[(size_t)b * per + i] = 2.f * wb * d / (float)B;
+            }
+        }
     }
     for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
@@ -269,8 +340,17 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float
 
 // Forward pack: Wf[i][k] = W[i][c][t] (k = c*9 + t) for i < Cout, zero elsewhere (32 x KP(Cin)).
 // Backward pack: Wb[c][k'] = W[o][c][8 - t] (k' = o*9 + t) for c < Cin (32 x KP(Cout)).
-__global__ void k_pack(const float* __restrict__ W, int Cin, int Cout, unsigned short* __restrict__ Wf,
-                       unsigned short* __restrict__ Wb) {
+// Layer blockIdx.y.
+struct PackArgs {
+    int cin[NN_MAXL], cout[NN_MAXL];
+    size_t woff[NN_MAXL], pf[NN_MAXL], pb[NN_MAXL];
+};
+__global__ void k_pack(const float* __restrict__ params, PackArgs A, unsigned short* __restrict__ wf,
+                       unsigned short* __restrict__ wb) {
+    const int Cin = A.cin[blockIdx.y], Cout = A.cout[blockIdx.y];
+    const float* __restrict__ W = params + A.woff[blockIdx.y];
+    unsigned short* __restrict__ Wf = wf + A.pf[blockIdx.y];
+    unsigned short* __restrict__ Wb = wb ? wb + A.pb[blockIdx.y] : nullptr;
     const int KPf = kpad(Cin), KPb = kpad(Cout);
     const int n1 = 32 * KPf, n2 = 32 * KPb;
     for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n1 + n2; idx += gridDim.x * blockDim.x) {
@@ -1028,13 +1108,18 @@ __global__ void k_sub(const double* __restrict__ a, const double* __restrict__ b
 static int conv_launch(int Cin, const float* in, const unsigned short* Wp, const float* bias, int Cout, float* out,
                        float* preact, const float* mask, bool relu, const float* in_scale, int B, int H, int W,
                        hipStream_t st) {
-    const int tiles = B * ((H + 3) / 4) * ((W + 31) / 32);
+    const bool narrow = W <= 16;   // 16-pixel rows, two to a wave
+    const int tiles = narrow ? B * ((H + 7) / 8) : B * ((H + 3) / 4) * ((W + 31) / 32);
     dim3 g(tiles), blk(256);
     switch (Cin) {
-#define RTE_CV(CI)                                                                                         \
-    case CI:                                                                                               \
-        hipLaunchKernelGGL((k_conv3x3<CI>), g, blk, 0, st, in, Wp, bias, Cout, out, preact, mask, relu ? 1 : 0, \
-                           in_scale, B, H, W);                                                             \
+#define RTE_CV(CI)                                                                                                   \
+    case CI:                                                                                                         \
+        if (narrow)                                                                                                  \
+            hipLaunchKernelGGL((k_conv3x3<CI, 16>), g, blk, 0, st, in, Wp, bias, Cout, out, preact, mask, relu ? 1 : 0, \
+                               in_scale, B, H, W);                                                                   \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_conv3x3<CI, 32>), g, blk, 0, st, in, Wp, bias, Cout, out, preact, mask, relu ? 1 : 0, \
+                               in_scale, B, H, W);                                                                   \
         return 0;
         RTE_CV(1) RTE_CV(3) RTE_CV(5) RTE_CV(7) RTE_CV(9) RTE_CV(11) RTE_CV(13) RTE_CV(15) RTE_CV(16) RTE_CV(17)
         RTE_CV(32)
@@ -1133,10 +1218,12 @@ struct rte_nn {
     bool use_bias = true;
     size_t cap = 0;                    // activation capacity in floats per tensor
     std::vector<float*> act, pre;      // act[l]: input of layer l (act[0] unused), pre[l]: pre-activation
-    float *gA = nullptr, *gB = nullptr;
+    std::vector<float*> gl;            // output gradients: one per layer, or two taken in turn
+    size_t gl_cap = 0;                 // their capacity in floats
     float* wpart = nullptr;            // per-tile partial weight gradients (k_conv3x3_wgrad)
     size_t wpart_cap = 0;              // its capacity in floats
-    double* lossb = nullptr;
+    double* lossb = nullptr;           // per-sample losses, pinned host memory that k_loss writes
+    double* lossb_dev = nullptr;       // its device address
     int lossb_cap = 0;
 };
 
@@ -1153,24 +1240,34 @@ template <typename P>
 static void nfree(P*& p) { if (p) (void)hipFree((void*)p); p = nullptr; }
 
 static void pack_all(const NetShape& sh, const float* params, unsigned short* wf, unsigned short* wb, hipStream_t st) {
-    for (int l = 0; l < sh.layers; ++l)
-        hipLaunchKernelGGL(k_pack, dim3(64), dim3(256), 0, st, params + sh.woff[l], sh.cin[l], sh.cout[l],
-                           wf + sh.pf_off[l], wb ? wb + sh.pb_off[l] : (unsigned short*)nullptr);
+    PackArgs a{};
+    for (int l = 0; l < sh.layers; ++l) {
+        a.cin[l] = sh.cin[l];
+        a.cout[l] = sh.cout[l];
+        a.woff[l] = sh.woff[l];
+        a.pf[l] = sh.pf_off[l];
+        a.pb[l] = sh.pb_off[l];
+    }
+    hipLaunchKernelGGL(k_pack, dim3(64, sh.layers), dim3(256), 0, st, params, a, wf, wb);
 }
 
 static int ensure_acts(rte_nn* nn, size_t per_tensor, int B) {
     if (per_tensor <= nn->cap && B <= nn->lossb_cap) return RTE_OK;
     for (auto& a : nn->act) nfree(a);
     for (auto& a : nn->pre) nfree(a);
-    nfree(nn->gA); nfree(nn->gB); nfree(nn->lossb);
+    if (nn->lossb) (void)hipHostFree(nn->lossb);
+    nn->lossb = nullptr;
+    nn->cap = 0;
+    nn->lossb_cap = 0;
     const int L = nn->sh.layers;
     nn->act.assign(L + 1, nullptr);
     nn->pre.assign(L, nullptr);
     int rc;
     for (int l = 1; l <= L; ++l) if ((rc = nalloc(&nn->act[l], per_tensor))) return rc;
     for (int l = 0; l < L; ++l) if ((rc = nalloc(&nn->pre[l], per_tensor))) return rc;
-    if ((rc = nalloc(&nn->gA, per_tensor)) || (rc = nalloc(&nn->gB, per_tensor))) return rc;
-    if ((rc = nalloc(&nn->lossb, (size_t)B))) return rc;
+    hipError_t e = hipHostMalloc((void**)&nn->lossb, (size_t)B * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&nn->lossb_dev, nn->lossb, 0);
+    if (e != hipSuccess) return set_hip_error(e, "hipHostMalloc", __FILE__, __LINE__);
     nn->cap = per_tensor;
     nn->lossb_cap = B;
     return RTE_OK;
@@ -1609,7 +1706,9 @@ void rte_nn_destroy(rte_nn* nn) {
     nfree(nn->p); nfree(nn->g); nfree(nn->m); nfree(nn->v); nfree(nn->wf); nfree(nn->wb);
     for (auto& a : nn->act) nfree(a);
     for (auto& a : nn->pre) nfree(a);
-    nfree(nn->gA); nfree(nn->gB); nfree(nn->lossb); nfree(nn->wpart);
+    for (auto& a : nn->gl) nfree(a);
+    if (nn->lossb) (void)hipHostFree(nn->lossb);
+    nfree(nn->wpart);
     delete nn;
 }
 
@@ -1677,43 +1776,75 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
     pack_all(sh, nn->p, nn->wf, nn->wb, st);
     if ((rc = net_forward(sh, nn->wf, nn->p, sh.boff, x, nullptr, nn->act.data(), nn->pre.data(), B, H, W, st)))
         return rc;
-    const int per = sh.C * H * W;
-    hipLaunchKernelGGL(k_loss, dim3(B), dim3(256), 0, st, nn->act[sh.layers], t, w, nn->gA, nn->lossb, per, B);
-    const size_t wneed = (size_t)wgrad_tiles(B, H, W) * 32 * wgrad_ktiles(WG_MAXCIN) * 32;
+    // The weight gradients of every layer go into one launch while that does not fill the chip by
+    // far (then every layer keeps its output gradient and partial sums); larger inputs take one layer
+    // after another through two gradient buffers and one set of partial sums.
+    const int L = sh.layers, ntiles = wgrad_tiles(B, H, W);
+    const bool together = ntiles <= 256;
+    const size_t per_tensor = (size_t)B * std::max(sh.hidden, sh.C) * H * W;
+    const size_t ngl = together ? L : 2;
+    if (nn->gl.size() < ngl || nn->gl_cap < per_tensor) {
+        for (auto& q : nn->gl) nfree(q);
+        nn->gl_cap = 0;
+        nn->gl.assign(ngl, nullptr);
+        for (auto& q : nn->gl)
+            if ((rc = nalloc(&q, per_tensor))) return rc;
+        nn->gl_cap = per_tensor;
+    }
+    WgradArgs wa{};
+    size_t wneed = 0;
+    int groups = 1, nout = 1;
+    for (int l = 0; l < L; ++l) {
+        const size_t n = (size_t)ntiles * 32 * wgrad_ktiles(sh.cin[l]) * 32;
+        wa.part[l] = together ? wneed : 0;
+        wneed = together ? wneed + n : std::max(wneed, n);
+        wa.x[l] = l == 0 ? x : nn->act[l];
+        wa.gy[l] = nn->gl[together ? l : l & 1];
+        wa.cin[l] = sh.cin[l];
+        wa.cout[l] = sh.cout[l];
+        wa.woff[l] = sh.woff[l];
+        wa.boff[l] = sh.boff[l];
+        groups = std::max(groups, (wgrad_ktiles(sh.cin[l]) + 3) / 4);
+        nout = std::max(nout, sh.cout[l] * (sh.cin[l] * 9 + 1));
+    }
     if (wneed > nn->wpart_cap) {
         nfree(nn->wpart);
         nn->wpart_cap = 0;
         if ((rc = nalloc(&nn->wpart, wneed))) return rc;
         nn->wpart_cap = wneed;
     }
-    // backward: gA holds dLoss/d(output of layer l)
-    float* gcur = nn->gA;
-    float* gnext = nn->gB;
-    for (int l = sh.layers - 1; l >= 0; --l) {
-        const float* a_in = l == 0 ? x : nn->act[l];
-        const int ntiles = wgrad_tiles(B, H, W);
-        const dim3 wg((unsigned)ntiles, (unsigned)((wgrad_ktiles(sh.cin[l]) + 3) / 4));
-        hipLaunchKernelGGL(k_conv3x3_wgrad, wg, dim3(256), 0, st, a_in, gcur, nn->wpart, B, sh.cin[l], sh.cout[l], H,
-                           W);
-        const int nout = sh.cout[l] * (sh.cin[l] * 9 + 1);
-        hipLaunchKernelGGL(k_wgrad_reduce, dim3((nout + 255) / 256), dim3(256), 0, st, nn->wpart, ntiles, sh.cin[l],
-                           sh.cout[l], nn->g + sh.woff[l], nn->g + sh.boff[l]);
+    const int per = sh.C * H * W;
+    hipLaunchKernelGGL(k_loss, dim3(B), dim3(256), 0, st, nn->act[L], t, w, const_cast<float*>(wa.gy[L - 1]),
+                       nn->lossb_dev, per, B);
+    auto weight_grads = [&](const WgradArgs& q, int nl) {
+        hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((unsigned)ntiles, (unsigned)groups, (unsigned)nl), dim3(256), 0, st, q,
+                           nn->wpart, B, H, W);
+        hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nout + 255) / 256), (unsigned)nl), dim3(256), 0, st, q,
+                           nn->wpart, ntiles, nn->use_bias ? 1 : 0, nn->g, grad);
+    };
+    // backward: gy[l] holds dLoss/d(output of layer l)
+    for (int l = L - 1; l >= 0; --l) {
+        if (!together) {
+            WgradArgs one{};
+            one.x[0] = wa.x[l];
+            one.gy[0] = wa.gy[l];
+            one.cin[0] = wa.cin[l];
+            one.cout[0] = wa.cout[l];
+            one.woff[0] = wa.woff[l];
+            one.boff[0] = wa.boff[l];
+            weight_grads(one, 1);
+        }
         if (l > 0) {   // data gradient, masked by the ReLU of layer l-1
-            if (conv_launch(sh.cout[l], gcur, nn->wb + sh.pb_off[l], nullptr, sh.cin[l], gnext, nullptr, nn->pre[l - 1],
-                            false, nullptr, B, H, W, st))
+            if (conv_launch(sh.cout[l], wa.gy[l], nn->wb + sh.pb_off[l], nullptr, sh.cin[l], const_cast<float*>(wa.gy[l - 1]),
+                            nullptr, nn->pre[l - 1], false, nullptr, B, H, W, st))
                 return set_error(RTE_EUNSUPPORTED, "unsupported convolution width");
-            std::swap(gcur, gnext);
         }
     }
-    if (!nn->use_bias)
-        for (int l = 0; l < sh.layers; ++l)
-            RTE_HIP_TRY(hipMemsetAsync(nn->g + sh.boff[l], 0, sh.cout[l] * sizeof(float), st));
-    std::vector<double> lb(B);
-    RTE_HIP_TRY(hipMemcpyAsync(lb.data(), nn->lossb, B * sizeof(double), hipMemcpyDeviceToHost, st));
-    if (grad) RTE_HIP_TRY(hipMemcpyAsync(grad, nn->g, sh.nparam * sizeof(float), hipMemcpyDeviceToDevice, st));
+    if (together) weight_grads(wa, L);
+    RTE_HIP_TRY(hipGetLastError());
     RTE_HIP_TRY(hipStreamSynchronize(st));
     double s = 0.0;
-    for (int b = 0; b < B; ++b) s += lb[b];
+    for (int b = 0; b < B; ++b) s += nn->lossb[b];
     if (loss) *loss = s;
     return RTE_OK;
 }
