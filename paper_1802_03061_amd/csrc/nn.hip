@@ -42,7 +42,7 @@ __device__ __forceinline__ unsigned short f2bf(float f) {   // round to nearest 
 constexpr int kpad(int cin) { return (cin * 9 + 7) / 8 * 8; }
 
 // ------------------------------------------------------------------ convolution (MFMA) --------
-// in [B][CIN][H][W] (times *in_scale if given); Wp [32][KP] bf16; out/preact [B][Cout][H][W].
+// in [B][CIN][H][W] (times *in_scale if given); Wp [32][KP] bf16; out [B][Cout][H][W].
 // mask (optional, same shape as out): the output is zeroed where mask <= 0.
 // A wave's 32 pixels are one row of 32 or, for images up to 16 wide, two rows of 16 (TW), so that no
 // column of the tile is idle there.  Both operands come from LDS: the weights with a row pitch of
@@ -53,7 +53,7 @@ constexpr int kpad(int cin) { return (cin * 9 + 7) / 8 * 8; }
 template <int CIN, int TW>
 __global__ __launch_bounds__(256) void k_conv3x3(const float* __restrict__ in, const unsigned short* __restrict__ Wp,
                                                  const float* __restrict__ bias, int Cout, float* __restrict__ out,
-                                                 float* __restrict__ preact, const float* __restrict__ mask, int relu,
+                                                 const float* __restrict__ mask, int relu,
                                                  const float* __restrict__ in_scale, int B, int H, int W) {
     constexpr int K = CIN * 9;
     constexpr int KP = kpad(CIN);
@@ -148,7 +148,6 @@ __global__ __launch_bounds__(256) void k_conv3x3(const float* __restrict__ in, c
             if (i < Cout) {
                 const size_t o = ((size_t)(b * Cout + i) * H + y) * W + x;
                 float z = acc[r] + bs[r];
-                if (preact) preact[o] = z;
                 if (!(mk[r] > 0.f)) z = 0.f;
                 if (relu) z = fmaxf(z, 0.f);
                 out[o] = z;
@@ -157,14 +156,171 @@ __global__ __launch_bounds__(256) void k_conv3x3(const float* __restrict__ in, c
     }
 }
 
+// All layers of a network over one image per block, the activations kept in LDS between layers
+// (BF16 with a zero halo, as k_conv3x3 stages them; the FP32 values also go to memory for the
+// backward pass).  Forward: layer l maps y[l] to y[l+1] with bias and, but for the last, ReLU.  Data
+// gradient (the layers in reverse with the transposed weights): step l maps a gradient to the one
+// before it, zeroed where the mask (that layer's ReLU output) is not positive.  The same tiles, K order
+// and rounding as k_conv3x3, so the values are the same; a tile is 32 consecutive pixels.  The next
+// layer's weights are loaded while a layer computes.
+// Bound by LDS instructions (the input's four 2-byte reads per K step) on the B compute units in use:
+// 32 images of 16^2, five layers of 32 channels take 41 us, where a launch of 11-13 us per layer took
+// 65 us.  (Reading an operand right before its product, one step at a time, took 77 us.)
+constexpr int NN_MAXL = 8;   // layers of a network
+struct ChainArgs {
+    const float* in;                     // first layer's input [B][cin[0]][H][W]
+    const unsigned short* w[NN_MAXL];    // weight packs [32][kpad(cin)]
+    const float* bias[NN_MAXL];          // or null
+    const float* mask[NN_MAXL];          // or null
+    float* out[NN_MAXL];                 // [B][cout][H][W], or null
+    int cin[NN_MAXL], cout[NN_MAXL], relu[NN_MAXL];
+    int layers;
+};
+constexpr int CHAIN_WPITCH = kpad(32) + 4;
+__host__ __device__ constexpr size_t chain_lds(int H, int W) {
+    return (size_t)2 * 32 * (H + 2) * (W + 2) * 2 + (size_t)2 * 32 * CHAIN_WPITCH * 2 + kpad(32) * 2;
+}
+
+// N steps of 8 along K: every LDS read of the group is issued before its first product.
+template <int N>
+__device__ __forceinline__ void chain_steps(f32x16& acc, const unsigned short* wa, const unsigned short* koff,
+                                            const unsigned short* px, int kb) {
+    bf16x4 a[N], bv[N];
+    ushort4 o[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) o[u] = *reinterpret_cast<const ushort4*>(koff + (kb + u) * 8);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        a[u] = *reinterpret_cast<const bf16x4*>(wa + (kb + u) * 8);
+        bv[u][0] = (short)px[o[u].x];
+        bv[u][1] = (short)px[o[u].y];
+        bv[u][2] = (short)px[o[u].z];
+        bv[u][3] = (short)px[o[u].w];
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a[u], bv[u], acc, 0, 0, 0);
+}
+
+constexpr int CHAIN_WAVES = 8;
+__global__ __launch_bounds__(64 * CHAIN_WAVES) void k_net_chain(ChainArgs A, int H, int W) {
+    extern __shared__ __align__(16) unsigned short smem_n[];
+    const int PW = W + 2, PP = (H + 2) * PW, HW = H * W;   // halo'd row and plane
+    unsigned short* ws = smem_n;                             // two weight buffers [32][CHAIN_WPITCH]
+    unsigned short* koff = ws + 2 * 32 * CHAIN_WPITCH;       // K offset k -> (channel, tap)
+    unsigned short* act = koff + kpad(32);                   // two activation buffers [32][H+2][W+2]
+    const int tid = threadIdx.x, nthr = blockDim.x, wave = tid >> 6, lane = tid & 63, nw = nthr >> 6;
+    const int b = blockIdx.x;
+    constexpr int WL = 5;            // 16-byte weight loads per thread (256 threads and more)
+    uint4 wv[WL];
+    auto load_weights = [&](int l) {
+        const int n8 = 32 * ((A.cin[l] * 9 + 7) / 8);
+#pragma unroll
+        for (int u = 0; u < WL; ++u) {
+            const int q = tid + u * nthr;
+            wv[u] = reinterpret_cast<const uint4*>(A.w[l])[q < n8 ? q : 0];
+        }
+    };
+    auto store_weights = [&](int l) {
+        const int k8 = (A.cin[l] * 9 + 7) / 8, n8 = 32 * k8;
+        unsigned short* dst = ws + (l & 1) * 32 * CHAIN_WPITCH;
+#pragma unroll
+        for (int u = 0; u < WL; ++u) {
+            const int q = tid + u * nthr;
+            if (q < n8) {
+                unsigned short* d = dst + (q / k8) * CHAIN_WPITCH + (q % k8) * 8;
+                *reinterpret_cast<uint2*>(d) = make_uint2(wv[u].x, wv[u].y);
+                *reinterpret_cast<uint2*>(d + 4) = make_uint2(wv[u].z, wv[u].w);
+            }
+        }
+    };
+    load_weights(0);
+    // input, then zeroed activation buffers (the halo stays zero)
+    const int n0 = A.cin[0] * HW;
+    const float* src = A.in + (size_t)b * n0;
+    for (int i = tid; i < 2 * 32 * PP / 2; i += nthr) reinterpret_cast<unsigned*>(act)[i] = 0u;
+    for (int k = tid; k < kpad(32); k += nthr) koff[k] = (unsigned short)((k / 9) * PP + ((k % 9) / 3) * PW + k % 3);
+    __syncthreads();
+    store_weights(0);
+    for (int base = 0; base < n0; base += 8 * nthr) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = base + u * nthr + tid;
+            v[u] = src[i < n0 ? i : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = base + u * nthr + tid;
+            if (i < n0) {
+                const int c = i / HW, p = i % HW;
+                act[c * PP + (p / W + 1) * PW + p % W + 1] = f2bf(v[u]);
+            }
+        }
+    }
+    __syncthreads();
+    const int kq = (lane >> 5) * 4, li = lane & 31;
+    auto chan = [&](int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };   // output channel of acc[r]
+    for (int l = 0; l < A.layers; ++l) {
+        const int Cout = A.cout[l], K = A.cin[l] * 9, KB = (K + 7) / 8;
+        if (l + 1 < A.layers) load_weights(l + 1);
+        const unsigned short* wa = ws + (l & 1) * 32 * CHAIN_WPITCH + li * CHAIN_WPITCH + kq;
+        const unsigned short* ain = act + (l & 1) * 32 * PP;
+        unsigned short* aout = act + ((l + 1) & 1) * 32 * PP;
+        for (int t = wave; t * 32 < HW; t += nw) {
+            const int p = t * 32 + li, pc = p < HW ? p : HW - 1;
+            const int py = pc / W, pxl = pc % W;
+            float mkv[16], bs[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = chan(r), ic = i < Cout ? i : 0;
+                mkv[r] = A.mask[l] ? A.mask[l][((size_t)b * Cout + ic) * HW + pc] : 1.f;
+                bs[r] = A.bias[l] ? A.bias[l][ic] : 0.f;
+            }
+            const unsigned short* px = ain + py * PW + pxl;
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            const int full = K / 8;
+            int kb = 0;
+            for (; kb + 6 <= full; kb += 6) chain_steps<6>(acc, wa, koff + kq, px, kb);
+            for (; kb < full; ++kb) chain_steps<1>(acc, wa, koff + kq, px, kb);
+            if (full < KB) {   // the last step's values past K are zero
+                const bf16x4 a = *reinterpret_cast<const bf16x4*>(wa + full * 8);
+                bf16x4 bv;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k = full * 8 + kq + r;
+                    bv[r] = k < K ? (short)px[koff[k]] : (short)0;
+                }
+                acc = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a, bv, acc, 0, 0, 0);
+            }
+            if (p < HW) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int i = chan(r);
+                    if (i < Cout) {
+                        float z = acc[r] + bs[r];
+                        if (!(mkv[r] > 0.f)) z = 0.f;
+                        if (A.relu[l]) z = fmaxf(z, 0.f);
+                        if (A.out[l]) A.out[l][((size_t)b * Cout + i) * HW + p] = z;
+                        aout[i * PP + (py + 1) * PW + pxl + 1] = f2bf(z);
+                    }
+                }
+            }
+        }
+        if (l + 1 < A.layers) store_weights(l + 1);
+        __syncthreads();
+    }
+}
+
 // Weight and bias gradients as one GEMM on MFMA: G[o][k] = sum_p gy[o][p] X[p][k] over every pixel
 // p of the batch, with X[p][k] = x[c][p + off_t] for k = c*9 + t < Cin*9 and X[p][Cin*9] = 1 (so
-// G[o][Cin*9] is the bias gradient); BF16 operands, FP32 accumulation, as in the forward.  Block
-// (tile, group) takes one tile of 256 pixels of one sample (WG_ROWS x WG_TW, or 16 x 16 when W <= 16),
-// stages the tile's input with its halo and the output gradient in LDS as BF16, and its wave w
-// accumulates the 32-column tile kt = 4 group + w of G over the tile's pixels, 8 at a time.  Each
+// G[o][Cin*9] is the bias gradient); BF16 operands, FP32 accumulation, as in the forward.  A block
+// takes one tile of 256 pixels of one sample (WG_ROWS x WG_TW, or 16 x 16 when W <= 16), stages the
+// tile's input with its halo and the output gradient in LDS as BF16, and its wave w (of WG_WAVES)
+// accumulates the 32-column tile w of G over the tile's pixels, 8 at a time.  Each
 // block writes its 32 x 32 sums to part[tile][32][NKT*32]; k_wgrad_reduce adds the tiles in order.
-// The staging loads are issued in batches of 16 so that their latencies overlap; the staged output
+// The staging loads are issued in batches so that their latencies overlap; the staged output
 // gradient has a row pitch of 260 (its 8-byte reads over 32 rows hit different banks; with 256 all
 // of them hit one).  Small batches launch every layer at once (blockIdx.z): 32 images of 16^2, 5
 // layers took 5 x (19.6 + 4.8) us one layer after another, most of it those bank conflicts.
@@ -177,7 +333,6 @@ __host__ __device__ inline int wgrad_tiles(int B, int H, int W) {
     return B * ((H + rows - 1) / rows) * ((W + tw - 1) / tw);
 }
 
-constexpr int NN_MAXL = 8;   // layers of a network
 struct WgradArgs {           // per layer: input, output gradient, shape, offsets into part and g
     const float* x[NN_MAXL];
     const float* gy[NN_MAXL];
@@ -186,30 +341,31 @@ struct WgradArgs {           // per layer: input, output gradient, shape, offset
 };
 constexpr int WG_GP = 260;
 
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgradArgs A, float* __restrict__ partb, int B, int H, int W) {
+constexpr int WG_WAVES = 10, WG_THREADS = 64 * WG_WAVES;   // 32 channels: 289 columns of G
+
+__global__ __launch_bounds__(WG_THREADS) void k_conv3x3_wgrad(WgradArgs A, float* __restrict__ partb, int B, int H, int W) {
     __shared__ unsigned short xs[WG_MAXCIN * (WG_ROWS + 2) * (WG_TW + 2)];
     __shared__ __align__(16) unsigned short gs[32 * WG_GP];
     const int Cin = A.cin[blockIdx.z], Cout = A.cout[blockIdx.z];
     const float* __restrict__ x = A.x[blockIdx.z];
     const float* __restrict__ gy = A.gy[blockIdx.z];
     float* __restrict__ part = partb + A.part[blockIdx.z];
-    if ((int)blockIdx.y * 4 >= wgrad_ktiles(Cin)) return;   // the whole block
     const int TW = wgrad_tw(W), ROWS = 256 / TW, PW = TW + 2, PH = ROWS + 2;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int NKT = wgrad_ktiles(Cin), K = Cin * 9;
-    const int kt = blockIdx.y * 4 + wave;
+    const int kt = wave;
     const int tiles_x = (W + TW - 1) / TW, tiles_y = (H + ROWS - 1) / ROWS;
     const int tile = blockIdx.x;
     const int tx = tile % tiles_x, ty = (tile / tiles_x) % tiles_y, b = tile / (tiles_x * tiles_y);
     const int x0 = tx * TW, y0 = ty * ROWS;
     const int NX = Cin * PH * PW;
-    constexpr int U = 16;
-    for (int base = 0; base < NX; base += U * 256) {
+    constexpr int U = 9;
+    for (int base = 0; base < NX; base += U * WG_THREADS) {
         float v[U];
         bool in[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int idx = base + u * 256 + threadIdx.x;
+            const int idx = base + u * WG_THREADS + threadIdx.x;
             const int c = idx / (PH * PW), rem = idx % (PH * PW);
             const int yy = y0 + rem / PW - 1, xx = x0 + rem % PW - 1;
             in[u] = idx < NX && yy >= 0 && yy < H && xx >= 0 && xx < W;
@@ -217,23 +373,24 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgradArgs A, float* __res
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int idx = base + u * 256 + threadIdx.x;
+            const int idx = base + u * WG_THREADS + threadIdx.x;
             if (idx < NX) xs[idx] = f2bf(in[u] ? v[u] : 0.f);
         }
     }
     {
-        const int pr = threadIdx.x, yy = y0 + pr / TW, xx = x0 + pr % TW;
-        const bool px = yy < H && xx < W;
+        constexpr int NG = 32 * 256, UG = (NG + WG_THREADS - 1) / WG_THREADS;
+        float v[UG];
 #pragma unroll
-        for (int base = 0; base < 32; base += U) {
-            float v[U];
+        for (int u = 0; u < UG; ++u) {
+            const int idx = u * WG_THREADS + threadIdx.x, o = idx / 256, pr = idx % 256;
+            const int yy = y0 + pr / TW, xx = x0 + pr % TW;
+            v[u] = gy[o < Cout && yy < H && xx < W ? ((size_t)(b * Cout + o) * H + yy) * W + xx : 0];
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int o = base + u;
-                v[u] = gy[px && o < Cout ? ((size_t)(b * Cout + o) * H + yy) * W + xx : 0];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) gs[(base + u) * WG_GP + pr] = f2bf(px && base + u < Cout ? v[u] : 0.f);
+        for (int u = 0; u < UG; ++u) {
+            const int idx = u * WG_THREADS + threadIdx.x, o = idx / 256, pr = idx % 256;
+            const int yy = y0 + pr / TW, xx = x0 + pr % TW;
+            if (idx < NG) gs[o * WG_GP + pr] = f2bf(o < Cout && yy < H && xx < W ? v[u] : 0.f);
         }
     }
     __syncthreads();
@@ -1106,7 +1263,7 @@ __global__ void k_sub(const double* __restrict__ a, const double* __restrict__ b
 
 // ------------------------------------------------------------------ host dispatch ------------
 static int conv_launch(int Cin, const float* in, const unsigned short* Wp, const float* bias, int Cout, float* out,
-                       float* preact, const float* mask, bool relu, const float* in_scale, int B, int H, int W,
+                       const float* mask, bool relu, const float* in_scale, int B, int H, int W,
                        hipStream_t st) {
     const bool narrow = W <= 16;   // 16-pixel rows, two to a wave
     const int tiles = narrow ? B * ((H + 7) / 8) : B * ((H + 3) / 4) * ((W + 31) / 32);
@@ -1115,10 +1272,10 @@ static int conv_launch(int Cin, const float* in, const unsigned short* Wp, const
 #define RTE_CV(CI)                                                                                                   \
     case CI:                                                                                                         \
         if (narrow)                                                                                                  \
-            hipLaunchKernelGGL((k_conv3x3<CI, 16>), g, blk, 0, st, in, Wp, bias, Cout, out, preact, mask, relu ? 1 : 0, \
+            hipLaunchKernelGGL((k_conv3x3<CI, 16>), g, blk, 0, st, in, Wp, bias, Cout, out, mask, relu ? 1 : 0, \
                                in_scale, B, H, W);                                                                   \
         else                                                                                                         \
-            hipLaunchKernelGGL((k_conv3x3<CI, 32>), g, blk, 0, st, in, Wp, bias, Cout, out, preact, mask, relu ? 1 : 0, \
+            hipLaunchKernelGGL((k_conv3x3<CI, 32>), g, blk, 0, st, in, Wp, bias, Cout, out, mask, relu ? 1 : 0, \
                                in_scale, B, H, W);                                                                   \
         return 0;
         RTE_CV(1) RTE_CV(3) RTE_CV(5) RTE_CV(7) RTE_CV(9) RTE_CV(11) RTE_CV(13) RTE_CV(15) RTE_CV(16) RTE_CV(17)
@@ -1217,7 +1374,7 @@ struct rte_nn {
     int step = 0;
     bool use_bias = true;
     size_t cap = 0;                    // activation capacity in floats per tensor
-    std::vector<float*> act, pre;      // act[l]: input of layer l (act[0] unused), pre[l]: pre-activation
+    std::vector<float*> act;           // act[l]: input of layer l (act[0] unused)
     std::vector<float*> gl;            // output gradients: one per layer, or two taken in turn
     size_t gl_cap = 0;                 // their capacity in floats
     float* wpart = nullptr;            // per-tile partial weight gradients (k_conv3x3_wgrad)
@@ -1254,17 +1411,14 @@ static void pack_all(const NetShape& sh, const float* params, unsigned short* wf
 static int ensure_acts(rte_nn* nn, size_t per_tensor, int B) {
     if (per_tensor <= nn->cap && B <= nn->lossb_cap) return RTE_OK;
     for (auto& a : nn->act) nfree(a);
-    for (auto& a : nn->pre) nfree(a);
     if (nn->lossb) (void)hipHostFree(nn->lossb);
     nn->lossb = nullptr;
     nn->cap = 0;
     nn->lossb_cap = 0;
     const int L = nn->sh.layers;
     nn->act.assign(L + 1, nullptr);
-    nn->pre.assign(L, nullptr);
     int rc;
     for (int l = 1; l <= L; ++l) if ((rc = nalloc(&nn->act[l], per_tensor))) return rc;
-    for (int l = 0; l < L; ++l) if ((rc = nalloc(&nn->pre[l], per_tensor))) return rc;
     hipError_t e = hipHostMalloc((void**)&nn->lossb, (size_t)B * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&nn->lossb_dev, nn->lossb, 0);
     if (e != hipSuccess) return set_hip_error(e, "hipHostMalloc", __FILE__, __LINE__);
@@ -1273,15 +1427,37 @@ static int ensure_acts(rte_nn* nn, size_t per_tensor, int B) {
     return RTE_OK;
 }
 
-// Forward through all layers; act[l+1] = layer l output, pre[l] = its pre-activation.
+// One launch for all layers where an image's activations fit LDS twice (up to about 28^2).
+static bool chain_fits(int H, int W) { return chain_lds(H, W) <= 156 * 1024; }
+static void chain_launch(const ChainArgs& a, int B, int H, int W, hipStream_t st) {
+    const int nw = std::min(CHAIN_WAVES, std::max(4, (H * W + 31) / 32));   // one wave per tile
+    hipLaunchKernelGGL(k_net_chain, dim3(B), dim3(64 * nw), chain_lds(H, W), st, a, H, W);
+}
+
+// Forward through all layers; act[l+1] = layer l output (keep: all of them, else the last at least).
 static int net_forward(const NetShape& sh, const unsigned short* wf, const float* params_bias_base,
-                       const std::vector<size_t>& boff, const float* x, const float* in_scale, float* const* act,
-                       float* const* pre, int B, int H, int W, hipStream_t st) {
+                       const std::vector<size_t>& boff, const float* x, float* const* act, bool keep, int B,
+                       int H, int W, hipStream_t st) {
+    if (chain_fits(H, W)) {
+        ChainArgs c{};
+        c.in = x;
+        c.layers = sh.layers;
+        for (int l = 0; l < sh.layers; ++l) {
+            c.w[l] = wf + sh.pf_off[l];
+            c.bias[l] = params_bias_base + boff[l];
+            c.out[l] = keep || l + 1 == sh.layers ? act[l + 1] : nullptr;
+            c.cin[l] = sh.cin[l];
+            c.cout[l] = sh.cout[l];
+            c.relu[l] = l + 1 < sh.layers;
+        }
+        chain_launch(c, B, H, W, st);
+        return RTE_OK;
+    }
     const float* a = x;
     for (int l = 0; l < sh.layers; ++l) {
         const bool last = l == sh.layers - 1;
-        if (conv_launch(sh.cin[l], a, wf + sh.pf_off[l], params_bias_base + boff[l], sh.cout[l], act[l + 1],
-                        pre ? pre[l] : nullptr, nullptr, !last, l == 0 ? in_scale : nullptr, B, H, W, st))
+        if (conv_launch(sh.cin[l], a, wf + sh.pf_off[l], params_bias_base + boff[l], sh.cout[l], act[l + 1], nullptr,
+                        !last, nullptr, B, H, W, st))
             return set_error(RTE_EUNSUPPORTED, "unsupported convolution width");
         a = act[l + 1];
     }
@@ -1337,7 +1513,7 @@ static int pc_net(rte_ctx* c, float* out) {
         for (int l = 0; l < sh.layers; ++l) {
             const bool last = l == sh.layers - 1;
             float* o = last ? out : bufs[l & 1];
-            if (conv_launch(sh.cin[l], a, wf + sh.pf_off[l], c->pc_b + sh.boff[l], sh.cout[l], o, nullptr, nullptr, !last,
+            if (conv_launch(sh.cin[l], a, wf + sh.pf_off[l], c->pc_b + sh.boff[l], sh.cout[l], o, nullptr, !last,
                             l == 0 ? c->pc_st + 1 : nullptr, 1, Hc, Wc, st))
                 return set_error(RTE_EUNSUPPORTED, "unsupported convolution width");
             a = o;
@@ -1573,7 +1749,7 @@ int pc_apply(rte_ctx* c, const double* v, double* z) {
         for (int l = 0; l < sh.layers; ++l) {
             const bool last = l == sh.layers - 1;
             float* o = bufs[l & 1];
-            if (conv_launch(sh.cin[l], a, wf + sh.pf_off[l], c->pc_b + sh.boff[l], sh.cout[l], o, nullptr, nullptr, !last,
+            if (conv_launch(sh.cin[l], a, wf + sh.pf_off[l], c->pc_b + sh.boff[l], sh.cout[l], o, nullptr, !last,
                             l == 0 ? c->pc_st + 1 : nullptr, 1, Hc, Wc, st))
                 return set_error(RTE_EUNSUPPORTED, "unsupported convolution width");
             a = o;
@@ -1705,7 +1881,6 @@ void rte_nn_destroy(rte_nn* nn) {
     if (nn->stream) (void)hipStreamSynchronize(nn->stream);
     nfree(nn->p); nfree(nn->g); nfree(nn->m); nfree(nn->v); nfree(nn->wf); nfree(nn->wb);
     for (auto& a : nn->act) nfree(a);
-    for (auto& a : nn->pre) nfree(a);
     for (auto& a : nn->gl) nfree(a);
     if (nn->lossb) (void)hipHostFree(nn->lossb);
     nfree(nn->wpart);
@@ -1737,7 +1912,7 @@ int rte_nn_forward(rte_nn* nn, const float* x, int B, int H, int W, float* y) {
     pack_all(nn->sh, nn->p, nn->wf, nullptr, nn->stream);
     std::vector<float*> act = nn->act;
     act[nn->sh.layers] = y;
-    rc = net_forward(nn->sh, nn->wf, nn->p, nn->sh.boff, x, nullptr, act.data(), nullptr, B, H, W, nn->stream);
+    rc = net_forward(nn->sh, nn->wf, nn->p, nn->sh.boff, x, act.data(), false, B, H, W, nn->stream);
     if (rc) return rc;
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? RTE_OK : set_hip_error(e, "rte_nn_forward", __FILE__, __LINE__);
@@ -1760,7 +1935,7 @@ int rte_nn_forward_noalloc(rte_nn* nn, const float* x, int B, int H, int W, floa
     act[sh.layers] = y;
     act[0] = nullptr;
     pack_all(sh, nn->p, nn->wf, nullptr, nn->stream);
-    int rc = net_forward(sh, nn->wf, nn->p, sh.boff, x, nullptr, act, nullptr, B, H, W, nn->stream);
+    int rc = net_forward(sh, nn->wf, nn->p, sh.boff, x, act, false, B, H, W, nn->stream);
     if (rc) return rc;
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? RTE_OK : set_hip_error(e, "rte_nn_forward_noalloc", __FILE__, __LINE__);
@@ -1774,7 +1949,7 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
     if (rc) return rc;
     hipStream_t st = nn->stream;
     pack_all(sh, nn->p, nn->wf, nn->wb, st);
-    if ((rc = net_forward(sh, nn->wf, nn->p, sh.boff, x, nullptr, nn->act.data(), nn->pre.data(), B, H, W, st)))
+    if ((rc = net_forward(sh, nn->wf, nn->p, sh.boff, x, nn->act.data(), true, B, H, W, st)))
         return rc;
     // The weight gradients of every layer go into one launch while that does not fill the chip by
     // far (then every layer keeps its output gradient and partial sums); larger inputs take one layer
@@ -1793,7 +1968,7 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
     }
     WgradArgs wa{};
     size_t wneed = 0;
-    int groups = 1, nout = 1;
+    int nout = 1;
     for (int l = 0; l < L; ++l) {
         const size_t n = (size_t)ntiles * 32 * wgrad_ktiles(sh.cin[l]) * 32;
         wa.part[l] = together ? wneed : 0;
@@ -1804,7 +1979,6 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
         wa.cout[l] = sh.cout[l];
         wa.woff[l] = sh.woff[l];
         wa.boff[l] = sh.boff[l];
-        groups = std::max(groups, (wgrad_ktiles(sh.cin[l]) + 3) / 4);
         nout = std::max(nout, sh.cout[l] * (sh.cin[l] * 9 + 1));
     }
     if (wneed > nn->wpart_cap) {
@@ -1817,13 +1991,29 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
     hipLaunchKernelGGL(k_loss, dim3(B), dim3(256), 0, st, nn->act[L], t, w, const_cast<float*>(wa.gy[L - 1]),
                        nn->lossb_dev, per, B);
     auto weight_grads = [&](const WgradArgs& q, int nl) {
-        hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((unsigned)ntiles, (unsigned)groups, (unsigned)nl), dim3(256), 0, st, q,
+        hipLaunchKernelGGL(k_conv3x3_wgrad, dim3((unsigned)ntiles, 1, (unsigned)nl), dim3(WG_THREADS), 0, st, q,
                            nn->wpart, B, H, W);
         hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nout + 255) / 256), (unsigned)nl), dim3(256), 0, st, q,
                            nn->wpart, ntiles, nn->use_bias ? 1 : 0, nn->g, grad);
     };
-    // backward: gy[l] holds dLoss/d(output of layer l)
-    for (int l = L - 1; l >= 0; --l) {
+    // backward: gy[l] holds dLoss/d(output of layer l); a data gradient is masked by the ReLU of the
+    // layer before (its output is positive where its pre-activation is)
+    const bool chain = together && L > 1 && chain_fits(H, W);
+    if (chain) {
+        ChainArgs c{};
+        c.in = wa.gy[L - 1];
+        c.layers = L - 1;
+        for (int i = 0; i < L - 1; ++i) {
+            const int l = L - 1 - i;
+            c.w[i] = nn->wb + sh.pb_off[l];
+            c.mask[i] = nn->act[l];
+            c.out[i] = const_cast<float*>(wa.gy[l - 1]);
+            c.cin[i] = sh.cout[l];
+            c.cout[i] = sh.cin[l];
+        }
+        chain_launch(c, B, H, W, st);
+    }
+    for (int l = L - 1; l >= 0 && !chain; --l) {
         if (!together) {
             WgradArgs one{};
             one.x[0] = wa.x[l];
@@ -1834,9 +2024,9 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
             one.boff[0] = wa.boff[l];
             weight_grads(one, 1);
         }
-        if (l > 0) {   // data gradient, masked by the ReLU of layer l-1
-            if (conv_launch(sh.cout[l], wa.gy[l], nn->wb + sh.pb_off[l], nullptr, sh.cin[l], const_cast<float*>(wa.gy[l - 1]),
-                            nullptr, nn->pre[l - 1], false, nullptr, B, H, W, st))
+        if (l > 0) {
+            if (conv_launch(sh.cout[l], wa.gy[l], nn->wb + sh.pb_off[l], nullptr, sh.cin[l],
+                            const_cast<float*>(wa.gy[l - 1]), nn->act[l], false, nullptr, B, H, W, st))
                 return set_error(RTE_EUNSUPPORTED, "unsupported convolution width");
         }
     }
