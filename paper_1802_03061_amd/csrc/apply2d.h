@@ -30,7 +30,8 @@ struct Apply2DArgs {
     int nx, ny, PX, PY, L, C;
     cx<T>* work;               // work buffer [nbatch][C][NKS][ny], NKS = pack ? PX/2 : PX/2+1
     cx<T>* work2;              // split form only: [nbatch][C][NKS][PY] (may be null otherwise)
-    const cx<T>* Q;            // quarter spectra [2L+1][PX/2+1][PY/2+1], scaled by 1/(PX PY)
+    const cx<T>* Q;            // quarter spectra [2L+1][PX/2+1][PY/2+1], scaled by 1/(PX PY); for pass B
+                               // in two halves each column's even frequencies before its odd ones
     const cx<T>* twx;          // exp(-2 pi i q/PX), q < PX
     const cx<T>* twy;          // exp(-2 pi i q/PY), q < PY
     hipStream_t stream;

@@ -26,6 +26,7 @@
 #pragma once
 #include "apply2d.h"
 #include "fft_wave.h"
+#include "spectra.h"
 
 namespace rte {
 
@@ -418,9 +419,12 @@ __global__ __launch_bounds__(NW * 64) void k_pass_b_wave(cx<T>* __restrict__ Tb,
 // zero past ny <= PH).  A block takes one column and runs the halves one after the other, half the
 // spectra of every channel in LDS at a time; the inverse is e[n] + W^-n o[n] of the halves' inverses,
 // with e kept in registers (a third round's in a spare LDS row) while the odd half runs.  The column
-// is read twice (the second time from the caches) and written once; no full-length buffer.  At 512^2,
-// L = 8 in FP64 pass B takes 85 us, where forward transforms, coupling and inverse transforms through
-// a full-length buffer (785 MB, at the HBM rate) took 150 us.
+// is read twice (the second time from the caches; up to L = 6 there are registers to hold one of a
+// wave's rows) and written once; no full-length buffer.  The quarter spectra are kept even frequencies
+// first (half_entry), so that each half reads whole lines of its own: with frequencies in order both
+// halves fetched every line.  At 512^2 in FP64 this took pass B from 98 to 88 us for L = 8 and from 73
+// to 66 for L = 6 (holding rows at L = 8 spills: 94 and 101 us for one and two); forward transforms, coupling and inverse transforms through a full-length buffer (785 MB, at
+// the HBM rate) took 150 us.
 
 // All PH inputs of a transform's first stage.
 template <typename T, int P, int LN>
@@ -478,6 +482,7 @@ __global__ __launch_bounds__(NW * 64) void k_pass_b_half(cx<T>* __restrict__ Tb,
     constexpr int LN = wave_lanes(PH);
     static_assert(LN == 64, "one transform per wave");
     constexpr int NP = (C + NW - 1) / NW;
+    constexpr int HOLD = L <= 6 ? 1 : 0;   // input rows kept from the even half to the odd one
     constexpr int NTHR = NW * 64;
     constexpr int LD = wave_ld(PH);
     constexpr int NSL = fft_last_ns(PH), RL = PH / NSL;
@@ -495,14 +500,16 @@ __global__ __launch_bounds__(NW * 64) void k_pass_b_half(cx<T>* __restrict__ Tb,
         const bool packed = pack && kx == 0;
         cx<T>* col = Tb + (size_t)(item / nkx) * C * cstride + (size_t)kx * ny;
         cx<T> e[NP < 2 ? NP : 2][Last::ITEMS][RL];
+        WaveFull<T, PH, LN> held[HOLD < 1 ? 1 : HOLD];
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
                 const int s = p * NW + wave, l = hide(l0);
                 if (s < C && (!single || s == 0)) {
-                    WaveFull<T, PH, LN> in;
-                    in.load(col + s * cstride, ny, l);
+                    WaveFull<T, PH, LN> again;
+                    WaveFull<T, PH, LN>& in = p < HOLD ? held[p < HOLD ? p : 0] : again;
+                    if (p >= HOLD || h == 0) in.load(col + s * cstride, ny, l);
                     in.first_stage(spec + s * LD, h ? wn : nullptr, ny, l);
                     wave_sync();
                     wave_stages<T, PH, LN, false, fft_radix(PH, 1), PH>(spec + s * LD, twh, l);
@@ -536,8 +543,9 @@ __global__ __launch_bounds__(NW * 64) void k_pass_b_half(cx<T>* __restrict__ Tb,
                 const int f = 2 * k + h;
                 const bool flip = f > PH;
                 const cx<T>* q = Q + (size_t)kq * KH;
-                if (single) couple_first<T, L, LD>(spec, slot, q, qs, flip ? PY - f : f, flip);
-                else couple_single<T, L, LD, false>(spec, slot, q, qs, flip ? PY - f : f, flip);
+                const int fe = half_entry(flip ? PY - f : f, PY);
+                if (single) couple_first<T, L, LD>(spec, slot, q, qs, fe, flip);
+                else couple_single<T, L, LD, false>(spec, slot, q, qs, fe, flip);
             }
             __syncthreads();
             if (packed) {

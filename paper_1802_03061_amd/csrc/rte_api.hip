@@ -1038,7 +1038,7 @@ int rte_setup(rte_ctx** out, const rte_grid* g, double mu_a, double mu_s, const 
             const size_t nq = (size_t)c->C * NK * (c->PY / 2 + 1);
             if ((rc = dalloc(&c->Qd, nq)) || (f32 && (rc = dalloc(&c->Qf, nq)))) { dfree(b0); dfree(b1); free_ctx(c); return rc; }
             SpectraArgs2D a{c->nx, c->ny, c->PX, c->PY, c->L, c->h, c->mu_t, b0, b1, c->twd[0], c->twd[1],
-                            c->Qf, c->Qd, c->stream};
+                            c->Qf, c->Qd, apply2d_b_halves<double>(c->L, c->PY), c->stream};
             rc = build_spectra_2d(a);
         } else {
             const size_t no = (size_t)NK * (c->PY / 2 + 1) * (c->PZ / 2 + 1);

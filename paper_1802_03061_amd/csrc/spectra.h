@@ -20,8 +20,11 @@ struct SpectraArgs2D {
     const cx<double>* twy;    // FP64 twiddles, PY
     cx<float>* Qf;            // [2L+1][PX/2+1][PY/2+1] or null
     cx<double>* Qd;           // same shape or null
+    bool halves;              // Qd: each column's even frequencies before its odd ones (half_entry)
     hipStream_t stream;
 };
+// Where a column of halves keeps frequency f of its PY/2 + 1.
+__host__ __device__ constexpr int half_entry(int f, int PY) { return (f & 1) ? PY / 4 + 1 + f / 2 : f / 2; }
 int build_spectra_2d(const SpectraArgs2D& a);
 
 struct SpectraArgs3D {

@@ -291,15 +291,15 @@ __global__ __launch_bounds__(256) void k_transpose(const E* __restrict__ in, E* 
 
 // Q[m][kx][fy] = s * F[kx][fy] (F is [PX][PY] after the y-transform), fy <= PY/2, kx <= PX/2.
 __global__ void k_extract_quarter(const cx<double>* __restrict__ F, cx<float>* __restrict__ Qf,
-                                  cx<double>* __restrict__ Qd, int PX, int PY, int m, double s) {
+                                  cx<double>* __restrict__ Qd, int PX, int PY, int m, double s, int halves) {
     const int KH = PY / 2 + 1, NK = PX / 2 + 1;
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (size_t)NK * KH) return;
     const int kx = (int)(idx / KH), fy = (int)(idx % KH);
     const cx<double> v = scale(F[(size_t)kx * PY + fy], s);
-    const size_t o = (size_t)m * NK * KH + idx;
-    if (Qd) Qd[o] = v;
-    if (Qf) Qf[o] = cvt<float>(v);
+    const size_t o = (size_t)m * NK * KH + (size_t)kx * KH;
+    if (Qd) Qd[o + (halves ? half_entry(fy, PY) : fy)] = v;
+    if (Qf) Qf[o + fy] = cvt<float>(v);
 }
 
 // 3D octant: data is [PY][PX][PZ] after three transforms; Q3[kx][ky][kz] = s Re data.
@@ -369,7 +369,7 @@ int build_spectra_2d(const SpectraArgs2D& a) {
         if (fft_rows_f64(a.buf1, a.twy, a.PY, NK, false, a.stream)) return -1;
         const unsigned nq = (unsigned)(((size_t)NK * KH + 255) / 256);
         hipLaunchKernelGGL(k_extract_quarter, dim3(nq), dim3(256), 0, a.stream, a.buf1, a.Qf, a.Qd, a.PX, a.PY, m,
-                           s);
+                           s, a.halves ? 1 : 0);
     }
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
