@@ -40,6 +40,7 @@ namespace {
 constexpr int BT = 256;                  // threads of the chunk kernels
 constexpr int CHUNK = 4096;              // vector elements per chunk
 constexpr int CPT = CHUNK / BT;          // elements per thread
+constexpr int KG = 2;                    // basis vectors a thread has in flight
 
 struct Chunk {
     int p, off, len;
@@ -83,6 +84,61 @@ __device__ __forceinline__ double wave_sum(double s) {
 
 // ---------------------------------------------------------------- inner iteration ------------
 
+// The dots and the update read the whole basis once each; their bound is the HBM rate.  A thread's
+// elements of a chunk are tid, tid + BT, ...; of a short chunk the last one stands in for those past
+// its end, so that every load is unconditional and those of KG basis vectors are in flight at once.
+// With a guard per element the compiler loads one element at a time, which left the late steps of a
+// cycle, when few problems still run, at 5 us per basis vector whatever they had to move: 128 problems
+// of 64^2 to 512^2, step 9 (all running) 188 -> 129 us (dots) and 216 -> 137 us (update), step 20 (few
+// running) 145 -> 36 and 110 -> 28 us.  KG = 4 measures the same; short chunks go one vector at a time
+// (sixteen more index registers).
+template <bool FULL>
+__device__ __forceinline__ int chunk_elem(int u, int len) {
+    const int e = threadIdx.x + u * BT;
+    return FULL || e < len ? e : len - 1;
+}
+template <bool FULL>
+__device__ __forceinline__ void chunk_load(double (&v)[CPT], const double* __restrict__ p, int len) {
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) v[u] = p[chunk_elem<FULL>(u, len)];
+}
+
+// Sums of G basis vectors i, ..., i + G - 1 against w: all their loads first.
+template <bool FULL, int G>
+__device__ __forceinline__ void chunk_dots(const double* v, size_t ld, int len, const double (&wv)[CPT], int i,
+                                           double* red) {
+    double a[G][CPT], s[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) chunk_load<FULL>(a[g], v + (size_t)(i + g) * ld, len);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        s[g] = 0.0;
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) s[g] += a[g][u] * wv[u];
+        s[g] = wave_sum(s[g]);
+    }
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int g = 0; g < G; ++g) red[(i + g) * 4 + (threadIdx.x >> 6)] = s[g];
+}
+template <bool FULL>
+__device__ __forceinline__ void chunk_dots(const KryProb& k, const Chunk& c, int j, double* red) {
+    const size_t ld = k.nvec;
+    const double* v = k.V + c.off;
+    double wv[CPT];
+    chunk_load<FULL>(wv, v + (j + 1) * ld, c.len);
+#pragma unroll
+    for (int u = 0; u < CPT; ++u)
+        if (!FULL && (int)(threadIdx.x + u * BT) >= c.len) wv[u] = 0.0;
+    int i = 0;
+    if constexpr (FULL) {
+#pragma unroll 1
+        for (; i + KG <= j + 1; i += KG) chunk_dots<FULL, KG>(v, ld, c.len, wv, i, red);
+    }
+#pragma unroll 1
+    for (; i <= j; ++i) chunk_dots<FULL, 1>(v, ld, c.len, wv, i, red);
+}
+
 // partial[chunk][i] = <V_i, w> over the chunk for i <= j, w = V_{j+1} (the new apply output).
 __global__ __launch_bounds__(BT) void kb_dots(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
                                               const int* __restrict__ act, const int* __restrict__ dj,
@@ -92,28 +148,10 @@ __global__ __launch_bounds__(BT) void kb_dots(const Chunk* __restrict__ ch, cons
     if (!act[c.p]) return;
     const KryProb& k = kp[c.p];
     const int j = *dj;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double* w = k.V + (size_t)(j + 1) * k.nvec + c.off;
-    double wv[CPT];
-#pragma unroll
-    for (int u = 0; u < CPT; ++u) {
-        const int e = tid + u * BT;
-        wv[u] = e < c.len ? w[e] : 0.0;
-    }
-#pragma unroll 2   // the next vector's loads go out while this one is summed
-    for (int i = 0; i <= j; ++i) {
-        const double* v = k.V + (size_t)i * k.nvec + c.off;
-        double s = 0.0;
-#pragma unroll
-        for (int u = 0; u < CPT; ++u) {
-            const int e = tid + u * BT;
-            if (e < c.len) s += v[e] * wv[u];
-        }
-        s = wave_sum(s);
-        if (lane == 0) red[i * 4 + wave] = s;
-    }
+    if (c.len == CHUNK) chunk_dots<true>(k, c, j, red);
+    else chunk_dots<false>(k, c, j, red);
     __syncthreads();
-    for (int i = tid; i <= j; i += BT)
+    for (int i = threadIdx.x; i <= j; i += BT)
         partial[(size_t)blockIdx.x * (m + 1) + i] = (red[i * 4] + red[i * 4 + 1]) + (red[i * 4 + 2] + red[i * 4 + 3]);
 }
 
@@ -132,49 +170,64 @@ __global__ __launch_bounds__(64) void kb_hcol(const KryProb* __restrict__ kp, co
     }
 }
 
-// w -= sum_i H[i][j] V_i over the chunk; part2[chunk] = |w|^2 over the chunk afterwards.
+template <bool FULL, int G>
+__device__ __forceinline__ void chunk_subtract(const double* v, size_t ld, int len, double (&wv)[CPT], int i,
+                                               const double* h) {
+    double a[G][CPT];
+#pragma unroll
+    for (int g = 0; g < G; ++g) chunk_load<FULL>(a[g], v + (size_t)(i + g) * ld, len);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) wv[u] -= h[i + g] * a[g][u];
+}
+// The sum of the squares of the thread's updated elements.
+template <bool FULL>
+__device__ __forceinline__ double chunk_update(const KryProb& k, const Chunk& c, int j, const double* h) {
+    const size_t ld = k.nvec;
+    const double* v = k.V + c.off;
+    double* w = k.V + c.off + (j + 1) * ld;
+    double wv[CPT];
+    chunk_load<FULL>(wv, w, c.len);
+    int i = 0;
+    if constexpr (FULL) {
+#pragma unroll 1
+        for (; i + KG <= j + 1; i += KG) chunk_subtract<FULL, KG>(v, ld, c.len, wv, i, h);
+    }
+#pragma unroll 1
+    for (; i <= j; ++i) chunk_subtract<FULL, 1>(v, ld, c.len, wv, i, h);
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        const int e = threadIdx.x + u * BT;
+        if (FULL || e < c.len) {
+            w[e] = wv[u];
+            s += wv[u] * wv[u];
+        }
+    }
+    return s;
+}
+
+// w -= sum_i H[i][j] V_i over the chunk; part2[chunk] = |w|^2 over the chunk afterwards.  The chunks are
+// taken backwards: the last ones the dots read are still in the memory-side cache (137 against 149 us).
 __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
                                                 const int* __restrict__ act, const int* __restrict__ dj,
                                                 double* __restrict__ part2, int m) {
     __shared__ double h[RTE_MAX_RESTART + 1];
     __shared__ double red[4];
-    const Chunk c = ch[blockIdx.x];
+    const int blk = gridDim.x - 1 - blockIdx.x;
+    const Chunk c = ch[blk];
     if (!act[c.p]) return;
     const KryProb& k = kp[c.p];
     const int j = *dj;
     const int tid = threadIdx.x;
     for (int i = tid; i <= j; i += BT) h[i] = k.H[(size_t)j * (m + 1) + i];
     __syncthreads();
-    double* w = k.V + (size_t)(j + 1) * k.nvec + c.off;
-    double wv[CPT];
-#pragma unroll
-    for (int u = 0; u < CPT; ++u) {
-        const int e = tid + u * BT;
-        wv[u] = e < c.len ? w[e] : 0.0;
-    }
-#pragma unroll 2   // the next vector's loads go out while this one is subtracted
-    for (int i = 0; i <= j; ++i) {
-        const double hi = h[i];
-        const double* v = k.V + (size_t)i * k.nvec + c.off;
-#pragma unroll
-        for (int u = 0; u < CPT; ++u) {
-            const int e = tid + u * BT;
-            if (e < c.len) wv[u] -= hi * v[e];
-        }
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int u = 0; u < CPT; ++u) {
-        const int e = tid + u * BT;
-        if (e < c.len) {
-            w[e] = wv[u];
-            s += wv[u] * wv[u];
-        }
-    }
+    double s = c.len == CHUNK ? chunk_update<true>(k, c, j, h) : chunk_update<false>(k, c, j, h);
     s = wave_sum(s);
     if ((tid & 63) == 0) red[tid >> 6] = s;
     __syncthreads();
-    if (tid == 0) part2[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0) part2[blk] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // H[j+1][j] = |w|, the previous Givens rotations and a new one on column j, the residual vector

@@ -127,11 +127,18 @@ __global__ __launch_bounds__(KT) void k_reduce_partials(const double* __restrict
     if (threadIdx.x == 0) out[v] = s;
 }
 
+// A thread's last index below n (n: none); a step of stride down from its first wraps to above n.
+__device__ __forceinline__ size_t last_of(size_t n, size_t stride) {
+    const size_t i0 = (size_t)blockIdx.x * KT + threadIdx.x;
+    return i0 < n ? i0 + (n - 1 - i0) / stride * stride : n;
+}
+
 // w[i] = a (w[i] - sum_v V[v][i] h[v]) (FP64 arithmetic, stored as TV); partial_norm[blk] = sum over
 // the slice of the stored new w[i]^2.
 // a = 1, or with s0.st set (the fused single pass, h = s0.st) the normalising factor computed here
 // (arnoldi_stage0_in_update), block 0 also doing stage 0 of the Arnoldi column.  PAIRS: as in
-// k_dot_partial, element pairs as 16-byte loads.
+// k_dot_partial, element pairs as 16-byte loads.  The vectors are walked backwards: what the dots read
+// last is still in the memory-side cache (512^2, L = 8: mean over a solve 45.9 -> 43.2 us).
 template <bool PAIRS, typename TV>
 __global__ __launch_bounds__(KT) void k_cgs_update(TV* __restrict__ w, const TV* __restrict__ V, size_t ld,
                                                    int nvec, const double* __restrict__ h, size_t n,
@@ -157,7 +164,7 @@ __global__ __launch_bounds__(KT) void k_cgs_update(TV* __restrict__ w, const TV*
         const size_t np = n / 2, ldp = ld / 2;
         P2* w2 = reinterpret_cast<P2*>(w);
         const P2* V2 = reinterpret_cast<const P2*>(V);
-        for (size_t i = (size_t)blockIdx.x * KT + threadIdx.x; i < np; i += stride) {
+        for (size_t i = last_of(np, stride); i < np; i -= stride) {
             const P2 wl = w2[i];
             double sx = (double)wl.x, sy = (double)wl.y;
 #pragma unroll 8
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(KT) void k_cgs_update(TV* __restrict__ w, const TV*
             nrm += (double)q.x * (double)q.x + (double)q.y * (double)q.y;
         }
     } else {
-        for (size_t i = (size_t)blockIdx.x * KT + threadIdx.x; i < n; i += stride) {
+        for (size_t i = last_of(n, stride); i < n; i -= stride) {
             double s = (double)w[i];
             // unrolled so that eight basis loads are in flight; subtraction order unchanged
 #pragma unroll 8
