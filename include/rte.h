@@ -262,8 +262,8 @@ int rte_time_batched_apply(int count, rte_ctx* const* ctxs, int reps, double* ms
 
 /* Kernel variants of the batched apply, per padded grid size of a batch (same arithmetic, equal
  * results up to rounding).  pass 0: the row tile of passes A and C (4 variants for a padded x >= 128,
- * as the single-problem row tiles); pass 1: the columns per block of pass B (the default columns and
- * threads, half the threads, twice or half the columns; padded y >= 128).  When rte_solve_batched
+ * as the single-problem row tiles); pass 1: the waves per block of pass B, each transforming columns
+ * of its own (4, 2, 8 or 1; padded y >= 128).  When rte_solve_batched
  * builds the plan of a new list of contexts it times the variants of every size class on all of
  * its problems and keeps the fastest (environment RTE_AUTOTUNE=0: variant 0).  This call forces
  * `variant` (0..3; a size class with fewer variants takes variant 0) or restores tuning (-1) for

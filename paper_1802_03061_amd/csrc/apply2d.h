@@ -89,8 +89,8 @@ struct BatchProb {
 // apply2d_batch_cols(PY, var) columns).  act[p] == 0 skips problem p (act may be NULL); dj (may be
 // NULL) points to the Krylov column index j.  Variants (same arithmetic, different tiling; -1 when
 // var is out of range): passes A and C share the row tile (the single-problem row tiles, padded
-// x >= 128); pass B takes the fused form's columns per block with its threads or half of them, or
-// twice or half the columns (padded y >= 128).
+// x >= 128); pass B takes 4, 2, 8 or 1 waves per block (padded y >= 128; a wave transforms 64 / (PY / 8)
+// columns side by side, at least one).
 template <typename T>
 int apply2d_batch_row_variants(int PX);
 template <typename T>

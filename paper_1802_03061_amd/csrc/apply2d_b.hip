@@ -2,7 +2,7 @@
 // -DRTE_PASSB_L=<L>): FFT along y of every channel, per-frequency mode coupling with the kernel
 // spectra, inverse FFT along y (Sec. 3.3.1: the kernel depends on x - y and on k' - k only, so
 // the convolution over y and the sum over k' meet at each frequency).  The kernels are in
-// passb_wave.h; the batched isotropic pass B is at the end of this file.
+// passb_wave.h.
 //
 // Coupling at frequency (kx, ky), for channels a_0 = u_0, (a_k, b_k) = sqrt2 (Re u_k, Im u_k) and the
 // complex modes W_{+-k} = (A_k +- i B_k)/sqrt2, W_0 = A_0:
@@ -12,7 +12,6 @@
 // channels (passb_wave.h).
 #include "apply2d.h"
 #include "apply2d_b.h"
-#include "fft.h"
 #include "passb_wave.h"
 
 #ifndef RTE_PASSB_L
@@ -31,6 +30,12 @@ static int launch_py(const Apply2DArgs<T>& a, int nbatch) {
     constexpr int L = RTE_PASSB_L;
     if (!a.pack || (a.bcorr.y && (sizeof(T) != 4 || a.single_in || nbatch != 1))) return -6;
     const int nkq = a.PX / 2 + 1, nkx = a.PX / 2;
+    if constexpr (L == 0) {
+        if (!a.bcorr.y) {   // the correction enters with k_pass_b_wave's loads
+            launch_iso<T, PY>(a, nbatch, nkx, nkq);
+            return 0;
+        }
+    }
     if constexpr (wave_fits<T, PY, L>()) {
         launch_wave<T, PY, L>(a, nbatch, nkx, nkq);
         return 0;
@@ -71,130 +76,33 @@ int RTE_CAT(pass_b_L, RTE_PASSB_L)<double>(const Apply2DArgs<double>& a, int nba
 #endif
 
 #if RTE_PASSB_L == 0
-// ---- batched isotropic form: one block per (problem, group of NCOL columns) ----
-//
-// The column spectra in LDS, the y-FFTs by the whole block.  The spectrum of the isotropic kernel is
-// real.  Column 0 packs x-frequencies 0 and PX/2 (see packed_split in passb_wave.h).
-template <typename T, int PY, int NCOL, int NTHR>
-__global__ __launch_bounds__(NTHR) void k_pass_b_batch(const BatchProb<T>* __restrict__ probs,
-                                                       const int2* __restrict__ items, const int* __restrict__ act) {
-    constexpr int LD = padded(PY);
-    constexpr int KH = PY / 2 + 1;
-    // FFT stages in groups of at most ~3 radix-8 butterflies per thread
-    constexpr int G0 = (3 * NTHR * 8) / PY;
-    constexpr int G = G0 >= NCOL ? NCOL : (G0 < 1 ? 1 : G0);
-    __shared__ cx<T> spec[NCOL * LD];
-    __shared__ cx<T> tws[PY];
-    const int2 item = items[blockIdx.x];
-    const BatchProb<T>& d = probs[item.x];
-    if (act && !act[item.x]) return;
-    const int tid = threadIdx.x;
-    const int ny = d.ny, nkx = d.PX / 2, kx0 = item.y * NCOL;
-    cx<T>* base = d.work;
-    stage_twiddles<T, PY, NTHR>(tws, d.twy, tid);
-    // first stage from the loads: rows y >= ny are zero padding
-    using In = PaddedIn<T, PY, NCOL, NTHR>;
-    constexpr int R0 = In::R0, NB0 = In::NB0;
-    In in;
-    fft_padded_load<T, PY, NCOL, NTHR>(in, tid, [&](int f, int y) {   // a clamped index instead of a branch
-        return base[(kx0 + f < nkx && y < ny) ? (size_t)(kx0 + f) * ny + y : 0];
-    });
-#pragma unroll
-    for (int it = 0; it < In::IT; ++it) {
-        const int idx = tid + it * NTHR;
-        const int j = idx % NB0, f = idx / NB0;
-#pragma unroll
-        for (int r = 0; r < R0 / 2; ++r)
-            if (!(kx0 + f < nkx && j + r * NB0 < ny)) in.v[it][r] = mk((T)0, (T)0);
-    }
-#pragma unroll
-    for (int it = 0; it < In::IT; ++it) {
-        const int idx = tid + it * NTHR;
-        if (In::NBT % NTHR == 0 || idx < In::NBT) {
-            const int j = idx % NB0, f = idx / NB0;
-            cx<T> v[R0];
-#pragma unroll
-            for (int r = 0; r < R0; ++r) v[r] = r < R0 / 2 ? in.v[it][r] : mk((T)0, (T)0);
-            dft_small<T, R0, false>(v);
-#pragma unroll
-            for (int r = 0; r < R0; ++r) spec[f * LD + sw(j * R0 + r)] = v[r];
-        }
-    }
-    __syncthreads();
-    block_fft_grouped_range<T, PY, NCOL, G, LD, NTHR, false, R0, PY>(spec, tws, tid);
-    for (int idx = tid; idx < NCOL * PY; idx += NTHR) {
-        const int f = idx % PY, kx = kx0 + idx / PY;
-        if (kx >= nkx) continue;
-        cx<T>* sp = spec + (idx / PY) * LD;
-        if (kx == 0) {
-            if (f > PY / 2) continue;
-            const int fm = (PY - f) & (PY - 1);
-            const T kd = d.Q[f].re, kq = d.Q[(size_t)nkx * KH + f].re;
-            const cx<T> z = sp[sw(f)], w = conj(sp[sw(fm)]);
-            const cx<T> D = scale(z + w, (T)0.5 * kd), Qv = scale(mul_mi(z - w), (T)0.5 * kq);
-            sp[sw(f)] = D + mul_i(Qv);
-            if (fm != f) sp[sw(fm)] = conj(D) + mul_i(conj(Qv));
-        } else {
-            const T k = d.Q[(size_t)kx * KH + (f > PY / 2 ? PY - f : f)].re;
-            sp[sw(f)] = scale(sp[sw(f)], k);
-        }
-    }
-    __syncthreads();
-    fft_inverse_cropped_grouped<T, PY, NCOL, G, LD, NTHR>(spec, tws, tid, [&](int f, int y, cx<T> v) {
-        if (kx0 + f < nkx && y < ny) base[(size_t)(kx0 + f) * ny + y] = v;
-    });
-}
+// ---- batched isotropic form ----
 
-constexpr int iso_cols() { return 4; }
-constexpr int iso_threads(int n) { return n / 8 >= 512 ? 512 : (n / 8 >= 256 ? 256 : (n / 8 >= 128 ? 128 : 64)); }
-
-// Batched pass-B variants (padded y >= 128): 0 = the fused form's columns per block and threads;
-// 1 = the same columns with half the threads; 2 = twice the columns; 3 = half the columns.
-template <typename T, int PY, int NCOL>
-constexpr bool batch_b_fits() {
-    return ((long)NCOL * padded(PY) + PY + 2) * (long)sizeof(cx<T>) <= 160 * 1024;
-}
-template <typename T, int PY>
-constexpr int batch_b_variants() {
-    return PY < 128 ? 1 : (batch_b_fits<T, PY, 2 * iso_cols()>() ? 4 : 2);
-}
-template <typename T, int PY, int NCOL, int NT>
-static void launch_b_batch_nc(const BatchProb<T>* probs, const int2* items, int nitems, const int* act,
+// Variants (padded y >= 128) = waves per block (the tuner times them).
+constexpr int batch_waves(int var) { return var == 1 ? 2 : var == 2 ? 8 : var == 3 ? 1 : 4; }
+template <typename T>
+constexpr int batch_b_variants(int PY) { return PY < 128 ? 1 : 4; }
+template <typename T, int PY, int NW>
+static void launch_b_batch_nw(const BatchProb<T>* probs, const int2* items, int nitems, const int* act,
                               hipStream_t st) {
-    static_assert(batch_b_fits<T, PY, NCOL>(), "batched pass-B columns exceed the LDS budget");
-    hipLaunchKernelGGL((k_pass_b_batch<T, PY, NCOL, NT>), dim3(nitems), dim3(NT), 0, st, probs, items, act);
+    hipLaunchKernelGGL((k_pass_b_batch<T, PY, NW>), dim3(nitems), dim3(NW * 64), 0, st, probs, items, act);
 }
 template <typename T, int PY>
 static void launch_b_batch(const BatchProb<T>* probs, const int2* items, int nitems, const int* act, int var,
                            hipStream_t st) {
-    constexpr int NCOL = iso_cols();
-    constexpr int NT = iso_threads(NCOL * PY);
-    if constexpr (batch_b_variants<T, PY>() >= 2) {
-        if (var == 1) return launch_b_batch_nc<T, PY, NCOL, (NT / 2 > 64 ? NT / 2 : 64)>(probs, items, nitems, act, st);
+    if constexpr (PY >= 128) {
+        if (var == 1) return launch_b_batch_nw<T, PY, 2>(probs, items, nitems, act, st);
+        if (var == 2) return launch_b_batch_nw<T, PY, 8>(probs, items, nitems, act, st);
+        if (var == 3) return launch_b_batch_nw<T, PY, 1>(probs, items, nitems, act, st);
     }
-    if constexpr (batch_b_variants<T, PY>() >= 4) {
-        if (var == 2) return launch_b_batch_nc<T, PY, 2 * NCOL, iso_threads(2 * NCOL * PY)>(probs, items, nitems,
-                                                                                            act, st);
-        if (var == 3) return launch_b_batch_nc<T, PY, NCOL / 2, iso_threads(NCOL / 2 * PY)>(probs, items, nitems,
-                                                                                            act, st);
-    }
-    launch_b_batch_nc<T, PY, NCOL, NT>(probs, items, nitems, act, st);
+    launch_b_batch_nw<T, PY, 4>(probs, items, nitems, act, st);
 }
 template <typename T>
-int apply2d_batch_col_variants(int PY) {
-    switch (PY) {
-        case 128: return batch_b_variants<T, 128>();
-        case 256: return batch_b_variants<T, 256>();
-        case 512: return batch_b_variants<T, 512>();
-        case 1024: return batch_b_variants<T, 1024>();
-        default: return 1;
-    }
-}
+int apply2d_batch_col_variants(int PY) { return batch_b_variants<T>(PY); }
 template <typename T>
 int apply2d_batch_cols(int PY, int var) {
-    constexpr int NCOL = iso_cols();   // the same for every PY when C = 1
     if (var < 0 || var >= apply2d_batch_col_variants<T>(PY)) return 0;
-    return var == 2 ? 2 * NCOL : var == 3 ? NCOL / 2 : NCOL;
+    return batch_waves(var) * (64 / wave_lanes(PY));
 }
 template <typename T>
 int apply2d_batch_pass_b(int PY, const BatchProb<T>* probs, const int2* items, int nitems, const int* act, int var,

@@ -185,17 +185,6 @@ __device__ __forceinline__ void fft_stages_range(cx<T>* buf, const cx<T>* tw, in
         fft_stages_range<T, P, NFFT, LD, NTHR, INV, NS * R, NSEND>(buf, tw, tid);
     }
 }
-// The same in groups of at most G transforms (fewer butterflies held in registers per stage, at the
-// price of more barriers).
-template <typename T, int P, int NFFT, int G, int LD, int NTHR, bool INV, int NS, int NSEND>
-__device__ __forceinline__ void block_fft_grouped_range(cx<T>* buf, const cx<T>* tw, int tid) {
-    if constexpr (NFFT <= G) {
-        fft_stages_range<T, P, NFFT, LD, NTHR, INV, NS, NSEND>(buf, tw, tid);
-    } else {
-        fft_stages_range<T, P, G, LD, NTHR, INV, NS, NSEND>(buf, tw, tid);
-        block_fft_grouped_range<T, P, NFFT - G, G, LD, NTHR, INV, NS, NSEND>(buf + G * LD, tw, tid);
-    }
-}
 // Sub-transform length of the last stage of a length-P transform.
 constexpr int fft_last_ns(int P) {
     int ns = 1;
@@ -206,43 +195,25 @@ constexpr int fft_last_ns(int P) {
 // Forward transforms of NFFT sequences whose entries y >= P/2 are zero (zero padding): the first
 // stage (radix R0, no twiddles) is computed in registers from ld(f, y), y < P/2 (the functor returns
 // zero past the data), and written to buf; the remaining stages run in LDS.  Ends with a barrier.
-// Split in two so that a caller can issue the loads of its next group early:
-// fft_padded_load fills the registers (PaddedIn), fft_padded_from_regs does the rest.
-template <typename T, int P, int NFFT, int NTHR>
-struct PaddedIn {
-    static constexpr int R0 = fft_radix(P, 1);
-    static constexpr int NB0 = P / R0;
-    static constexpr int NBT = NFFT * NB0;
-    static constexpr int IT = (NBT + NTHR - 1) / NTHR;
-    cx<T> v[IT][R0 / 2];
-};
-
-template <typename T, int P, int NFFT, int NTHR, typename Ld>
-__device__ __forceinline__ void fft_padded_load(PaddedIn<T, P, NFFT, NTHR>& in, int tid, Ld ld) {
-    using PI = PaddedIn<T, P, NFFT, NTHR>;
+template <typename T, int P, int NFFT, int LD, int NTHR, typename Ld>
+__device__ __forceinline__ void fft_forward_padded(cx<T>* buf, const cx<T>* tws, int tid, Ld ld) {
+    constexpr int R0 = fft_radix(P, 1), NB0 = P / R0, NBT = NFFT * NB0, IT = (NBT + NTHR - 1) / NTHR;
+    cx<T> in[IT][R0 / 2];
 #pragma unroll
-    for (int it = 0; it < PI::IT; ++it) {
+    for (int it = 0; it < IT; ++it) {
         const int idx = tid + it * NTHR;
-        const int f = idx / PI::NB0, j = idx % PI::NB0;
+        const int f = idx / NB0, j = idx % NB0;
 #pragma unroll
-        for (int r = 0; r < PI::R0 / 2; ++r)
-            in.v[it][r] = (PI::NBT % NTHR == 0 || idx < PI::NBT) ? ld(f, j + r * PI::NB0) : mk((T)0, (T)0);
+        for (int r = 0; r < R0 / 2; ++r) in[it][r] = (NBT % NTHR == 0 || idx < NBT) ? ld(f, j + r * NB0) : mk((T)0, (T)0);
     }
-}
-
-template <typename T, int P, int NFFT, int LD, int NTHR>
-__device__ __forceinline__ void fft_padded_from_regs(cx<T>* buf, const cx<T>* tws, int tid,
-                                                     const PaddedIn<T, P, NFFT, NTHR>& in) {
-    using PI = PaddedIn<T, P, NFFT, NTHR>;
-    constexpr int R0 = PI::R0;
 #pragma unroll
-    for (int it = 0; it < PI::IT; ++it) {
+    for (int it = 0; it < IT; ++it) {
         const int idx = tid + it * NTHR;
-        if (PI::NBT % NTHR == 0 || idx < PI::NBT) {
-            const int f = idx / PI::NB0, j = idx % PI::NB0;
+        if (NBT % NTHR == 0 || idx < NBT) {
+            const int f = idx / NB0, j = idx % NB0;
             cx<T> v[R0];
 #pragma unroll
-            for (int r = 0; r < R0; ++r) v[r] = r < R0 / 2 ? in.v[it][r] : mk((T)0, (T)0);
+            for (int r = 0; r < R0; ++r) v[r] = r < R0 / 2 ? in[it][r] : mk((T)0, (T)0);
             dft_small<T, R0, false>(v);
 #pragma unroll
             for (int r = 0; r < R0; ++r) buf[f * LD + sw(j * R0 + r)] = v[r];
@@ -252,22 +223,15 @@ __device__ __forceinline__ void fft_padded_from_regs(cx<T>* buf, const cx<T>* tw
     fft_stages_range<T, P, NFFT, LD, NTHR, false, R0, P>(buf, tws, tid);
 }
 
-template <typename T, int P, int NFFT, int LD, int NTHR, typename Ld>
-__device__ __forceinline__ void fft_forward_padded(cx<T>* buf, const cx<T>* tws, int tid, Ld ld) {
-    PaddedIn<T, P, NFFT, NTHR> in;
-    fft_padded_load<T, P, NFFT, NTHR>(in, tid, ld);
-    fft_padded_from_regs<T, P, NFFT, LD, NTHR>(buf, tws, tid, in);
-}
-
 // Inverse transforms of the NFFT sequences in buf of which only outputs y < P/2 are wanted: every
-// stage but the last in LDS (in groups of at most G transforms), the last in registers, handing
+// stage but the last in LDS, the last in registers, handing
 // y = j + r NSL (r < RL/2) to st(f, y, value) (the functor skips y past the data).  No barrier at
 // the end.
-template <typename T, int P, int NFFT, int G, int LD, int NTHR, typename St>
-__device__ __forceinline__ void fft_inverse_cropped_grouped(cx<T>* buf, const cx<T>* tws, int tid, St st) {
+template <typename T, int P, int NFFT, int LD, int NTHR, typename St>
+__device__ __forceinline__ void fft_inverse_cropped(cx<T>* buf, const cx<T>* tws, int tid, St st) {
     constexpr int NSL = fft_last_ns(P);
     constexpr int RL = P / NSL;
-    block_fft_grouped_range<T, P, NFFT, G, LD, NTHR, true, 1, NSL>(buf, tws, tid);
+    fft_stages_range<T, P, NFFT, LD, NTHR, true, 1, NSL>(buf, tws, tid);
     constexpr int TWL = stage_tw_offset(P, NSL);
     for (int idx = tid; idx < NFFT * NSL; idx += NTHR) {
         const int j = idx % NSL, f = idx / NSL;
@@ -287,11 +251,6 @@ __device__ __forceinline__ void fft_inverse_cropped_grouped(cx<T>* buf, const cx
         for (int r = 0; r < RL / 2; ++r) st(f, j + r * NSL, v[r]);
     }
 }
-template <typename T, int P, int NFFT, int LD, int NTHR, typename St>
-__device__ __forceinline__ void fft_inverse_cropped(cx<T>* buf, const cx<T>* tws, int tid, St st) {
-    fft_inverse_cropped_grouped<T, P, NFFT, NFFT, LD, NTHR>(buf, tws, tid, st);
-}
-
 // Copy the P-entry twiddle table into LDS (all threads; followed by the caller's barrier).  Every
 // load is issued before the first LDS store, so the copy costs one load latency, not P / NTHR.
 template <typename T, int P, int NTHR>

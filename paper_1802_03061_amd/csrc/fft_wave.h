@@ -110,7 +110,7 @@ struct WaveIn {
     static constexpr int ITEMS = NB > LN ? NB / LN : 1;
     static constexpr bool FULL = NB >= LN;
     cx<T> v[ITEMS][R0 / 2];
-    // rows y < ny of src; every load takes a clamped index instead of a branch (see pass_b_cols)
+    // rows y < ny of src; every load takes a clamped index instead of a branch
     __device__ __forceinline__ void load(const cx<T>* __restrict__ src, int ny, int l) {
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it)

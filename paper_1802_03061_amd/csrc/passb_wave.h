@@ -589,6 +589,108 @@ __global__ __launch_bounds__(NW * 64) void k_pass_b_half(cx<T>* __restrict__ Tb,
     }
 }
 
+// ---- isotropic media: nothing couples the columns ---------------------------------------------
+//
+// Each column is transformed by one wave or part of one, from its loads to its stores, in an LDS row
+// of its own: no block barrier.  The spectrum is real and multiplies the last forward stage's
+// registers, except in a packed column 0, whose frequencies f and -f mix (packed_split) and are
+// multiplied in LDS.  in: the column's rows, loaded; q: its kernel column, KH = PY/2 + 1 entries; nkq
+// columns of them.  with_packed (the same for the whole wave): one of the wave's columns may be packed.
+template <typename T, int PY>
+__device__ __forceinline__ void iso_column(const WaveIn<T, PY, wave_lanes(PY)>& in, cx<T>* __restrict__ col,
+                                           const cx<T>* __restrict__ Q, const cx<T>* __restrict__ tw, int kx, int ny,
+                                           int nkq, bool live, bool with_packed, bool pack, cx<T>* buf, int l) {
+    constexpr int LN = wave_lanes(PY), KH = PY / 2 + 1;
+    constexpr int NSL = fft_last_ns(PY), RL = PY / NSL, R0 = fft_radix(PY, 1);
+    using Last = WaveStage<T, PY, LN, RL, NSL, false>;
+    const cx<T>* q = Q + (size_t)kx * KH;
+    const bool packed = pack && kx == 0;
+    T qv[Last::ITEMS][RL];
+#pragma unroll
+    for (int it = 0; it < Last::ITEMS; ++it)
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+            const int f = (l + it * LN + r * NSL) & (PY - 1);
+            qv[it][r] = q[f <= PY / 2 ? f : PY - f].re;
+        }
+    in.first_stage(buf, ny, live, l);
+    wave_sync();
+    if constexpr (NSL > 1) {
+        wave_stages<T, PY, LN, false, R0, NSL>(buf, tw, l);
+        cx<T> v[Last::ITEMS][RL];
+        Last::compute(v, buf, tw, l);
+        wave_sync();
+#pragma unroll
+        for (int it = 0; it < Last::ITEMS; ++it)
+#pragma unroll
+            for (int r = 0; r < RL; ++r) v[it][r] = scale(v[it][r], packed ? (T)1 : qv[it][r]);
+        Last::store(v, buf, l);
+    } else if (l == 0) {   // a single stage: lane 0 holds the whole spectrum
+#pragma unroll
+        for (int r = 0; r < RL; ++r) buf[sw(r)] = scale(buf[sw(r)], packed ? (T)1 : qv[0][r]);
+    }
+    wave_sync();
+    if (with_packed) {
+        if (packed) {
+            const cx<T>* qn = Q + (size_t)(nkq - 1) * KH;
+            for (int f = l; f <= PY / 2; f += LN) {
+                const int fm = (PY - f) & (PY - 1);
+                const cx<T> z = buf[sw(f)], w = conj(buf[sw(fm)]);
+                const cx<T> D = scale(z + w, (T)0.5 * q[f].re), E = scale(mul_mi(z - w), (T)0.5 * qn[f].re);
+                buf[sw(f)] = D + mul_i(E);
+                if (fm != f) buf[sw(fm)] = conj(D) + mul_i(conj(E));
+            }
+        }
+        wave_sync();
+    }
+    wave_inverse<T, PY, LN>(buf, tw, col, ny, live, l);
+}
+
+// Columns (batch entry, kx) by turns, a wave per block, the next ones' loads issued ahead (as in the
+// 3D z-pass).  Bound: launches and latency at these sizes.  One 512^2 medium: FP32 11.3 -> 9.1 us, FP64
+// 14.1 -> 10.4 us (event to event, the launch included) against k_pass_b_wave's four columns per block
+// with barriers round the multiply; four waves per block 9.4 and 11.9 us.
+template <typename T, int PY>
+__global__ __launch_bounds__(64) void k_pass_b_iso(cx<T>* __restrict__ Tb, const cx<T>* __restrict__ Q,
+                                                   const cx<T>* __restrict__ tw, int ny, int nkx, int nkq, int pack,
+                                                   int ncol) {
+    constexpr int LN = wave_lanes(PY), SPW = 64 / LN, LD = padded(PY);
+    __shared__ cx<T> rows[SPW * LD];
+    const int l = threadIdx.x % LN, sub = threadIdx.x / LN;
+    cx<T>* buf = rows + sub * LD;
+    const int step = gridDim.x * SPW;
+    WaveIn<T, PY, LN> in;
+    in.load(Tb + (size_t)min((int)blockIdx.x * SPW + sub, ncol - 1) * ny, ny, l);
+    for (int base = blockIdx.x * SPW; base < ncol; base += step) {
+        const int c = min(base + sub, ncol - 1);
+        const WaveIn<T, PY, LN> cur = in;
+        if (base + step < ncol) in.load(Tb + (size_t)min(base + step + sub, ncol - 1) * ny, ny, l);
+        iso_column<T, PY>(cur, Tb + (size_t)c * ny, Q, tw, c % nkx, ny, nkq, base + sub < ncol, true, pack != 0, buf, l);
+        wave_sync();
+    }
+}
+
+// Batched form: a block takes the NW * SPW columns of one item.  Bound: HBM.  32 media of 512^2 in
+// FP32 (201 MB) take 51 us, in FP64 103 us, 32 of 256^2 in FP32 18 us; with four columns per block in
+// block-wide stages 75, 212 and 24 us.
+template <typename T, int PY, int NW>
+__global__ __launch_bounds__(NW * 64) void k_pass_b_batch(const BatchProb<T>* __restrict__ probs,
+                                                          const int2* __restrict__ items, const int* __restrict__ act) {
+    constexpr int LN = wave_lanes(PY), SPW = 64 / LN, LD = padded(PY);
+    __shared__ cx<T> rows[NW * SPW * LD];
+    const int2 item = items[blockIdx.x];
+    const BatchProb<T>& d = probs[item.x];
+    if (act && !act[item.x]) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = (threadIdx.x & 63) % LN, sub = (threadIdx.x & 63) / LN;
+    const int nkx = d.PX / 2, ny = d.ny, kx0 = (item.y * NW + wave) * SPW, kx = min(kx0 + sub, nkx - 1);
+    cx<T>* col = d.work + (size_t)kx * ny;
+    WaveIn<T, PY, LN> in;
+    in.load(col, ny, l);
+    iso_column<T, PY>(in, col, d.Q, d.twy, kx, ny, nkx + 1, kx0 + sub < nkx, kx0 == 0, true,
+                      rows + (wave * SPW + sub) * LD, l);
+}
+
 // ---- launch ---------------------------------------------------------------------------------
 
 // Columns per block: enough sequences for a few waves.
@@ -629,7 +731,17 @@ inline void launch_wave(const Apply2DArgs<T>& a, int nbatch, int nkx, int nkq) {
     if constexpr (sizeof(T) == 4 && L <= 8) {   // the preconditioner takes up to 17 modes
         if (a.bcorr.y) return launch_wave_nw<T, PY, L, NW, true>(a, nbatch, nkx, nkq);
     }
-    launch_wave_nw<T, PY, L, NW, false>(a, nbatch, nkx, nkq);
+    if constexpr (L > 0) launch_wave_nw<T, PY, L, NW, false>(a, nbatch, nkx, nkq);   // L = 0: launch_iso
+}
+
+// One wave per block: the columns of a small grid spread over the CUs (see k_pass_b_iso).
+template <typename T, int PY>
+inline void launch_iso(const Apply2DArgs<T>& a, int nbatch, int nkx, int nkq) {
+    auto* k = k_pass_b_iso<T, PY>;
+    static const unsigned cap = resident_blocks(k, 64);
+    const int ncol = nkx * nbatch, per = 64 / wave_lanes(PY);
+    const unsigned want = (unsigned)((ncol + per - 1) / per), nb = want < cap ? want : cap;
+    hipLaunchKernelGGL(k, dim3(nb), dim3(64), 0, a.stream, a.work, a.Q, a.twy, a.ny, nkx, nkq, a.pack, ncol);
 }
 
 template <typename T, int PY, int L, int NW>

@@ -24,7 +24,7 @@ def rte():
 
 CASES = [(5, 2, 0), (9, 8, 3), (3, 9, 1), (13, 16, 8), (7, 17, 2), (17, 32, 5), (6, 33, 7), (11, 64, 1), (5, 65, 8),
          (9, 128, 4), (6, 129, 6), (7, 256, 8), (4, 257, 5), (9, 300, 8), (6, 511, 6), (5, 512, 7), (3, 512, 8),
-         (5, 400, 4), (3, 512, 0), (512, 20, 8), (300, 257, 5),
+         (5, 400, 4), (3, 512, 0), (70, 64, 0), (7, 8, 0), (40, 33, 0), (300, 129, 0), (9, 300, 0), (512, 20, 8), (300, 257, 5),
          (6, 256, 16), (5, 130, 16), (9, 40, 9), (4, 200, 12), (300, 10, 13), (7, 8, 11), (3, 257, 16), (5, 64, 17)]
 
 
