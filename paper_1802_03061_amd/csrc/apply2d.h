@@ -82,6 +82,7 @@ struct BatchProb {
     const double* bvec;
     size_t stride;
     int jin, jout;
+    const double* scale;       // factor of in per Krylov column (entry j), or null
 };
 
 // Batched passes over a list of (problem index, tile) items whose problems all have this PX

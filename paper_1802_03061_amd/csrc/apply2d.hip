@@ -69,8 +69,8 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_batch(const BatchProb<T>* __res
     const int tid = threadIdx.x;
     const size_t j = dj ? (size_t)*dj : 0;
     stage_twiddles<T, PX, NTHR>(tws, d.twx, tid);
-    pass_a_tile<T, PX, TR, NTHR>(d.in + (d.jin ? j * d.stride : 0), d.work, d.nx, d.ny, d.s, 1, item.y * TR, buf, tws,
-                                 tid);
+    pass_a_tile<T, PX, TR, NTHR>(d.in + (d.jin ? j * d.stride : 0), d.work, d.nx, d.ny,
+                                 d.scale ? d.s * d.scale[j] : d.s, 1, item.y * TR, buf, tws, tid);
 }
 
 // ---------------------------------------------------------------------------- pass C --------

@@ -56,6 +56,7 @@ struct KryProb {
     double* sn;
     double* g;          // m + 1
     double* y;          // m
+    double* sc;         // m + 1: basis vector i is sc[i] times the stored one (see kb_givens)
     cx<double>* u;      // output modes (complex, L = 0)
     int nvec;
     int c0, nc;         // chunks of this problem
@@ -64,7 +65,6 @@ struct KryProb {
 struct BState {
     double target;      // absolute inner target of the current cycle
     double est;         // residual estimate after the last iteration
-    double inv;         // 1 / H[j+1][j], 0 at breakdown
     double rn;          // residual norm at the cycle start
     int jd;             // valid columns of the current cycle
     int iters;          // inner iterations so far
@@ -155,7 +155,8 @@ __global__ __launch_bounds__(BT) void kb_dots(const Chunk* __restrict__ ch, cons
         partial[(size_t)blockIdx.x * (m + 1) + i] = (red[i * 4] + red[i * 4 + 1]) + (red[i * 4 + 2] + red[i * 4 + 3]);
 }
 
-// H[0..j][j] = sum over the problem's chunks (in chunk order); one block per problem.
+// H[0..j][j] = <v_i, K v_j>: sc[i] times the sum over the problem's chunks (in chunk order); one
+// block per problem.
 __global__ __launch_bounds__(64) void kb_hcol(const KryProb* __restrict__ kp, const int* __restrict__ act,
                                               const int* __restrict__ dj, const double* __restrict__ partial, int m) {
     const int p = blockIdx.x;
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(64) void kb_hcol(const KryProb* __restrict__ kp, co
         double s = 0.0;
 #pragma unroll 8
         for (int c = 0; c < k.nc; ++c) s += partial[(size_t)(k.c0 + c) * (m + 1) + i];
-        k.H[(size_t)j * (m + 1) + i] = s;
+        k.H[(size_t)j * (m + 1) + i] = k.sc[i] * s;
     }
 }
 
@@ -208,7 +209,7 @@ __device__ __forceinline__ double chunk_update(const KryProb& k, const Chunk& c,
     return s;
 }
 
-// w -= sum_i H[i][j] V_i over the chunk; part2[chunk] = |w|^2 over the chunk afterwards.  The chunks are
+// w -= sum_i H[i][j] sc[i] V_i over the chunk; part2[chunk] = |w|^2 over the chunk afterwards.  The chunks are
 // taken backwards: the last ones the dots read are still in the memory-side cache (137 against 149 us).
 __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
                                                 const int* __restrict__ act, const int* __restrict__ dj,
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, co
     const KryProb& k = kp[c.p];
     const int j = *dj;
     const int tid = threadIdx.x;
-    for (int i = tid; i <= j; i += BT) h[i] = k.H[(size_t)j * (m + 1) + i];
+    for (int i = tid; i <= j; i += BT) h[i] = k.H[(size_t)j * (m + 1) + i] * k.sc[i];
     __syncthreads();
     double s = c.len == CHUNK ? chunk_update<true>(k, c, j, h) : chunk_update<false>(k, c, j, h);
     s = wave_sum(s);
@@ -230,6 +231,12 @@ __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, co
     if (tid == 0) part2[blk] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// The basis spans the Krylov space of K, A = I - K: A v_j = v_j - K v_j, so column j of A's Hessenberg
+// matrix is e_j - H[.][j] with -|w| below, and the applies need not read their input again.  The basis
+// vectors are stored as the update leaves them, with their factors 1/|w| in sc: pass A, the dots, the
+// update and the combination multiply by those, and no pass over w normalises it.  (128 problems of
+// 64^2 to 512^2: the normalising pass took 31 us of a step of all problems, the second read 17 us.)
+//
 // H[j+1][j] = |w|, the previous Givens rotations and a new one on column j, the residual vector
 // g and the estimate |g[j+1]|; decides whether the problem keeps iterating.  One 64-lane block per
 // problem: the lanes sum the chunk partials of |w|^2 and the squares of H[.][j] (fixed-order
@@ -254,7 +261,9 @@ __global__ __launch_bounds__(64) void kb_givens(const KryProb* __restrict__ kp, 
     BState& s = bs[p];
     w2 = w2 > 0.0 ? w2 : 0.0;
     const double hn = sqrt(w2);
-    Hj[j + 1] = hn;
+    for (int i = 0; i < j; ++i) Hj[i] = -Hj[i];
+    Hj[j] = 1.0 - Hj[j];
+    Hj[j + 1] = -hn;
     for (int i = 0; i < j; ++i) {
         const double t = k.cs[i] * Hj[i] + k.sn[i] * Hj[i + 1];
         Hj[i + 1] = -k.sn[i] * Hj[i] + k.cs[i] * Hj[i + 1];
@@ -279,20 +288,8 @@ __global__ __launch_bounds__(64) void kb_givens(const KryProb* __restrict__ kp, 
     const bool breakdown = !(hn > 1e-14 * sqrt(h2 + w2));
     s.jd = j + 1;
     s.est = est;
-    s.inv = breakdown ? 0.0 : 1.0 / hn;
+    k.sc[j + 1] = breakdown ? 0.0 : 1.0 / hn;
     if (breakdown || est <= s.target || j + 1 >= m || s.iters >= max_iter) act[p] = 0;
-}
-
-// V_{j+1} = w / H[j+1][j] for the problems still iterating.
-__global__ __launch_bounds__(BT) void kb_scale_next(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
-                                                    const int* __restrict__ act, const int* __restrict__ dj,
-                                                    const BState* __restrict__ bs) {
-    const Chunk c = ch[blockIdx.x];
-    if (!act[c.p]) return;
-    const KryProb& k = kp[c.p];
-    const double a = bs[c.p].inv;
-    double* w = k.V + (size_t)(*dj + 1) * k.nvec + c.off;
-    for (int e = threadIdx.x; e < c.len; e += BT) w[e] *= a;
 }
 
 // count[j] = the number of problems still iterating, then j += 1.  Single block.  count is
@@ -365,24 +362,53 @@ __global__ void kb_cycle_start(const KryProb* __restrict__ kp, const int* __rest
     if (p == 0) *dj = 0;
     if (p >= P || !act[p]) return;
     kp[p].g[0] = bs[p].rn;
+    kp[p].sc[0] = 1.0;   // kb_vec normalises V_0
     for (int i = 1; i <= m; ++i) kp[p].g[i] = 0.0;
 }
 
-// y = R^{-1} g over the cycle's jd columns (problems in mask without a non-finite value).
-__global__ void kb_backsolve(const KryProb* __restrict__ kp, const int* __restrict__ mask,
-                             const BState* __restrict__ bs, int m, int P) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+// y = R^{-1} g over the cycle's jd columns (problems in mask without a non-finite value), one wave per
+// problem by columns: lane l holds the running right-hand sides l and l + 64 (m <= 128), and the
+// columns' loads, which depend on no result, go out ahead.  (One thread per problem, its loads in
+// the chain: 78 us for 22 columns.)
+__global__ __launch_bounds__(64) void kb_backsolve(const KryProb* __restrict__ kp, const int* __restrict__ mask,
+                                                   const BState* __restrict__ bs, int m, int P) {
+    static_assert(RTE_MAX_RESTART <= 128, "two rows per lane");
+    const int p = blockIdx.x, l = threadIdx.x;
     if (p >= P || !mask[p] || (bs[p].flags & 2)) return;
     const KryProb& k = kp[p];
     const int jd = bs[p].jd;
-    for (int i = jd - 1; i >= 0; --i) {
-        double s = k.g[i];
-        for (int q = i + 1; q < jd; ++q) s -= k.H[(size_t)q * (m + 1) + i] * k.y[q];
-        k.y[i] = s / k.H[(size_t)i * (m + 1) + i];
+    double t0 = l < jd ? k.g[l] : 0.0, t1 = l + 64 < jd ? k.g[l + 64] : 0.0;
+    constexpr int G = 4;
+    double r0[G], r1[G];   // rows l and l + 64 of the next G columns
+    auto load = [&](int i) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const double* col = k.H + (size_t)(i - q > 0 ? i - q : 0) * (m + 1);
+            r0[q] = l <= i - q ? col[l] : 0.0;
+            r1[q] = l + 64 <= i - q ? col[l + 64] : 0.0;
+        }
+    };
+    load(jd - 1);
+    for (int i = jd - 1; i >= 0; i -= G) {
+        double a0[G], a1[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) { a0[q] = r0[q]; a1[q] = r1[q]; }
+        if (i >= G) load(i - G);
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int c = i - q;
+            if (c < 0) break;
+            const double y = c < 64 ? __shfl(t0, c, 64) / __shfl(a0[q], c, 64)
+                                    : __shfl(t1, c - 64, 64) / __shfl(a1[q], c - 64, 64);
+            t0 = l == c ? y : t0 - a0[q] * y;       // rows past the column have a zero
+            t1 = l + 64 == c ? y : t1 - a1[q] * y;
+        }
     }
+    if (l < jd) k.y[l] = t0;
+    if (l + 64 < jd) k.y[l + 64] = t1;
 }
 
-// x += sum_{i < jd} y_i V_i over the chunk.
+// x += sum_{i < jd} y_i sc[i] V_i over the chunk.
 __global__ __launch_bounds__(BT) void kb_combine(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
                                                  const int* __restrict__ mask, const BState* __restrict__ bs) {
     __shared__ double y[RTE_MAX_RESTART];
@@ -391,7 +417,7 @@ __global__ __launch_bounds__(BT) void kb_combine(const Chunk* __restrict__ ch, c
     const KryProb& k = kp[c.p];
     const int jd = bs[c.p].jd;
     if (jd <= 0) return;
-    for (int i = threadIdx.x; i < jd; i += BT) y[i] = k.y[i];
+    for (int i = threadIdx.x; i < jd; i += BT) y[i] = k.y[i] * k.sc[i];
     __syncthreads();
     for (int e = threadIdx.x; e < c.len; e += BT) {
         const size_t o = (size_t)c.off + e;
@@ -415,7 +441,8 @@ struct SizeClass {
 
 template <typename T>
 BatchProb<T> batch_prob(const rte_ctx* c, const cx<T>* Q, const cx<T>* twx, const cx<T>* twy, cx<T>* work,
-                        double s, const double* in, double* out, const double* bvec, int jin, int jout) {
+                        double s, const double* in, double* out, const double* bvec, int jin, int jout,
+                        const double* scale = nullptr) {
     BatchProb<T> d;
     d.nx = c->nx; d.ny = c->ny; d.PX = c->PX; d.PY = c->PY;
     d.s = s;
@@ -423,6 +450,7 @@ BatchProb<T> batch_prob(const rte_ctx* c, const cx<T>* Q, const cx<T>* twx, cons
     d.in = in; d.out = out; d.bvec = bvec;
     d.stride = c->nvec;
     d.jin = jin; d.jout = jout;
+    d.scale = scale;
     return d;
 }
 
@@ -584,7 +612,7 @@ int tune_plan(Plan& pl, rte_ctx* const* ctxs) {
     auto launch = [&](const SizeClass& k, int which) {
         if (which == 1) return apply2d_batch_pass_b<T>(k.PY, probs, k.db, (int)k.b.size(), pl.d_act, k.vb, st);
         if (apply2d_batch_pass_a<T>(k.PX, probs, k.dac, (int)k.ac.size(), pl.d_act, pl.d_j, k.vr, st)) return -1;
-        return apply2d_batch_pass_c<T>(k.PX, probs, k.dac, (int)k.ac.size(), pl.d_act, pl.d_j, APPLY_A, k.vr, st);
+        return apply2d_batch_pass_c<T>(k.PX, probs, k.dac, (int)k.ac.size(), pl.d_act, pl.d_j, APPLY_KT, k.vr, st);
     };
     auto timed = [&](SizeClass& k, int which, double* ms) -> int {
         fill_items(k, ctxs, apply2d_batch_rows<T>(k.vr), apply2d_batch_cols<T>(k.PY, k.vb));
@@ -652,7 +680,7 @@ int build_plan(Plan& pl, int P, rte_ctx* const* ctxs) {
     std::vector<std::pair<size_t, size_t>> room;
     for (auto& k : pl.cls) room.push_back(item_room<T>(k, ctxs));
     const int NCH = pl.NCH = (int)pl.chunks.size();
-    const size_t S = pl.S = (size_t)(m + 1) * m + 4 * (size_t)m + 2;   // Arnoldi slab per problem
+    const size_t S = pl.S = (size_t)(m + 1) * m + 5 * (size_t)m + 3;   // Arnoldi slab per problem
     size_t items = 0;
     for (auto& r : room) items += r.first + r.second;
     for (auto& k : pl.cls_d) items += k.ac.size() + k.b.size();
@@ -698,12 +726,13 @@ int build_plan(Plan& pl, int P, rte_ctx* const* ctxs) {
         k.sn = k.cs + m;
         k.g = k.sn + m;
         k.y = k.g + m + 1;
+        k.sc = k.y + m;
         k.u = nullptr;
         const double s = c->mu_s * c->sigma[0];
         if constexpr (sizeof(T) == 4)
-            it[p] = batch_prob<float>(c, c->Qf, c->twf[0], c->twf[1], c->wf, s, k.V, k.V, nullptr, 1, 1);
+            it[p] = batch_prob<float>(c, c->Qf, c->twf[0], c->twf[1], c->wf, s, k.V, k.V, nullptr, 1, 1, k.sc);
         else
-            it[p] = batch_prob<double>(c, c->Qd, c->twd[0], c->twd[1], c->wd, s, k.V, k.V, nullptr, 1, 1);
+            it[p] = batch_prob<double>(c, c->Qd, c->twd[0], c->twd[1], c->wd, s, k.V, k.V, nullptr, 1, 1, k.sc);
         res[p] = batch_prob<double>(c, c->Qd, c->twd[0], c->twd[1], c->wd, s, c->xv, c->rv, c->bv, 0, 0);
     }
     BK_TRY(hipMemcpyAsync(pl.d_ch, pl.chunks.data(), sizeof(Chunk) * NCH, hipMemcpyHostToDevice, st));
@@ -728,13 +757,12 @@ int build_plan(Plan& pl, int P, rte_ctx* const* ctxs) {
     // h_cnt[i], which the host polls one replay behind
     const unsigned gP = (unsigned)((P + 63) / 64);
     BK_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeRelaxed));
-    int crc = apply_batch<T>(pl.cls, (const BatchProb<T>*)pl.d_it, pl.d_act, pl.d_j, APPLY_A, st);
+    int crc = apply_batch<T>(pl.cls, (const BatchProb<T>*)pl.d_it, pl.d_act, pl.d_j, APPLY_KT, st);
     hipLaunchKernelGGL(kb_dots, dim3(NCH), dim3(BT), 0, st, pl.d_ch, pl.d_kp, pl.d_act, pl.d_j, pl.d_part, m);
     hipLaunchKernelGGL(kb_hcol, dim3(P), dim3(64), 0, st, pl.d_kp, pl.d_act, pl.d_j, pl.d_part, m);
     hipLaunchKernelGGL(kb_update, dim3(NCH), dim3(BT), 0, st, pl.d_ch, pl.d_kp, pl.d_act, pl.d_j, pl.d_part2, m);
     hipLaunchKernelGGL(kb_givens, dim3(P), dim3(64), 0, st, pl.d_kp, pl.d_act, pl.d_j, pl.d_part2, pl.d_bs, m, P,
                        pl.d_maxit);
-    hipLaunchKernelGGL(kb_scale_next, dim3(NCH), dim3(BT), 0, st, pl.d_ch, pl.d_kp, pl.d_act, pl.d_j, pl.d_bs);
     hipLaunchKernelGGL(kb_tick, dim3(1), dim3(BT), 0, st, pl.d_j, pl.d_act, P, pl.h_cnt_dev);
     hipError_t ce = hipStreamEndCapture(st, &pl.graph);
     if (crc) return set_error(RTE_EUNSUPPORTED, "batched apply: unsupported size");
@@ -806,7 +834,6 @@ int run_plan(Plan& pl, rte_ctx* const* ctxs, const double* const* f, const doubl
             h_bs[p].target = target;
             h_bs[p].rn = rn[p];
             h_bs[p].jd = 0;
-            h_bs[p].inv = 0.0;
             h_bs[p].flags = 0;
         }
         BK_TRY(hipMemcpyAsync(pl.d_bs, h_bs, sizeof(BState) * P, hipMemcpyHostToDevice, st));
@@ -834,7 +861,7 @@ int run_plan(Plan& pl, rte_ctx* const* ctxs, const double* const* f, const doubl
             }
         }
         // x += V y, r = b - A x (FP64), |r|
-        hipLaunchKernelGGL(kb_backsolve, dim3(gP), dim3(64), 0, st, pl.d_kp, pl.d_todo, pl.d_bs, m, P);
+        hipLaunchKernelGGL(kb_backsolve, dim3(P), dim3(64), 0, st, pl.d_kp, pl.d_todo, pl.d_bs, m, P);
         hipLaunchKernelGGL(kb_combine, dim3(NCH), dim3(BT), 0, st, pl.d_ch, pl.d_kp, pl.d_todo, pl.d_bs);
         if (apply_batch<double>(pl.cls_d, pl.d_res, pl.d_todo, nullptr, APPLY_RESID, st))
             return set_error(RTE_EUNSUPPORTED, "batched apply: unsupported size");
@@ -959,7 +986,7 @@ int time_plan(Plan& pl, int reps, double* ms_total, int max_launch, int* n_launc
                           : pass == 1
                               ? apply2d_batch_pass_b<T>(k.PY, probs, k.db, (int)k.b.size(), pl.d_act, k.vb, st)
                               : apply2d_batch_pass_c<T>(k.PX, probs, k.dac, (int)k.ac.size(), pl.d_act, pl.d_j,
-                                                        APPLY_A, k.vr, st);
+                                                        APPLY_KT, k.vr, st);
                 if (bad) { rc = set_error(RTE_EUNSUPPORTED, "batched apply: unsupported size"); break; }
                 if (hipEventRecord(ev[++q], st) != hipSuccess) { rc = set_error(RTE_EDEVICE, "hipEventRecord failed"); break; }
             }
