@@ -2,10 +2,12 @@
 #pragma once
 #include "../../include/rte.h"
 #include "common.h"
+#include "krylov.h"
 
 namespace rte {
 
-enum { APPLY_A = 0, APPLY_KT = 1, APPLY_RESID = 2 };
+// APPLY_K: K = K~ D alone (pass C as APPLY_KT, with the factors of APPLY_A)
+enum { APPLY_A = 0, APPLY_KT = 1, APPLY_RESID = 2, APPLY_K = 3 };
 
 struct ChanScale {
     double s[2 * RTE_MAX_L + 1];   // per-channel factor applied in pass A (D for operator A, 1 for K~)
@@ -118,6 +120,12 @@ int apply2d(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mo
             const ChanScale& sc, int nbatch);
 template <typename T, typename TV>
 int apply2d_pass_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, int nbatch);
+// The Gram-Schmidt update of Krylov vector w = K u_j against u_0 .. u_j (rows of V, pitch ld) and pass A
+// of the next apply, whose input it is, in one launch (k_update_a); t: the column's Arnoldi state.
+// partial takes one partial sum of |u_{j+1}|^2 per block, at most one per grid row; *nblk: their number.
+template <typename T, typename TV>
+int apply2d_update_a(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
+                     const ChanScale& sc, int nbatch, int* nblk);
 template <typename T>
 int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch);
 // Whether pass B runs in split form (a full-length buffer, work2, between its transforms and its

@@ -28,9 +28,11 @@
 #include "apply2d.h"
 #include "apply2d_b.h"
 #include "apply2d_tile.h"
+#include "arnoldi_dev.h"
 #include "fft.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rte {
 
@@ -53,6 +55,85 @@ __global__ __launch_bounds__(NTHR) void k_pass_a(const TV* __restrict__ x, cx<T>
     pass_a_tile<T, PX, TR, NTHR, TV, STAGED>(x + (size_t)bc * ny * nx, Tb + (size_t)bc * NKS * ny, nx, ny,
                                              sc.s[bc % C], pack, xcd_tile(blockIdx.x, gridDim.x) * TR, buf, tws,
                                              tid, cc, cF, cs, crow);
+}
+
+// The plain solver's Gram-Schmidt update fused with pass A of the next apply.  The basis spans the
+// Krylov space of K (A = I - K), so the apply needs its input only here; basis vector i is inv[i] times
+// the stored u_i, where inv comes from the exact |u_i|^2 that the next reduction adds up, so that
+// nothing rescales u_i and one pass reads w and writes u_{j+1} and its x-spectrum:
+//     u_{j+1} = a (w - sum_i inv_i^2 <u_i, w> u_i),  w = K u_j,  a as in arnoldi_stage0_lazy.
+// Bound: HBM, the basis read once; the tiles are taken backwards, since the last lines the dots read
+// are still in the memory-side cache.  At 512^2, L = 8 in FP32 with 12 basis vectors it takes 100 us
+// (5.3 TB/s), where the update (88), the rescaling launch (6) and pass A (17) took 111, and pass C without
+// its input 18.5 instead of 21.5; a solve of 37 iterations 6.57 -> 6.06 ms.  G vectors' loads are in flight at
+// once, as many as registers hold.
+template <typename T, int PX, int TR, int NTHR, typename TV>
+__global__ __launch_bounds__(NTHR) void k_update_a(TV* w, const TV* V, size_t ld, ArnoldiArgs t, double* partial,
+                                                   cx<T>* Tb, const cx<T>* tw, int nx, int ny, int C, ChanScale sc,
+                                                   int pack) {
+    using P = PassATile<PX, TR, NTHR>;
+    constexpr int IT = P::IT, RH = P::RH;
+    constexpr int E = 2 * IT * RH, G = E >= 16 ? 1 : (E >= 8 ? 2 : (E >= 4 ? 4 : 8));   // vectors in flight
+    __shared__ cx<T> buf[TR / 2 * P::LD];
+    __shared__ cx<T> tws[PX];
+    __shared__ double nc[RTE_KRYLOV_MAXVEC], g[RTE_KRYLOV_MAXVEC];
+    __shared__ double red[NTHR / 64], a_sh;
+    const int tid = threadIdx.x;
+    const int bx = gridDim.x - 1 - blockIdx.x, bc = gridDim.y - 1 - blockIdx.y;
+    const int y0 = xcd_tile(bx, gridDim.x) * TR;
+    const size_t base = (size_t)bc * ny * nx;
+    TV la[IT][RH], lb[IT][RH];
+    pass_a_load<PX, TR, NTHR>(w + base, nx, ny, y0, tid, la, lb);
+    stage_twiddles<T, PX, NTHR>(tws, tw, tid);
+    arnoldi_stage0_lazy<NTHR>(t, bx == 0 && bc == 0, nc, g, &a_sh);
+    double ra[IT][RH], rb[IT][RH];
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int r = 0; r < RH; ++r) { ra[it][r] = (double)la[it][r]; rb[it][r] = (double)lb[it][r]; }
+    auto subtract = [&](int i, auto gc) {
+        constexpr int N = decltype(gc)::value;
+        TV va[N][IT][RH], vb[N][IT][RH];
+#pragma unroll
+        for (int q = 0; q < N; ++q) pass_a_load<PX, TR, NTHR>(V + (size_t)(i + q) * ld + base, nx, ny, y0, tid, va[q], vb[q]);
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const double c = nc[i + q];
+#pragma unroll
+            for (int it = 0; it < IT; ++it)
+#pragma unroll
+                for (int r = 0; r < RH; ++r) {
+                    ra[it][r] += c * (double)va[q][it][r];
+                    rb[it][r] += c * (double)vb[q][it][r];
+                }
+        }
+    };
+    int i = 0;
+#pragma unroll 1
+    for (; i + G <= t.j + 1; i += G) subtract(i, std::integral_constant<int, G>{});
+#pragma unroll 1
+    for (; i <= t.j; ++i) subtract(i, std::integral_constant<int, 1>{});
+    __syncthreads();   // a_sh
+    const double a = a_sh;
+    double nrm = 0.0;
+    P::each(nx, ny, y0, tid, [&](int it, int r, bool oka, bool okb, int ya, int m) {
+        const TV qa = (TV)(oka ? a * ra[it][r] : 0.0), qb = (TV)(okb ? a * rb[it][r] : 0.0);
+        if (oka) w[base + (size_t)ya * nx + m] = qa;
+        if (okb) w[base + (size_t)(ya + 1) * nx + m] = qb;
+        ra[it][r] = (double)qa;
+        rb[it][r] = (double)qb;
+        nrm += ra[it][r] * ra[it][r] + rb[it][r] * rb[it][r];
+    });
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
+    if ((tid & 63) == 0) red[tid >> 6] = nrm;
+    const int NKS = pack ? PX / 2 : PX / 2 + 1;
+    pass_a_transform<T, PX, TR, NTHR>(ra, rb, Tb + (size_t)bc * NKS * ny, ny, sc.s[bc % C], pack, y0, buf, tws, tid);
+    if (tid == 0) {   // red: written before the transform's barriers
+        double s = 0.0;
+        for (int v = 0; v < NTHR / 64; ++v) s += red[v];
+        partial[(size_t)bc * gridDim.x + bx] = s;
+    }
 }
 
 // Batched form (isotropic problems of one padded size): one block per (problem, row tile).
@@ -257,6 +338,26 @@ static void launch_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, 
 }
 
 template <typename T, int PX, int TR, typename TV>
+static void launch_ua_tr(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
+                         const ChanScale& sc, int nchan_total, int* nblk) {
+    dim3 grid((a.ny + TR - 1) / TR, nchan_total);
+    *nblk = (int)(grid.x * grid.y);
+    hipLaunchKernelGGL((k_update_a<T, PX, TR, 256, TV>), grid, dim3(256), 0, a.stream, w, V, ld, t, partial, a.work,
+                       a.twx, a.nx, a.ny, a.C, sc, a.pack);
+}
+// the row tiles of pass A
+template <typename T, int PX, typename TV>
+static void launch_ua(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
+                      const ChanScale& sc, int nchan_total, int* nblk) {
+    constexpr int TR = tile_rows<T>();
+    if constexpr (PX >= 128) {
+        if (a.var[0] == 1) return launch_ua_tr<T, PX, TR / 2>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+        if (a.var[0] == 2) return launch_ua_tr<T, PX, TR * 2>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+        if (a.var[0] == 3) return launch_ua_tr<T, PX, TR / 4>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+    }
+    launch_ua_tr<T, PX, TR>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+}
+template <typename T, int PX, int TR, typename TV>
 static void launch_c_tr(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                         int nchan_total) {
     dim3 grid((a.ny + TR - 1) / TR, nchan_total);
@@ -367,6 +468,12 @@ int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch) {
     return pass_b_large<T>(a, nbatch);
 }
 template <typename T, typename TV>
+int apply2d_update_a(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
+                     const ChanScale& sc, int nbatch, int* nblk) {
+    RTE_P_SWITCH(a.PX, launch_ua, a, w, V, ld, t, partial, sc, nbatch * a.C, nblk);
+    return 0;
+}
+template <typename T, typename TV>
 int apply2d_pass_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                    int nbatch) {
     RTE_P_SWITCH(a.PX, launch_c, a, x, b, y, mode, nbatch * a.C);
@@ -464,6 +571,8 @@ int apply2d_from_b(const Apply2DArgs<T>& a, const TV* x, TV* y) {
     template int apply2d<T, TV>(const Apply2DArgs<T>&, const TV*, const double*, TV*, int, const ChanScale&, \
                                 int);                                                                       \
     template int apply2d_pass_a<T, TV>(const Apply2DArgs<T>&, const TV*, const ChanScale&, int);            \
+    template int apply2d_update_a<T, TV>(const Apply2DArgs<T>&, TV*, const TV*, size_t, const ArnoldiArgs&, \
+                                         double*, const ChanScale&, int, int*);                             \
     template int apply2d_pass_c<T, TV>(const Apply2DArgs<T>&, const TV*, const double*, TV*, int, int);     \
     template int apply2d_from_b<T, TV>(const Apply2DArgs<T>&, const TV*, TV*);
 RTE_APPLY2D_INST(float, double)

@@ -58,54 +58,72 @@ __device__ __forceinline__ int xcd_tile(int b, int G) { return (G & 7) ? b : (b 
 // ---------------------------------------------------------------------------- pass A --------
 // With pack != 0 the x-frequencies 0 and PX/2, whose values are real for real rows, share
 // column 0 of T as (X[0], X[PX/2]); T then has PX/2 columns.
-// One tile of TR rows of one channel: xin is the channel's [ny][nx] input, out its [NKS][ny]
-// transposed x-spectrum; tws holds the staged twiddles.
+//
+// A tile is TR rows of one channel.  Rows y0+2p (real part) and y0+2p+1 (imaginary part); only
+// m < nx <= PX/2 is non-zero, so the first Stockham stage (radix R0, no twiddles) runs in registers
+// on the loads: butterfly j takes m = j + r PX/R0 (non-zero only for r < R0/2) and writes its R0
+// outputs at j R0 + r.
+template <int PX, int TR, int NTHR>
+struct PassATile {
+    static constexpr int NP = TR / 2;        // complex FFTs per block (two real rows each)
+    static constexpr int LD = padded(PX) + 1;   // odd row pitch: the NP transforms start on different banks
+    static constexpr int R0 = fft_radix(PX, 1);
+    static constexpr int NB0 = PX / R0;
+    static constexpr int NBT = NP * NB0;
+    static constexpr int IT = (NBT + NTHR - 1) / NTHR;
+    static constexpr int RH = R0 / 2;
+    // f(it, r, in row a's range, in row b's range, row a, column) for every input of this thread
+    template <typename F>
+    static __device__ __forceinline__ void each(int nx, int ny, int y0, int tid, F f) {
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int idx = tid + it * NTHR;
+            const int p = idx / NB0, j = idx % NB0;
+            const int ya = y0 + 2 * p;
+#pragma unroll
+            for (int r = 0; r < RH; ++r) {
+                const int m = j + r * NB0;
+                const bool ok = (NBT % NTHR == 0 || idx < NBT) && m < nx;
+                f(it, r, ok && ya < ny, ok && ya + 1 < ny, ya, m);
+            }
+        }
+    }
+};
+
+// Every load of the tile is issued before the first use: the loads take a clamped index (the
+// channel's first entry when out of range) instead of a branch, and the widening to FP64
+// follows all of them (a conversion next to each load made the FP32 loads wait one by one).
+template <int PX, int TR, int NTHR, typename TV, int IT, int RH>
+__device__ __forceinline__ void pass_a_load(const TV* xin, int nx, int ny, int y0, int tid, TV (&la)[IT][RH],
+                                            TV (&lb)[IT][RH]) {
+    PassATile<PX, TR, NTHR>::each(nx, ny, y0, tid, [&](int it, int r, bool oka, bool okb, int ya, int m) {
+        la[it][r] = xin[oka ? (size_t)ya * nx + m : 0];
+        lb[it][r] = xin[okb ? (size_t)(ya + 1) * nx + m : 0];
+    });
+}
+
+// The tile's transforms: inputs ra, rb times s, out the channel's [NKS][ny] transposed x-spectrum;
+// tws holds the staged twiddles.
+template <typename T, int PX, int TR, int NTHR, int IT, int RH>
+__device__ __forceinline__ void pass_a_transform(const double (&ra)[IT][RH], const double (&rb)[IT][RH],
+                                                 cx<T>* __restrict__ out, int ny, double s, int pack, int y0,
+                                                 cx<T>* buf, const cx<T>* tws, int tid);
+
+// One tile: xin is the channel's [ny][nx] input.
 template <typename T, int PX, int TR, int NTHR, typename TV, bool STAGED = false>
 __device__ __forceinline__ void pass_a_tile(const TV* __restrict__ xin, cx<T>* __restrict__ out, int nx, int ny,
                                             double s, int pack, int y0, cx<T>* buf, const cx<T>* tws, int tid,
                                             const float* __restrict__ corr_c = nullptr, int cF = 1, double cs = 0.0,
                                             float* crow = nullptr) {
-    constexpr int NP = TR / 2;        // complex FFTs per block (two real rows each)
-    constexpr int LD = padded(PX) + 1;   // odd row pitch: the NP transforms start on different banks
-    constexpr int H = PX / 2;
-    // Rows y0+2p (real part) and y0+2p+1 (imaginary part); only m < nx <= PX/2 is non-zero, so the
-    // first Stockham stage (radix R0, no twiddles) runs in registers on the loads: butterfly j takes
-    // m = j + r PX/R0 (non-zero only for r < R0/2) and writes its R0 outputs at j R0 + r.
-    constexpr int R0 = fft_radix(PX, 1);
-    constexpr int NB0 = PX / R0;
-    constexpr int NBT = NP * NB0;
-    constexpr int IT = (NBT + NTHR - 1) / NTHR;
-    // Every load of the tile is issued before the first use: the loads take a clamped index (the
-    // channel's first entry when out of range) instead of a branch, and the widening to FP64
-    // follows all of them (a conversion next to each load made the FP32 loads wait one by one).
+    using P = PassATile<PX, TR, NTHR>;
+    constexpr int NB0 = P::NB0, NBT = P::NBT, IT = P::IT, R0 = P::R0;
     TV la[IT][R0 / 2], lb[IT][R0 / 2];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int idx = tid + it * NTHR;
-        const int p = idx / NB0, j = idx % NB0;
-        const int ya = y0 + 2 * p, yb = ya + 1;
-#pragma unroll
-        for (int r = 0; r < R0 / 2; ++r) {
-            const int m = j + r * NB0;
-            const bool ok = (NBT % NTHR == 0 || idx < NBT) && m < nx;
-            la[it][r] = xin[(ok && ya < ny) ? (size_t)ya * nx + m : 0];
-            lb[it][r] = xin[(ok && yb < ny) ? (size_t)yb * nx + m : 0];
-        }
-    }
+    pass_a_load<PX, TR, NTHR>(xin, nx, ny, y0, tid, la, lb);
     double ra[IT][R0 / 2], rb[IT][R0 / 2];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-        const int idx = tid + it * NTHR;
-        const int p = idx / NB0, j = idx % NB0;
-        const int ya = y0 + 2 * p, yb = ya + 1;
-#pragma unroll
-        for (int r = 0; r < R0 / 2; ++r) {
-            const int m = j + r * NB0;
-            const bool ok = (NBT % NTHR == 0 || idx < NBT) && m < nx;
-            ra[it][r] = (ok && ya < ny) ? (double)la[it][r] : 0.0;
-            rb[it][r] = (ok && yb < ny) ? (double)lb[it][r] : 0.0;
-        }
-    }
+    P::each(nx, ny, y0, tid, [&](int it, int r, bool oka, bool okb, int, int) {
+        ra[it][r] = oka ? (double)la[it][r] : 0.0;
+        rb[it][r] = okb ? (double)lb[it][r] : 0.0;
+    });
     if (STAGED) {
         // y-interpolated coarse rows in LDS (nx / cF <= CORR_WMAX), as in pass C; a separate
         // instantiation, since one kernel holding both forms needed 102 registers instead of 66
@@ -144,6 +162,15 @@ __device__ __forceinline__ void pass_a_tile(const TV* __restrict__ xin, cx<T>* _
             }
         }
     }
+    pass_a_transform<T, PX, TR, NTHR>(ra, rb, out, ny, s, pack, y0, buf, tws, tid);
+}
+
+template <typename T, int PX, int TR, int NTHR, int IT, int RH>
+__device__ __forceinline__ void pass_a_transform(const double (&ra)[IT][RH], const double (&rb)[IT][RH],
+                                                 cx<T>* __restrict__ out, int ny, double s, int pack, int y0,
+                                                 cx<T>* buf, const cx<T>* tws, int tid) {
+    using P = PassATile<PX, TR, NTHR>;
+    constexpr int NP = P::NP, LD = P::LD, R0 = P::R0, NB0 = P::NB0, NBT = P::NBT, H = PX / 2;
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int idx = tid + it * NTHR;

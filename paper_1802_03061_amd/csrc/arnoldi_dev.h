@@ -69,7 +69,9 @@ __device__ __forceinline__ void arnoldi_stage0_in_update(const ArnoldiArgs& t, c
 // on breakdown) it sets flags[3] and inv[j+1] = 1/sqrt(nu2), and the caller's rescale pass, which
 // runs only under that flag, makes the stored vector unit-norm with H[j+1, j] = sqrt(nu2)/a.
 // st layout: [0..m] h pass 1 | [m+1] |w|^2 | [m+2] |w1|^2 | [m+4..2m+4] h pass 2 | [2m+5] a
-__device__ __forceinline__ void arnoldi_block(const ArnoldiArgs t) {
+// of_k: the columns are those of K; A v_j = v_j - K v_j makes A's column e_j - h with -H[j+1, j] below.
+// nu2, when given, stands for st[j+2].
+__device__ __forceinline__ void arnoldi_block(const ArnoldiArgs t, const double* nu2 = nullptr) {
     __shared__ double red[ARN_MAXROW];
     __shared__ double hl[ARN_MAXROW], csl[ARN_MAXROW], snl[ARN_MAXROW];
     const int tid = threadIdx.x, nt = blockDim.x;
@@ -106,7 +108,7 @@ __device__ __forceinline__ void arnoldi_block(const ArnoldiArgs t) {
     const int second = flags[0];
     const int prev_nonfinite = flags[2];
     const double w0 = st[m + 3];
-    const double w1r = st[j + 2];
+    const double w1r = nu2 ? *nu2 : st[j + 2];
     const double a = t.fused ? st[2 * m + 5] : 1.0;
     const double gj = t.g[j];
     if (second) {
@@ -126,6 +128,10 @@ __device__ __forceinline__ void arnoldi_block(const ArnoldiArgs t) {
         inv = breakdown ? 0.0 : 1.0 / hn;
     }
     hl[j + 1] = hval;
+    if (t.of_k) {
+        for (int i = 0; i <= j + 1; ++i) hl[i] = -hl[i];
+        hl[j] += 1.0;
+    }
     for (int i = 0; i < j; ++i) {
         const double x = csl[i] * hl[i] + snl[i] * hl[i + 1];
         hl[i + 1] = -snl[i] * hl[i] + csl[i] * hl[i + 1];
@@ -214,6 +220,34 @@ __device__ __forceinline__ double arnoldi_stage1_in_rescale(const ArnoldiArgs& t
     if (blockIdx.x == 0) arnoldi_block(t);
     __syncthreads();
     return inv_sh;
+}
+
+// Stage 0 of a column of K with lazy factors (k_update_a): the basis vectors are inv[i] times the
+// stored u_i, and raw[i] = <u_i, w> (t.st), w = K u_j.  For the update w - sum_i c_i u_i: c_i =
+// inv[i]^2 raw[i], returned negative in nc (LDS), and the factor a that makes the result near unit
+// length (fused_factor), in *a_sh.  The first block also stores H[i][j] = inv[i] inv[j] raw[i] and, for
+// stage 1, |K v_j|^2 and a / inv[j].  g: as nc.  The caller synchronises the block before it reads them.
+template <int NTHR>
+__device__ __forceinline__ void arnoldi_stage0_lazy(const ArnoldiArgs& t, bool first_block, double* nc, double* g,
+                                                    double* a_sh) {
+    const int j = t.j, m = t.m;
+    for (int i = threadIdx.x; i <= j; i += NTHR) {
+        const double f = t.inv[i], gi = f * t.st[i];
+        g[i] = gi;
+        nc[i] = -f * gi;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const double w0 = t.st[j + 1], a = fused_factor(w0, sum_sq(g, j));
+    *a_sh = a;
+    if (first_block) {
+        const double f = t.inv[j];
+        double* Hj = t.H + (size_t)j * (m + 1);
+        for (int i = 0; i <= j; ++i) Hj[i] = f * g[i];
+        t.flags[0] = 0;
+        t.st[m + 3] = w0 * f * f;
+        t.st[2 * m + 5] = a / f;
+    }
 }
 
 }  // namespace rte

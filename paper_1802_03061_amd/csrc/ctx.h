@@ -56,6 +56,7 @@ struct rte_ctx {
     unsigned char* V = nullptr;
     double* Z = nullptr;
     double* partial = nullptr;
+    double* partial_u = nullptr;   // per-block norms of the update fused with pass A: one per grid row
     double* dsmall = nullptr;
     double* arn = nullptr;      // device Arnoldi state (H, Givens, g, estimates)
     int* arn_flags = nullptr;   // [second pass, breakdown, non-finite, spare]

@@ -35,20 +35,38 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
     return r;
 }
 
+// Stage 1 of the column t (one block), |u|^2 = the sum of upd[0..nupd) (the update's partial sums).
+__device__ __forceinline__ void arn1_block(const ArnoldiArgs& t, const double* __restrict__ upd, int nupd) {
+    __shared__ double nu2;
+    const double s = block_sum_fixed(upd, nupd);
+    if (threadIdx.x == 0) nu2 = s;
+    __syncthreads();
+    arnoldi_block(t, &nu2);
+}
+__global__ __launch_bounds__(KT) void k_arn1(ArnoldiArgs t, const double* __restrict__ upd, int nupd) {
+    arn1_block(t, upd, nupd);
+}
+
 // partial[v * nblk + blk] = sum over the block's slice of V[v][i] * w[i] for the NV vectors V[v]
 // (v < NV, row stride ld), and norm_partial[blk] = sum of w[i]^2 over the slice when norm_partial
 // is given.  The vector count is a template parameter so that every load of a step is issued before
 // the first multiply.  With even n and ld (and 16-byte aligned V and w) each thread reads element
-// pairs as 16-byte loads.  The slice a block covers and the order of its sums do not depend on the data.
+// pairs as 16-byte loads.  With upd, one more block (the first to start) runs stage 1 of the column
+// before, which nothing needs until this column's update: 7 us out of the way of the step.  The slice a block covers and the order of its sums do not depend on the data.
 template <int NV, bool PAIRS, typename TV>
 __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, size_t ld,
                                                     const TV* __restrict__ w, size_t n,
                                                     double* __restrict__ partial,
                                                     double* __restrict__ norm_partial,
-                                                    const int* __restrict__ active) {
+                                                    const int* __restrict__ active, ArnoldiArgs t,
+                                                    const double* __restrict__ upd, int nupd) {
     __shared__ double sh[KT / 64];
     if (active && *active == 0) return;
-    const int nblk = gridDim.x;
+    const int blk = (int)blockIdx.x - (upd ? 1 : 0), nblk = (int)gridDim.x - (upd ? 1 : 0);
+    if (blk < 0) {
+        arn1_block(t, upd, nupd);
+        return;
+    }
     const bool do_norm = norm_partial != nullptr;
     double acc[NV > 0 ? NV : 1];
 #pragma unroll
@@ -60,7 +78,7 @@ __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, si
         const size_t np = n / 2, ldp = ld / 2;
         const P2* w2 = reinterpret_cast<const P2*>(w);
         const P2* V2 = reinterpret_cast<const P2*>(V);
-        for (size_t i = (size_t)blockIdx.x * KT + threadIdx.x; i < np; i += stride) {
+        for (size_t i = (size_t)blk * KT + threadIdx.x; i < np; i += stride) {
             const P2 wl = w2[i];
             P2 al[NV > 0 ? NV : 1];
 #pragma unroll
@@ -71,7 +89,7 @@ __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, si
             for (int v = 0; v < NV; ++v) acc[v] += (double)al[v].x * wx + (double)al[v].y * wy;
         }
     } else {
-        for (size_t i = (size_t)blockIdx.x * KT + threadIdx.x; i < n; i += stride) {
+        for (size_t i = (size_t)blk * KT + threadIdx.x; i < n; i += stride) {
             const double wi = (double)w[i];
             double a[NV > 0 ? NV : 1];
 #pragma unroll
@@ -84,22 +102,24 @@ __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, si
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const double s = block_sum(acc[v], sh);
-        if (threadIdx.x == 0) partial[(size_t)v * nblk + blockIdx.x] = s;
+        if (threadIdx.x == 0) partial[(size_t)v * nblk + blk] = s;
     }
     if (do_norm) {
         const double s = block_sum(nrm, sh);
-        if (threadIdx.x == 0) norm_partial[blockIdx.x] = s;
+        if (threadIdx.x == 0) norm_partial[blk] = s;
     }
 }
 
 template <bool PAIRS, typename TV>
 static void launch_dots(int nv, unsigned nblk, hipStream_t st, const TV* V, size_t ld, const TV* w, size_t n,
-                        double* partial, double* norm_partial, const int* active) {
+                        double* partial, double* norm_partial, const int* active, const ArnoldiArgs& t,
+                        const double* upd, int nupd) {
+    const unsigned grid = nblk + (upd ? 1 : 0);
     switch (nv) {
 #define RTE_DOTS_CASE(K)                                                                                     \
     case K:                                                                                                  \
-        hipLaunchKernelGGL((k_dot_partial<K, PAIRS, TV>), dim3(nblk), dim3(KT), 0, st, V, ld, w, n, partial,     \
-                           norm_partial, active);                                                            \
+        hipLaunchKernelGGL((k_dot_partial<K, PAIRS, TV>), dim3(grid), dim3(KT), 0, st, V, ld, w, n, partial,     \
+                           norm_partial, active, t, upd, nupd);                                                            \
         break;
         RTE_DOTS_CASE(0) RTE_DOTS_CASE(1) RTE_DOTS_CASE(2) RTE_DOTS_CASE(3) RTE_DOTS_CASE(4) RTE_DOTS_CASE(5)
         RTE_DOTS_CASE(6) RTE_DOTS_CASE(7) RTE_DOTS_CASE(8) RTE_DOTS_CASE(9) RTE_DOTS_CASE(10) RTE_DOTS_CASE(11)
@@ -109,11 +129,9 @@ static void launch_dots(int nv, unsigned nblk, hipStream_t st, const TV* V, size
     }
 }
 
-// out[v] = sum_b partial[v * nblk + b] in a fixed order.
-__global__ __launch_bounds__(KT) void k_reduce_partials(const double* __restrict__ partial, int nblk,
-                                                        double* __restrict__ out, const int* __restrict__ active) {
-    __shared__ double sh[KT / 64];
-    if (active && *active == 0) return;
+// out[v] = sum_b partial[v * nblk + b] in a fixed order, v the block.
+__device__ __forceinline__ void reduce_row(const double* __restrict__ partial, int nblk, double* __restrict__ out,
+                                           double* sh) {
     const int v = blockIdx.x;
     const double* __restrict__ p = partial + (size_t)v * nblk;
     double s = 0.0;
@@ -125,6 +143,12 @@ __global__ __launch_bounds__(KT) void k_reduce_partials(const double* __restrict
     for (; b < nblk; b += KT) s += p[b];
     s = block_sum(s, sh);
     if (threadIdx.x == 0) out[v] = s;
+}
+__global__ __launch_bounds__(KT) void k_reduce_partials(const double* __restrict__ partial, int nblk,
+                                                        double* __restrict__ out, const int* __restrict__ active) {
+    __shared__ double sh[KT / 64];
+    if (active && *active == 0) return;
+    reduce_row(partial, nblk, out, sh);
 }
 
 // A thread's last index below n (n: none); a step of stride down from its first wraps to above n.
@@ -194,15 +218,15 @@ __global__ __launch_bounds__(KT) void k_cgs_update(TV* __restrict__ w, const TV*
     if (threadIdx.x == 0) partial_norm[blockIdx.x] = t;
 }
 
-// x[i] += sum_v Z[v][i] y[v]; nothing when skip is given and skip[2] (the device's non-finite
+// x[i] += sum_v Z[v][i] f[v] y[v] (f NULL: 1); nothing when skip is given and skip[2] (the device's non-finite
 // flag) is set.
 template <typename TV>
 __global__ __launch_bounds__(KT) void k_combine(double* __restrict__ x, const TV* __restrict__ Z, size_t ld,
                                                 int nvec, const double* __restrict__ y, size_t n,
-                                                const int* __restrict__ skip) {
+                                                const int* __restrict__ skip, const double* __restrict__ f) {
     __shared__ double ys[RTE_KRYLOV_MAXVEC];
     if (skip && skip[2] != 0) return;
-    for (int v = threadIdx.x; v < nvec; v += KT) ys[v] = y[v];
+    for (int v = threadIdx.x; v < nvec; v += KT) ys[v] = f ? f[v] * y[v] : y[v];
     __syncthreads();
     const size_t stride = (size_t)gridDim.x * KT;
     for (size_t i = (size_t)blockIdx.x * KT + threadIdx.x; i < n; i += stride) {
@@ -276,7 +300,9 @@ __global__ __launch_bounds__(256) void k_back_solve(const double* __restrict__ H
 }
 
 // g = (g0, 0, ..., 0), n entries, and flags[0..nflags) = 0
-__global__ void k_init_g(double* __restrict__ g, int n, double g0, int* __restrict__ flags, int nflags) {
+__global__ void k_init_g(double* __restrict__ g, int n, double g0, int* __restrict__ flags, int nflags,
+                         double* __restrict__ one) {
+    if (one && threadIdx.x == 0) *one = 1.0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) g[i] = i == 0 ? g0 : 0.0;
     for (int i = threadIdx.x; i < nflags; i += blockDim.x) flags[i] = 0;
 }
@@ -375,15 +401,19 @@ unsigned krylov_nblk(size_t n) { return grid_for(n, RTE_KRYLOV_NBLK); }
 
 template <typename TV>
 void krylov_dots(const TV* V, size_t ld, int nvec, const TV* w, size_t n, double* partial,
-                 double* out, bool with_norm, hipStream_t st, const int* active) {
+                 double* out, bool with_norm, hipStream_t st, const int* active, const ArnoldiArgs* stage1,
+                 const double* upd, int nupd) {
+    const ArnoldiArgs none;
     const unsigned nblk = grid_for(n, RTE_KRYLOV_NBLK);
     const bool pairs = n % 2 == 0 && ld % 2 == 0 && ((uintptr_t)V % 16) == 0 && ((uintptr_t)w % 16) == 0;
     // groups of up to VB basis vectors; the first group also sums w^2 (into row nvec of partial)
     for (int v0 = 0; v0 < nvec || (v0 == 0 && with_norm); v0 += VB) {
         const int nv = std::min(VB, nvec - v0);
         double* np = (with_norm && v0 == 0) ? partial + (size_t)nvec * nblk : nullptr;
-        if (pairs) launch_dots<true>(nv, nblk, st, V + (size_t)v0 * ld, ld, w, n, partial + (size_t)v0 * nblk, np, active);
-        else launch_dots<false>(nv, nblk, st, V + (size_t)v0 * ld, ld, w, n, partial + (size_t)v0 * nblk, np, active);
+        const bool s1 = stage1 && v0 == 0;
+        auto launch = pairs ? launch_dots<true, TV> : launch_dots<false, TV>;
+        launch(nv, nblk, st, V + (size_t)v0 * ld, ld, w, n, partial + (size_t)v0 * nblk, np, active, s1 ? *stage1 : none,
+               s1 ? upd : nullptr, nupd);
     }
     const int nout = nvec + (with_norm ? 1 : 0);
     if (out && nout > 0)
@@ -416,14 +446,18 @@ void back_solve_dev(const double* H, int ld, const double* g, int k, double* y, 
     hipLaunchKernelGGL(k_back_solve, dim3(1), dim3(256), lds, st, H, ld, g, k, y, flags);
 }
 
-void init_g(double* g, int n, double g0, int* flags, int nflags, hipStream_t st) {
-    hipLaunchKernelGGL(k_init_g, dim3(1), dim3(256), 0, st, g, n, g0, flags, nflags);
+void init_g(double* g, int n, double g0, int* flags, int nflags, hipStream_t st, double* one) {
+    hipLaunchKernelGGL(k_init_g, dim3(1), dim3(256), 0, st, g, n, g0, flags, nflags, one);
 }
 
 template <typename TV>
 void rescale_arn1(const ArnoldiArgs& t, TV* w, size_t n, const double* partial, int nblk, hipStream_t st) {
     // usually nothing to rescale, so a small grid
     hipLaunchKernelGGL(k_rescale_arn1<TV>, dim3(grid_for(n, 512)), dim3(KT), 0, st, t, w, n, partial, nblk);
+}
+
+void arn1_run(const ArnoldiArgs& t, const double* upd, int nupd, hipStream_t st) {
+    hipLaunchKernelGGL(k_arn1, dim3(1), dim3(KT), 0, st, t, upd, nupd);
 }
 
 void reduce_partials(const double* partial, int nblk, double* out, int nout, hipStream_t st) {
@@ -436,8 +470,8 @@ void arnoldi_run(const ArnoldiArgs& t, hipStream_t s) {
 
 template <typename TV>
 void krylov_combine(double* x, const TV* Z, size_t ld, int nvec, const double* y, size_t n, hipStream_t st,
-                    const int* skip) {
-    hipLaunchKernelGGL(k_combine<TV>, dim3(grid_for(n, 4096)), dim3(KT), 0, st, x, Z, ld, nvec, y, n, skip);
+                    const int* skip, const double* f) {
+    hipLaunchKernelGGL(k_combine<TV>, dim3(grid_for(n, 4096)), dim3(KT), 0, st, x, Z, ld, nvec, y, n, skip, f);
 }
 
 template <typename TD>
@@ -475,13 +509,13 @@ void nonfinite_scan(const double* x, size_t n, int* flag, hipStream_t st) {
 
 #define RTE_KRYLOV_INST(TV)                                                                                     \
     template void krylov_dots<TV>(const TV*, size_t, int, const TV*, size_t, double*, double*, bool, hipStream_t, \
-                                  const int*);                                                                  \
+                                  const int*, const ArnoldiArgs*, const double*, int);                          \
     template void krylov_update<TV>(TV*, const TV*, size_t, int, const double*, size_t, double*, double*,       \
                                     hipStream_t, const int*, const ArnoldiArgs*);                               \
     template void vec_scale_dev<TV>(TV*, const TV*, const double*, size_t, hipStream_t);                        \
     template void rescale_arn1<TV>(const ArnoldiArgs&, TV*, size_t, const double*, int, hipStream_t);          \
     template void krylov_combine<TV>(double*, const TV*, size_t, int, const double*, size_t, hipStream_t,      \
-                                     const int*);                                                              \
+                                     const int*, const double*);                                               \
     template void vec_scale<TV>(TV*, const double*, double, size_t, hipStream_t);
 RTE_KRYLOV_INST(double)
 RTE_KRYLOV_INST(float)

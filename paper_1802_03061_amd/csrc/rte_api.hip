@@ -81,6 +81,7 @@ static void free_krylov(rte_ctx* c) {
     dfree(c->V);
     dfree(c->Z);
     dfree(c->partial);
+    dfree(c->partial_u);
     dfree(c->dsmall);
     dfree(c->arn);
     dfree(c->arn_flags);
@@ -135,6 +136,7 @@ int ensure_krylov(rte_ctx* c, int m, bool need_z, size_t vbytes, size_t nlen) {
     if ((rc = dalloc(&c->V, (size_t)(m + 1) * n * vbytes))) return rc;
     if (need_z && (rc = dalloc(&c->Z, (size_t)m * n))) return rc;
     if ((rc = dalloc(&c->partial, (size_t)(m + 3) * RTE_KRYLOV_NBLK))) return rc;
+    if ((rc = dalloc(&c->partial_u, n / c->nx))) return rc;
     if ((rc = dalloc(&c->dsmall, (size_t)(2 * m + 16)))) return rc;
     // device Arnoldi state: H [(m+1) x m] | cs [m] | sn [m] | g [m+1] | est [m] | inv [m+1]
     if ((rc = dalloc(&c->arn, (size_t)(m + 1) * m + 4 * (size_t)m + 2))) return rc;
@@ -231,32 +233,48 @@ Apply2DArgs<double> args2d<double>(const rte_ctx* c) {
     return a;
 }
 
-template <typename T, typename TV>
-static int apply_t(rte_ctx* c, int mode, const TV* x, const double* b, TV* y, int nbatch, hipEvent_t* ev) {
-    const ChanScale sc = channel_scale(c, mode);
+// The arguments of the x-passes on nbatch channel vectors: nchan "channels" of them with factors sc.
+// In 3D every z-slab of every channel of every batch entry counts as one channel of a 2D apply; the
+// factor of D is applied per channel when pass B loads it.
+template <typename T>
+static Apply2DArgs<T> x_pass_args(const rte_ctx* c, int mode, int nbatch, ChanScale& sc, int& nb) {
+    Apply2DArgs<T> a = args2d<T>(c);
     if (c->dim == 2) {
-        Apply2DArgs<T> a = args2d<T>(c);
         a.pack = pack_for(a);
-        if (ev) (void)hipEventRecord(ev[0], c->stream);
-        if (apply2d_pass_a<T>(a, x, sc, nbatch)) return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
-        if (ev) (void)hipEventRecord(ev[1], c->stream);
+        sc = channel_scale(c, mode);
+        nb = nbatch;
+        return a;
+    }
+    const int* v3 = sizeof(T) == 4 ? c->var3f : c->var3d;
+    a.C = 1;
+    a.L = 0;
+    a.pack = 0;
+    a.var[0] = v3[0];
+    a.var[1] = 0;
+    a.var[2] = v3[4];
+    for (int i = 0; i < 2 * RTE_MAX_L + 1; ++i) sc.s[i] = 1.0;
+    nb = nbatch * c->C * c->nz;
+    return a;
+}
+
+// have_a: pass A's output is in the work buffer (x is not read then in mode APPLY_K).
+template <typename T, typename TV>
+static int apply_t(rte_ctx* c, int mode, const TV* x, const double* b, TV* y, int nbatch, hipEvent_t* ev,
+                   bool have_a = false) {
+    ChanScale sc;
+    int nx_b;
+    const Apply2DArgs<T> a = x_pass_args<T>(c, mode, nbatch, sc, nx_b);
+    const int cmode = mode == APPLY_K ? APPLY_KT : mode;
+    if (ev) (void)hipEventRecord(ev[0], c->stream);
+    if (!have_a && apply2d_pass_a<T>(a, x, sc, nx_b)) return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
+    if (ev) (void)hipEventRecord(ev[1], c->stream);
+    if (c->dim == 2) {
         if (apply2d_pass_b<T>(a, nbatch)) return set_error(RTE_EUNSUPPORTED, "pass B: unsupported size");
         if (ev) (void)hipEventRecord(ev[2], c->stream);
-        if (apply2d_pass_c<T>(a, x, b, y, mode, nbatch)) return set_error(RTE_EUNSUPPORTED, "pass C: unsupported size");
+        if (apply2d_pass_c<T>(a, x, b, y, cmode, nx_b)) return set_error(RTE_EUNSUPPORTED, "pass C: unsupported size");
         if (ev) (void)hipEventRecord(ev[3], c->stream);
     } else {
-        // x-passes treat every z-slab of every channel of every batch entry as one channel of a 2D
-        // apply; the factor of D is applied per channel when pass B loads it
-        Apply2DArgs<T> a = args2d<T>(c);
-        a.C = 1;
-        a.L = 0;
-        a.pack = 0;
         const int* v3 = sizeof(T) == 4 ? c->var3f : c->var3d;
-        a.var[0] = v3[0];
-        a.var[1] = 0;
-        a.var[2] = v3[4];
-        ChanScale ones;
-        for (int i = 0; i < 2 * RTE_MAX_L + 1; ++i) ones.s[i] = 1.0;
         Apply3DArgs<T> a3;
         a3.nx = c->nx; a3.ny = c->ny; a3.nz = c->nz; a3.PX = c->PX; a3.PY = c->PY; a3.PZ = c->PZ;
         a3.C = c->C;
@@ -270,10 +288,6 @@ static int apply_t(rte_ctx* c, int mode, const TV* x, const double* b, TV* y, in
         } else {
             a3.T1 = c->wd; a3.T2 = c->wd2; a3.Q3 = c->Q3d; a3.twy = c->twd[1]; a3.twz = c->twd[2];
         }
-        const int slabs = nbatch * c->C * c->nz;
-        if (ev) (void)hipEventRecord(ev[0], c->stream);
-        if (apply2d_pass_a<T>(a, x, ones, slabs)) return set_error(RTE_EUNSUPPORTED, "3D pass A: unsupported size");
-        if (ev) (void)hipEventRecord(ev[1], c->stream);
         cx<T>* T1base = a3.T1;
         for (int bi = 0; bi < nbatch; ++bi) {
             a3.T1 = T1base + (size_t)bi * t1sz;
@@ -284,7 +298,7 @@ static int apply_t(rte_ctx* c, int mode, const TV* x, const double* b, TV* y, in
             if (apply3d_pass<T>(a3, 3)) return set_error(RTE_EUNSUPPORTED, "3D pass D: unsupported size");
         }
         if (ev) (void)hipEventRecord(ev[4], c->stream);
-        if (apply2d_pass_c<T>(a, x, b, y, mode, slabs)) return set_error(RTE_EUNSUPPORTED, "3D pass E: unsupported size");
+        if (apply2d_pass_c<T>(a, x, b, y, cmode, nx_b)) return set_error(RTE_EUNSUPPORTED, "3D pass E: unsupported size");
         if (ev) (void)hipEventRecord(ev[5], c->stream);
     }
     hipError_t e = hipGetLastError();
@@ -304,6 +318,31 @@ static int apply_basis(rte_ctx* c, const TV* x, TV* y, int nb = 1) {
     if constexpr (sizeof(TV) == sizeof(float)) return apply_t<float>(c, APPLY_A, x, nullptr, y, nb, nullptr);
     else return c->prec == RTE_PREC_FP32 ? apply_t<float>(c, APPLY_A, x, nullptr, y, nb, nullptr)
                                          : apply_t<double>(c, APPLY_A, x, nullptr, y, nb, nullptr);
+}
+
+// The plain solver's step (k_update_a): y = K x, pass A done before when have_a, ...
+template <typename TV>
+static int apply_basis_k(rte_ctx* c, const TV* x, TV* y, int nb, bool have_a) {
+    if constexpr (sizeof(TV) == sizeof(float)) return apply_t<float>(c, APPLY_K, x, nullptr, y, nb, nullptr, have_a);
+    else return c->prec == RTE_PREC_FP32 ? apply_t<float>(c, APPLY_K, x, nullptr, y, nb, nullptr, have_a)
+                                         : apply_t<double>(c, APPLY_K, x, nullptr, y, nb, nullptr, have_a);
+}
+// ... and the update of w = K u_j with the next pass A.
+template <typename T, typename TV>
+static int update_a_t(rte_ctx* c, TV* w, const TV* V, size_t n, const ArnoldiArgs& t, int nb, int* nblk) {
+    ChanScale sc;
+    int nx_b;
+    const Apply2DArgs<T> a = x_pass_args<T>(c, APPLY_K, nb, sc, nx_b);
+    if (apply2d_update_a<T>(a, w, V, n, t, c->partial_u, sc, nx_b, nblk))
+        return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RTE_OK : set_hip_error(e, "update launch", __FILE__, __LINE__);
+}
+template <typename TV>
+static int update_a(rte_ctx* c, TV* w, const TV* V, size_t n, const ArnoldiArgs& t, int nb, int* nblk) {
+    if constexpr (sizeof(TV) == sizeof(float)) return update_a_t<float>(c, w, V, n, t, nb, nblk);
+    else return c->prec == RTE_PREC_FP32 ? update_a_t<float>(c, w, V, n, t, nb, nblk)
+                                         : update_a_t<double>(c, w, V, n, t, nb, nblk);
 }
 
 // y = A (v + s P Y) in the context precision, the coarse correction added inside passes A and C.
@@ -582,6 +621,8 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
                        (!use_pc || (size_t)pc_update_pool_blocks(c) <= (size_t)(m + 3) * RTE_KRYLOV_NBLK);
     const bool rescale_net = fused && use_pc && pc_rescale_net_ok(c);
     const bool early_a = rescale_net && early_a_ok(c);
+    // the plain form: Arnoldi on K with lazy factors, the update fused with the next pass A
+    const bool lazy = fused && !use_pc;
     // tolerance on |v_{j+1}|^2 - 1 beyond which the stored vector is rescaled; RTE_RENORM_TOL
     // overrides it (a negative value rescales at every step, which tests use)
     const char* renorm_env = std::getenv("RTE_RENORM_TOL");
@@ -608,7 +649,7 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
             pc_scale_pool(c, (const double*)rv, V, nullptr, 1.0 / rn, dg, m + 1, rn, dfl, 4);
         } else {
             vec_scale(V, rv, 1.0 / rn, n, st);
-            init_g(dg, m + 1, rn, dfl, 4, st);
+            init_g(dg, m + 1, rn, dfl, 4, st, dinv);
         }
         est = rn;
         const double cycle_start_rn = rn;
@@ -618,6 +659,8 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
         int launched = 0;
         bool net_ready = false;   // the network output of the next step is already being computed
         bool a_ready = false;     // and pass A of its apply (early_a)
+        ArnoldiArgs prev;         // lazy: the last column, whose stage 1 is still to run
+        int prev_nblk = 0;
         bool stop = false, bad = false;
         for (int j = 0; j < m && it + launched < max_iter && !stop; ++j) {
             TV* vj = V + (size_t)j * n;
@@ -636,7 +679,7 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
                 rc = a_ready ? apply_basis_pc_from_b(c, vj, w, pc_slot(c, j)) : apply_basis_pc(c, vj, w, pc_slot(c, j));
                 a_ready = false;
                 if (rc) return rc;
-            } else if ((rc = apply_basis(c, vj, w, nb))) {
+            } else if ((rc = lazy ? apply_basis_k(c, vj, w, nb, j > 0) : apply_basis(c, vj, w, nb))) {
                 return rc;
             }
             ++inf.applies;
@@ -657,7 +700,18 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
             at.est = dest;
             at.inv = dinv;
             at.flags = dfl;
-            if (fused) {
+            if (lazy) {
+                // stage 1 of the last column runs beside this column's dots
+                krylov_dots(V, n, j + 1, w, n, c->partial, sd, true, st, nullptr, j > 0 ? &prev : nullptr, c->partial_u,
+                            prev_nblk);
+                at.of_k = 1;
+                at.renorm_tol = -1.0;   // H[j+1, j] and inv[j+1] from the exact norm
+                if ((rc = update_a(c, w, V, n, at, nb, &prev_nblk))) return rc;
+                at.stage = 1;
+                at.est_out = c->hpipe_dev + j;
+                at.flags_out = c->hpipe_flags_dev + 2 * j;
+                prev = at;
+            } else if (fused) {
                 // one pass: the update computes the normalising factor from |w|^2 - |h|^2 and writes
                 // the normalised vector (and, when preconditioning, the network's pooled input),
                 // with stage 0 of the column in its block 0; the rescale kernel runs stage 1 in its
@@ -718,6 +772,8 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
                 if (e1 <= target) stop = true;                                  // column j is kept too
             }
         }
+        const double* fac = lazy ? dinv : nullptr;   // factors of the stored basis vectors
+        if (lazy && launched > 0) arn1_run(prev, c->partial_u, prev_nblk, st);
         // The cycle end (least squares, solution update, true residual and its norm) is enqueued
         // before the last iteration's flags are read, so the device has it queued when that
         // iteration ends.  The column count assumes that iteration is sound; if it produced a
@@ -735,7 +791,7 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
                 const int* guard = last_kept ? dfl : nullptr;
                 back_solve_dev(dH, m + 1, dg, jd_end, c->dsmall, st, guard);
                 if (pc_live) pc_combine(c, x, (const TV*)V, jd_end, c->dsmall, guard);
-                else krylov_combine(x, V, n, jd_end, c->dsmall, n, st, guard);
+                else krylov_combine(x, V, n, jd_end, c->dsmall, n, st, guard, fac);
             }
             if ((rc = apply_channels(c, APPLY_RESID, RTE_PREC_FP64, x, b, rv, nb))) return rc;
             ++inf.applies;
@@ -784,13 +840,13 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
                         double* xr = rec + (size_t)(k - 1) * n;
                         vec_fill(xr, 0.0, n, st);
                         if (pc_live) pc_combine(c, xr, (const TV*)V, k, c->dsmall);
-                        else krylov_combine(xr, V, n, k, c->dsmall, n, st);
+                        else krylov_combine(xr, V, n, k, c->dsmall, n, st, nullptr, fac);
                     }
                     if (nrec) *nrec = nr;
                 }
                 back_solve_dev(dH, m + 1, dg, jd, c->dsmall, st);
                 if (pc_live) pc_combine(c, x, (const TV*)V, jd, c->dsmall);
-                else krylov_combine(x, V, n, jd, c->dsmall, n, st);
+                else krylov_combine(x, V, n, jd, c->dsmall, n, st, nullptr, fac);
             }
             // true residual with the FP64 apply
             if ((rc = apply_channels(c, APPLY_RESID, RTE_PREC_FP64, x, b, rv, nb))) return rc;
