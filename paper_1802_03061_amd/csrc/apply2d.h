@@ -140,6 +140,10 @@ bool apply2d_b_halves(int L, int PY);
 template <typename T, typename TV>
 int apply2d_pass_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                    int nbatch);
+// Pass A (pass 0) or C (pass 2) of v = A u or K~ u on general complex mode vectors u, v
+// [2L+1][ny][nx] (complex double), as two batch entries of the work buffer (apply2d_modes.hip).
+template <typename T>
+int apply2d_modes_pass(const Apply2DArgs<T>& a, int pass, const void* u, void* v, int mode, const ChanScale& sc);
 // Passes B and C of y = A (x + cs P y) for one batch entry, pass A having already written the
 // x-spectrum of the scaled x alone into a.work; a.bcorr and a.corr describe the correction.
 template <typename T, typename TV>

@@ -1,0 +1,243 @@
+// Passes A and C of the 2D apply on general complex mode vectors u[2L+1][ny][nx] (mode k at row k + L).
+//
+// Such a vector is two real fields p + i q, whose channels the apply handles as two batch entries
+// (channels as in apply2d.hip).  Channel by channel the two are the real and imaginary part of
+//     z_0 = u_0,   z_{2k-1} = (u_k + u_-k)/sqrt2,   z_{2k} = -i (u_k - u_-k)/sqrt2,
+// so one complex x-transform of a row of z_c carries that row of both entries (where the channel form
+// puts two rows of one real channel into it), and the same unpacking gives their spectra.  Inverse:
+// u_{+-k} = (z_{2k-1} +- i z_{2k})/sqrt2.  The modes are read and written once, in the passes themselves;
+// separate conversions to channels and back were two launches and 4 (2L+1) real vectors of traffic.
+//
+// A block takes R rows of one mode pair (k, -k), 2R transforms (k = 0: R).  Bound: latency at small
+// grids, HBM at large ones.  Applies with conversions and without, us: FP32 200x150, L = 2 32.7 and 24.0;
+// 16^2, L = 7 25.6 and 12.8; 512^2, L = 2 63.8 and 49.3; FP64 512^2, L = 0 40.8 and 29.3.
+#include "apply2d.h"
+#include "apply2d_tile.h"
+#include "fft.h"
+
+namespace rte {
+
+constexpr double kHalfSqrt2 = 0.70710678118654752440084436210485;
+
+template <typename T, int PX, int R, int NTHR>
+__global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restrict__ u, cx<T>* __restrict__ Tb,
+                                                       const cx<T>* __restrict__ tw, int nx, int ny, int L,
+                                                       ChanScale sc, int pack) {
+    constexpr int LD = padded(PX) + 1, H = PX / 2;
+    constexpr int R0 = fft_radix(PX, 1), NB0 = PX / R0, NBT = R * NB0, IT = (NBT + NTHR - 1) / NTHR;
+    __shared__ cx<T> buf[2 * R * LD];
+    __shared__ cx<T> tws[PX];
+    const int tid = threadIdx.x, k = blockIdx.y;
+    const int y0 = xcd_tile(blockIdx.x, gridDim.x) * R;
+    const size_t N = (size_t)nx * ny;
+    const cx<double>* up = u + (size_t)(L + k) * N;
+    const cx<double>* um = u + (size_t)(L - k) * N;
+    stage_twiddles<T, PX, NTHR>(tws, tw, tid);
+    cx<double> p[IT][R0 / 2], m[IT][R0 / 2];   // every load before the first use, clamped instead of guarded
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int idx = tid + it * NTHR, row = idx / NB0, j = idx % NB0, y = y0 + row;
+#pragma unroll
+        for (int r = 0; r < R0 / 2; ++r) {
+            const int x = j + r * NB0;
+            const size_t o = ((NBT % NTHR == 0 || idx < NBT) && x < nx && y < ny) ? (size_t)y * nx + x : 0;
+            p[it][r] = up[o];
+            m[it][r] = um[o];
+        }
+    }
+    const double s = sc.s[k ? 2 * k : 0] * (k ? kHalfSqrt2 : 1.0);
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int idx = tid + it * NTHR, row = idx / NB0, j = idx % NB0, y = y0 + row;
+        if (NBT % NTHR == 0 || idx < NBT) {
+            cx<T> a[R0], b[R0];
+#pragma unroll
+            for (int r = 0; r < R0; ++r) {
+                const bool ok = r < R0 / 2 && j + r * NB0 < nx && y < ny;
+                const cx<double> vp = p[it][r < R0 / 2 ? r : 0], vm = m[it][r < R0 / 2 ? r : 0];
+                const cx<double> za = k ? vp + vm : vp, zb = mul_mi(vp - vm);
+                a[r] = ok ? mk((T)(s * za.re), (T)(s * za.im)) : mk((T)0, (T)0);
+                b[r] = ok ? mk((T)(s * zb.re), (T)(s * zb.im)) : mk((T)0, (T)0);
+            }
+            dft_small<T, R0, false>(a);
+            dft_small<T, R0, false>(b);
+#pragma unroll
+            for (int r = 0; r < R0; ++r) {
+                buf[row * LD + sw(j * R0 + r)] = a[r];
+                buf[(R + row) * LD + sw(j * R0 + r)] = b[r];
+            }
+        }
+    }
+    __syncthreads();
+    if (k) fft_stages_range<T, PX, 2 * R, LD, NTHR, false, R0, PX>(buf, tws, tid);
+    else fft_stages_range<T, PX, R, LD, NTHR, false, R0, PX>(buf, tws, tid);
+    // spectra of the real parts (batch entry 0) and the imaginary parts (entry 1) of each channel
+    const int NKS = pack ? H : H + 1, C = 2 * L + 1;
+    const size_t chan = (size_t)NKS * ny, entry = C * chan;
+    const int nf = NKS * R;
+    for (int idx = tid; idx < (k ? 2 * nf : nf); idx += NTHR) {
+        const int row = idx % R, half = idx >= nf ? 1 : 0, kx = (idx - half * nf) / R, y = y0 + row;
+        if (y >= ny) continue;
+        const cx<T>* b = buf + (half * R + row) * LD;
+        cx<T> P, Q;
+        if (pack && kx == 0) {   // (X[0], X[PX/2])
+            const cx<T> z0 = b[sw(0)], zh = b[sw(H)];
+            P = mk(z0.re, zh.re);
+            Q = mk(z0.im, zh.im);
+        } else {
+            const cx<T> z = b[sw(kx)], zc = conj(b[sw((PX - kx) & (PX - 1))]);
+            P = scale(z + zc, (T)0.5);
+            Q = scale(mul_mi(z - zc), (T)0.5);
+        }
+        cx<T>* out = Tb + (size_t)(k ? 2 * k - 1 + half : 0) * chan + (size_t)kx * ny + y;
+        out[0] = P;
+        out[entry] = Q;
+    }
+}
+
+template <typename T, int PX, int R, int NTHR>
+__global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__ Tb, const cx<double>* __restrict__ u,
+                                                       cx<double>* __restrict__ v, const cx<T>* __restrict__ tw, int nx,
+                                                       int ny, int L, int mode, int pack) {
+    constexpr int LD = padded(PX) + 1, H = PX / 2;
+    __shared__ cx<T> buf[2 * R * LD];
+    __shared__ cx<T> tws[PX];
+    const int tid = threadIdx.x, k = blockIdx.y;
+    const int y0 = xcd_tile(blockIdx.x, gridDim.x) * R;
+    const int NKS = pack ? H : H + 1, C = 2 * L + 1;
+    const size_t N = (size_t)nx * ny, chan = (size_t)NKS * ny, entry = C * chan;
+    const cx<T>* src = Tb + (size_t)(k ? 2 * k - 1 : 0) * chan;
+    stage_twiddles<T, PX, NTHR>(tws, tw, tid);
+    constexpr int U = 4;   // spectrum entries per thread at a time, loads first
+    const int nf = NKS * R, nl = k ? 2 * nf : nf;
+    for (int i0 = tid; i0 < nl; i0 += U * NTHR) {
+        cx<T> xa[U], xb[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int idx = i0 + q * NTHR, row = idx % R, half = idx >= nf ? 1 : 0, kx = (idx - half * nf) / R;
+            const size_t o = idx < nl && y0 + row < ny ? half * chan + (size_t)kx * ny + y0 + row : 0;
+            xa[q] = src[o];
+            xb[q] = src[o + entry];
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int idx = i0 + q * NTHR, row = idx % R, half = idx >= nf ? 1 : 0, kx = (idx - half * nf) / R;
+            if (idx >= nl) continue;
+            const bool in = y0 + row < ny;
+            cx<T> P = in ? xa[q] : mk((T)0, (T)0), Q = in ? xb[q] : mk((T)0, (T)0);
+            cx<T>* b = buf + (half * R + row) * LD;
+            if (pack && kx == 0) {
+                b[sw(0)] = mk(P.re, Q.re);
+                b[sw(H)] = mk(P.im, Q.im);
+            } else {
+                if (kx == 0 || kx == H) { P.im = 0; Q.im = 0; }
+                b[sw(kx)] = P + mul_i(Q);
+                if (kx > 0 && kx < H) b[sw(PX - kx)] = conj(P) + mul_i(conj(Q));
+            }
+        }
+    }
+    __syncthreads();
+    // the last stage in registers, both channels of a mode pair by one thread (see pass_c_tile)
+    constexpr int NSL = fft_last_ns(PX), RL = PX / NSL, TWL = stage_tw_offset(PX, NSL);
+    if (k) fft_stages_range<T, PX, 2 * R, LD, NTHR, true, 1, NSL>(buf, tws, tid);
+    else fft_stages_range<T, PX, R, LD, NTHR, true, 1, NSL>(buf, tws, tid);
+    const cx<double>* up = u + (size_t)(L + k) * N;
+    const cx<double>* um = u + (size_t)(L - k) * N;
+    cx<double>* vp = v + (size_t)(L + k) * N;
+    cx<double>* vm = v + (size_t)(L - k) * N;
+    for (int idx = tid; idx < R * NSL; idx += NTHR) {
+        const int row = idx / NSL, j = idx % NSL, y = y0 + row;
+        cx<double> p[RL / 2], m[RL / 2];
+        if (mode == APPLY_A) {
+#pragma unroll
+            for (int r = 0; r < RL / 2; ++r) {
+                const size_t o = (j + r * NSL < nx && y < ny) ? (size_t)y * nx + j + r * NSL : 0;
+                p[r] = up[o];
+                m[r] = um[o];
+            }
+        }
+        cx<T> a[RL], b[RL];
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+            a[r] = buf[row * LD + sw(j + r * NSL)];
+            b[r] = k ? buf[(R + row) * LD + sw(j + r * NSL)] : mk((T)0, (T)0);
+        }
+        if constexpr (NSL > 1) {
+#pragma unroll
+            for (int r = 1; r < RL; ++r) {
+                cx<T> w = tws[TWL + j * (RL - 1) + (r - 1)];
+                w.im = -w.im;
+                a[r] = a[r] * w;
+                b[r] = b[r] * w;
+            }
+        }
+        dft_small<T, RL, true>(a);
+        if (k) dft_small<T, RL, true>(b);
+        if (y >= ny) continue;
+#pragma unroll
+        for (int r = 0; r < RL / 2; ++r) {
+            const int x = j + r * NSL;
+            if (x >= nx) continue;
+            const size_t o = (size_t)y * nx + x;
+            const cx<double> za = cvt<double>(a[r]), zb = mul_i(cvt<double>(b[r]));
+            const cx<double> yp = k ? scale(za + zb, kHalfSqrt2) : za;
+            vp[o] = mode == APPLY_A ? p[r] - yp : yp;
+            if (k) {
+                const cx<double> ym = scale(za - zb, kHalfSqrt2);
+                vm[o] = mode == APPLY_A ? m[r] - ym : ym;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------- dispatch -------
+// Rows per block: 2R transforms in at most 70 KB (two blocks per CU), at most 8 rows (64 bytes of a
+// spectrum column in FP32), and half of that where the grid would not give every CU a block.  Whole
+// applies in FP32 with R and R/2 rows: 200x150, L = 2 (57 blocks of R) 30.1 and 24.0 us; 512^2, L = 0 (128)
+// 23.2 and 20.6; 256^2, L = 4 (160) 34.2 and 29.5; 300x257, L = 3 (260) 58.2 and 65.3; 400x300, L = 8
+// (675) 131 and 161.
+template <typename T, int PX>
+constexpr int mode_rows() {
+    int r = 8;
+    while (r > 1 && 2L * r * (padded(PX) + 1) * (long)sizeof(cx<T>) > 70 * 1024) r /= 2;
+    return r;
+}
+template <typename T, int PX, int R>
+static void launch_modes_r(const Apply2DArgs<T>& a, int pass, const cx<double>* u, cx<double>* v, int mode,
+                           const ChanScale& sc) {
+    dim3 grid((a.ny + R - 1) / R, a.L + 1);
+    if (pass == 0)
+        hipLaunchKernelGGL((k_pass_a_modes<T, PX, R, 256>), grid, dim3(256), 0, a.stream, u, a.work, a.twx, a.nx, a.ny,
+                           a.L, sc, a.pack);
+    else
+        hipLaunchKernelGGL((k_pass_c_modes<T, PX, R, 256>), grid, dim3(256), 0, a.stream, a.work, u, v, a.twx, a.nx,
+                           a.ny, a.L, mode, a.pack);
+}
+template <typename T, int PX>
+static int launch_modes(const Apply2DArgs<T>& a, int pass, const cx<double>* u, cx<double>* v, int mode,
+                        const ChanScale& sc) {
+    constexpr int R = mode_rows<T, PX>();
+    const bool few = (long)((a.ny + R - 1) / R) * (a.L + 1) < 256;
+    if (R > 1 && few) launch_modes_r<T, PX, (R > 1 ? R / 2 : 1)>(a, pass, u, v, mode, sc);
+    else launch_modes_r<T, PX, R>(a, pass, u, v, mode, sc);
+    return 0;
+}
+template <typename T>
+int apply2d_modes_pass(const Apply2DArgs<T>& a, int pass, const void* u, void* v, int mode, const ChanScale& sc) {
+    const auto* x = (const cx<double>*)u;
+    auto* y = (cx<double>*)v;
+    switch (a.PX) {
+        case 16: return launch_modes<T, 16>(a, pass, x, y, mode, sc);
+        case 32: return launch_modes<T, 32>(a, pass, x, y, mode, sc);
+        case 64: return launch_modes<T, 64>(a, pass, x, y, mode, sc);
+        case 128: return launch_modes<T, 128>(a, pass, x, y, mode, sc);
+        case 256: return launch_modes<T, 256>(a, pass, x, y, mode, sc);
+        case 512: return launch_modes<T, 512>(a, pass, x, y, mode, sc);
+        case 1024: return launch_modes<T, 1024>(a, pass, x, y, mode, sc);
+    }
+    return -1;
+}
+template int apply2d_modes_pass<float>(const Apply2DArgs<float>&, int, const void*, void*, int, const ChanScale&);
+template int apply2d_modes_pass<double>(const Apply2DArgs<double>&, int, const void*, void*, int, const ChanScale&);
+
+}  // namespace rte

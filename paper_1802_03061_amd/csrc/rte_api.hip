@@ -1226,6 +1226,19 @@ static void to_modes(const rte_ctx* c, const double* ch, void* y, bool one_part)
     else channels_to_modes(ch, y, c->L, c->ncell, one_part, c->stream);
 }
 
+// The 2D apply on complex modes, the conversions from and to channels inside passes A and C.
+template <typename T>
+static int apply_modes(rte_ctx* c, int mode, const void* x, void* y) {
+    ChanScale sc;
+    int nb;
+    const Apply2DArgs<T> a = x_pass_args<T>(c, mode, 2, sc, nb);
+    if (apply2d_modes_pass<T>(a, 0, x, nullptr, mode, sc)) return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
+    if (apply2d_pass_b<T>(a, 2)) return set_error(RTE_EUNSUPPORTED, "pass B: unsupported size");
+    if (apply2d_modes_pass<T>(a, 2, x, y, mode, sc)) return set_error(RTE_EUNSUPPORTED, "pass C: unsupported size");
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? RTE_OK : set_hip_error(e, "rte_apply", __FILE__, __LINE__);
+}
+
 extern "C" {
 
 int rte_apply(rte_ctx* c, int op, int layout, int prec, const void* x, void* y) {
@@ -1238,6 +1251,7 @@ int rte_apply(rte_ctx* c, int op, int layout, int prec, const void* x, void* y) 
     if (x == y) return set_error(RTE_EINVAL, "x and y may not alias");
     const int mode = op == RTE_OP_A ? APPLY_A : APPLY_KT;
     if (layout == RTE_LAYOUT_CHANNELS) return apply_channels(c, mode, prec, (const double*)x, nullptr, (double*)y, 1);
+    if (c->dim == 2) return prec == RTE_PREC_FP32 ? apply_modes<float>(c, mode, x, y) : apply_modes<double>(c, mode, x, y);
     to_channels(c, x, c->t0, false);
     int rc = apply_channels(c, mode, prec, c->t0, nullptr, c->t1, 2);
     if (rc) return rc;
