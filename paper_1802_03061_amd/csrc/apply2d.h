@@ -141,9 +141,11 @@ template <typename T, typename TV>
 int apply2d_pass_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                    int nbatch);
 // Pass A (pass 0) or C (pass 2) of v = A u or K~ u on general complex mode vectors u, v
-// [2L+1][ny][nx] (complex double), as two batch entries of the work buffer (apply2d_modes.hip).
+// [2L+1][ny][nx] (complex double), as two batch entries of the work buffer (apply2d_modes.hip).  singles > 0:
+// on so many [ny][nx] slabs instead, each a channel of its own (3D).
 template <typename T>
-int apply2d_modes_pass(const Apply2DArgs<T>& a, int pass, const void* u, void* v, int mode, const ChanScale& sc);
+int apply2d_modes_pass(const Apply2DArgs<T>& a, int pass, const void* u, void* v, int mode, const ChanScale& sc,
+                       int singles);
 // Passes B and C of y = A (x + cs P y) for one batch entry, pass A having already written the
 // x-spectrum of the scaled x alone into a.work; a.bcorr and a.corr describe the correction.
 template <typename T, typename TV>

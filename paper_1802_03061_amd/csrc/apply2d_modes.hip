@@ -1,4 +1,5 @@
-// Passes A and C of the 2D apply on general complex mode vectors u[2L+1][ny][nx] (mode k at row k + L).
+// The x-passes (2D: A and C, 3D: the first and the last) on general complex mode vectors, in 2D
+// u[2L+1][ny][nx] (mode k at row k + L).
 //
 // Such a vector is two real fields p + i q, whose channels the apply handles as two batch entries
 // (channels as in apply2d.hip).  Channel by channel the two are the real and imaginary part of
@@ -8,9 +9,11 @@
 // u_{+-k} = (z_{2k-1} +- i z_{2k})/sqrt2.  The modes are read and written once, in the passes themselves;
 // separate conversions to channels and back were two launches and 4 (2L+1) real vectors of traffic.
 //
-// A block takes R rows of one mode pair (k, -k), 2R transforms (k = 0: R).  Bound: latency at small
+// A block takes R rows of one mode pair (k, -k), 2R transforms (k = 0: R); without PAIR (3D, where every
+// mode is a channel) R rows of one slab.  Bound: latency at small
 // grids, HBM at large ones.  Applies with conversions and without, us: FP32 200x150, L = 2 32.7 and 24.0;
-// 16^2, L = 7 25.6 and 12.8; 512^2, L = 2 63.8 and 49.3; FP64 512^2, L = 0 40.8 and 29.3.
+// 16^2, L = 7 25.6 and 12.8; 512^2, L = 2 63.8 and 49.3; FP64 512^2, L = 0 40.8 and 29.3;
+// 3D FP32 isotropic 32^3 33.7 and 24.9, 128^3 155 and 116, 64^3 to degree 2 177 and 155.
 #include "apply2d.h"
 #include "apply2d_tile.h"
 #include "fft.h"
@@ -19,19 +22,19 @@ namespace rte {
 
 constexpr double kHalfSqrt2 = 0.70710678118654752440084436210485;
 
-template <typename T, int PX, int R, int NTHR>
+template <typename T, int PX, int R, int NTHR, bool PAIR>
 __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restrict__ u, cx<T>* __restrict__ Tb,
                                                        const cx<T>* __restrict__ tw, int nx, int ny, int L,
                                                        ChanScale sc, int pack) {
     constexpr int LD = padded(PX) + 1, H = PX / 2;
     constexpr int R0 = fft_radix(PX, 1), NB0 = PX / R0, NBT = R * NB0, IT = (NBT + NTHR - 1) / NTHR;
-    __shared__ cx<T> buf[2 * R * LD];
+    __shared__ cx<T> buf[(PAIR ? 2 : 1) * R * LD];
     __shared__ cx<T> tws[PX];
-    const int tid = threadIdx.x, k = blockIdx.y;
+    const int tid = threadIdx.x, k = PAIR ? blockIdx.y : 0;
     const int y0 = xcd_tile(blockIdx.x, gridDim.x) * R;
     const size_t N = (size_t)nx * ny;
-    const cx<double>* up = u + (size_t)(L + k) * N;
-    const cx<double>* um = u + (size_t)(L - k) * N;
+    const cx<double>* up = u + (size_t)(PAIR ? L + k : blockIdx.y) * N;
+    const cx<double>* um = u + (size_t)(PAIR ? L - k : blockIdx.y) * N;
     stage_twiddles<T, PX, NTHR>(tws, tw, tid);
     cx<double> p[IT][R0 / 2], m[IT][R0 / 2];   // every load before the first use, clamped instead of guarded
 #pragma unroll
@@ -42,7 +45,7 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
             const int x = j + r * NB0;
             const size_t o = ((NBT % NTHR == 0 || idx < NBT) && x < nx && y < ny) ? (size_t)y * nx + x : 0;
             p[it][r] = up[o];
-            m[it][r] = um[o];
+            m[it][r] = PAIR ? um[o] : p[it][r];
         }
     }
     const double s = sc.s[k ? 2 * k : 0] * (k ? kHalfSqrt2 : 1.0);
@@ -60,19 +63,19 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
                 b[r] = ok ? mk((T)(s * zb.re), (T)(s * zb.im)) : mk((T)0, (T)0);
             }
             dft_small<T, R0, false>(a);
-            dft_small<T, R0, false>(b);
+            if (PAIR) dft_small<T, R0, false>(b);
 #pragma unroll
             for (int r = 0; r < R0; ++r) {
                 buf[row * LD + sw(j * R0 + r)] = a[r];
-                buf[(R + row) * LD + sw(j * R0 + r)] = b[r];
+                if (PAIR) buf[(R + row) * LD + sw(j * R0 + r)] = b[r];
             }
         }
     }
     __syncthreads();
-    if (k) fft_stages_range<T, PX, 2 * R, LD, NTHR, false, R0, PX>(buf, tws, tid);
+    if (PAIR && k) fft_stages_range<T, PX, 2 * R, LD, NTHR, false, R0, PX>(buf, tws, tid);
     else fft_stages_range<T, PX, R, LD, NTHR, false, R0, PX>(buf, tws, tid);
     // spectra of the real parts (batch entry 0) and the imaginary parts (entry 1) of each channel
-    const int NKS = pack ? H : H + 1, C = 2 * L + 1;
+    const int NKS = pack ? H : H + 1, C = PAIR ? 2 * L + 1 : gridDim.y;
     const size_t chan = (size_t)NKS * ny, entry = C * chan;
     const int nf = NKS * R;
     for (int idx = tid; idx < (k ? 2 * nf : nf); idx += NTHR) {
@@ -89,24 +92,24 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
             P = scale(z + zc, (T)0.5);
             Q = scale(mul_mi(z - zc), (T)0.5);
         }
-        cx<T>* out = Tb + (size_t)(k ? 2 * k - 1 + half : 0) * chan + (size_t)kx * ny + y;
+        cx<T>* out = Tb + (size_t)(PAIR ? (k ? 2 * k - 1 + half : 0) : blockIdx.y) * chan + (size_t)kx * ny + y;
         out[0] = P;
         out[entry] = Q;
     }
 }
 
-template <typename T, int PX, int R, int NTHR>
+template <typename T, int PX, int R, int NTHR, bool PAIR>
 __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__ Tb, const cx<double>* __restrict__ u,
                                                        cx<double>* __restrict__ v, const cx<T>* __restrict__ tw, int nx,
                                                        int ny, int L, int mode, int pack) {
     constexpr int LD = padded(PX) + 1, H = PX / 2;
-    __shared__ cx<T> buf[2 * R * LD];
+    __shared__ cx<T> buf[(PAIR ? 2 : 1) * R * LD];
     __shared__ cx<T> tws[PX];
-    const int tid = threadIdx.x, k = blockIdx.y;
+    const int tid = threadIdx.x, k = PAIR ? blockIdx.y : 0;
     const int y0 = xcd_tile(blockIdx.x, gridDim.x) * R;
-    const int NKS = pack ? H : H + 1, C = 2 * L + 1;
+    const int NKS = pack ? H : H + 1, C = PAIR ? 2 * L + 1 : gridDim.y;
     const size_t N = (size_t)nx * ny, chan = (size_t)NKS * ny, entry = C * chan;
-    const cx<T>* src = Tb + (size_t)(k ? 2 * k - 1 : 0) * chan;
+    const cx<T>* src = Tb + (size_t)(PAIR ? (k ? 2 * k - 1 : 0) : blockIdx.y) * chan;
     stage_twiddles<T, PX, NTHR>(tws, tw, tid);
     constexpr int U = 4;   // spectrum entries per thread at a time, loads first
     const int nf = NKS * R, nl = k ? 2 * nf : nf;
@@ -139,12 +142,12 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
     __syncthreads();
     // the last stage in registers, both channels of a mode pair by one thread (see pass_c_tile)
     constexpr int NSL = fft_last_ns(PX), RL = PX / NSL, TWL = stage_tw_offset(PX, NSL);
-    if (k) fft_stages_range<T, PX, 2 * R, LD, NTHR, true, 1, NSL>(buf, tws, tid);
+    if (PAIR && k) fft_stages_range<T, PX, 2 * R, LD, NTHR, true, 1, NSL>(buf, tws, tid);
     else fft_stages_range<T, PX, R, LD, NTHR, true, 1, NSL>(buf, tws, tid);
-    const cx<double>* up = u + (size_t)(L + k) * N;
-    const cx<double>* um = u + (size_t)(L - k) * N;
-    cx<double>* vp = v + (size_t)(L + k) * N;
-    cx<double>* vm = v + (size_t)(L - k) * N;
+    const cx<double>* up = u + (size_t)(PAIR ? L + k : blockIdx.y) * N;
+    const cx<double>* um = u + (size_t)(PAIR ? L - k : blockIdx.y) * N;
+    cx<double>* vp = v + (size_t)(PAIR ? L + k : blockIdx.y) * N;
+    cx<double>* vm = v + (size_t)(PAIR ? L - k : blockIdx.y) * N;
     for (int idx = tid; idx < R * NSL; idx += NTHR) {
         const int row = idx / NSL, j = idx % NSL, y = y0 + row;
         cx<double> p[RL / 2], m[RL / 2];
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
             for (int r = 0; r < RL / 2; ++r) {
                 const size_t o = (j + r * NSL < nx && y < ny) ? (size_t)y * nx + j + r * NSL : 0;
                 p[r] = up[o];
-                m[r] = um[o];
+                m[r] = PAIR ? um[o] : p[r];
             }
         }
         cx<T> a[RL], b[RL];
@@ -202,42 +205,51 @@ constexpr int mode_rows() {
     while (r > 1 && 2L * r * (padded(PX) + 1) * (long)sizeof(cx<T>) > 70 * 1024) r /= 2;
     return r;
 }
-template <typename T, int PX, int R>
+template <typename T, int PX, int R, bool PAIR>
 static void launch_modes_r(const Apply2DArgs<T>& a, int pass, const cx<double>* u, cx<double>* v, int mode,
-                           const ChanScale& sc) {
-    dim3 grid((a.ny + R - 1) / R, a.L + 1);
+                           const ChanScale& sc, int ngroups) {
+    dim3 grid((a.ny + R - 1) / R, ngroups);
     if (pass == 0)
-        hipLaunchKernelGGL((k_pass_a_modes<T, PX, R, 256>), grid, dim3(256), 0, a.stream, u, a.work, a.twx, a.nx, a.ny,
+        hipLaunchKernelGGL((k_pass_a_modes<T, PX, R, 256, PAIR>), grid, dim3(256), 0, a.stream, u, a.work, a.twx, a.nx, a.ny,
                            a.L, sc, a.pack);
     else
-        hipLaunchKernelGGL((k_pass_c_modes<T, PX, R, 256>), grid, dim3(256), 0, a.stream, a.work, u, v, a.twx, a.nx,
+        hipLaunchKernelGGL((k_pass_c_modes<T, PX, R, 256, PAIR>), grid, dim3(256), 0, a.stream, a.work, u, v, a.twx, a.nx,
                            a.ny, a.L, mode, a.pack);
 }
 template <typename T, int PX>
 static int launch_modes(const Apply2DArgs<T>& a, int pass, const cx<double>* u, cx<double>* v, int mode,
-                        const ChanScale& sc) {
-    constexpr int R = mode_rows<T, PX>();
-    const bool few = (long)((a.ny + R - 1) / R) * (a.L + 1) < 256;
-    if (R > 1 && few) launch_modes_r<T, PX, (R > 1 ? R / 2 : 1)>(a, pass, u, v, mode, sc);
-    else launch_modes_r<T, PX, R>(a, pass, u, v, mode, sc);
+                        const ChanScale& sc, int singles) {
+    constexpr int R = mode_rows<T, PX>(), RH = R > 1 ? R / 2 : 1;
+    const int ngroups = singles ? singles : a.L + 1;
+    const bool few = (long)((a.ny + R - 1) / R) * ngroups < 256;
+    if (singles) {
+        if (few) launch_modes_r<T, PX, RH, false>(a, pass, u, v, mode, sc, ngroups);
+        else launch_modes_r<T, PX, R, false>(a, pass, u, v, mode, sc, ngroups);
+    } else {
+        if (few) launch_modes_r<T, PX, RH, true>(a, pass, u, v, mode, sc, ngroups);
+        else launch_modes_r<T, PX, R, true>(a, pass, u, v, mode, sc, ngroups);
+    }
     return 0;
 }
 template <typename T>
-int apply2d_modes_pass(const Apply2DArgs<T>& a, int pass, const void* u, void* v, int mode, const ChanScale& sc) {
+int apply2d_modes_pass(const Apply2DArgs<T>& a, int pass, const void* u, void* v, int mode, const ChanScale& sc,
+                       int singles) {
     const auto* x = (const cx<double>*)u;
     auto* y = (cx<double>*)v;
     switch (a.PX) {
-        case 16: return launch_modes<T, 16>(a, pass, x, y, mode, sc);
-        case 32: return launch_modes<T, 32>(a, pass, x, y, mode, sc);
-        case 64: return launch_modes<T, 64>(a, pass, x, y, mode, sc);
-        case 128: return launch_modes<T, 128>(a, pass, x, y, mode, sc);
-        case 256: return launch_modes<T, 256>(a, pass, x, y, mode, sc);
-        case 512: return launch_modes<T, 512>(a, pass, x, y, mode, sc);
-        case 1024: return launch_modes<T, 1024>(a, pass, x, y, mode, sc);
+        case 16: return launch_modes<T, 16>(a, pass, x, y, mode, sc, singles);
+        case 32: return launch_modes<T, 32>(a, pass, x, y, mode, sc, singles);
+        case 64: return launch_modes<T, 64>(a, pass, x, y, mode, sc, singles);
+        case 128: return launch_modes<T, 128>(a, pass, x, y, mode, sc, singles);
+        case 256: return launch_modes<T, 256>(a, pass, x, y, mode, sc, singles);
+        case 512: return launch_modes<T, 512>(a, pass, x, y, mode, sc, singles);
+        case 1024: return launch_modes<T, 1024>(a, pass, x, y, mode, sc, singles);
     }
     return -1;
 }
-template int apply2d_modes_pass<float>(const Apply2DArgs<float>&, int, const void*, void*, int, const ChanScale&);
-template int apply2d_modes_pass<double>(const Apply2DArgs<double>&, int, const void*, void*, int, const ChanScale&);
+template int apply2d_modes_pass<float>(const Apply2DArgs<float>&, int, const void*, void*, int, const ChanScale&,
+                                       int);
+template int apply2d_modes_pass<double>(const Apply2DArgs<double>&, int, const void*, void*, int, const ChanScale&,
+                                       int);
 
 }  // namespace rte

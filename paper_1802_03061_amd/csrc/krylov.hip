@@ -1,6 +1,6 @@
 // Vector kernels of the (flexible) GMRES iteration: multi-vector dot products against the Krylov
 // basis, the classical Gram-Schmidt update with its norm, linear combinations, and the packing
-// between complex mode vectors and real channel vectors.  Basis vectors are stored as TV (double,
+// between conjugate-symmetric mode vectors and real channel vectors.  Basis vectors are stored as TV (double,
 // or float for the inner solve of the FP32 apply); every sum and product is taken in FP64.
 //
 // Reductions are deterministic: a fixed grid of blocks writes one partial per (vector, block) and
@@ -320,68 +320,45 @@ __global__ __launch_bounds__(KT) void k_fill(double* __restrict__ dst, double a,
     for (size_t i = (size_t)blockIdx.x * KT + threadIdx.x; i < n; i += stride) dst[i] = a;
 }
 
-// Real channels of the conjugate-symmetric parts of a general complex mode vector x[M][N]:
-//   p_k = (x_k + conj x_{-k})/2,  q_k = (x_k - conj x_{-k})/(2i),  x = p + i q,
-// each stored as channels ch0 = Re(.)_0, ch_{2k-1} = sqrt2 Re(.)_k, ch_{2k} = sqrt2 Im(.)_k.
-// Output [2][C][N] (p first); with one_part only p (the input is taken as conjugate-symmetric).
+// Real channels of a conjugate-symmetric mode vector x[M][N]: ch0 = Re x_0, ch_{2k-1} = sqrt2 Re x_k,
+// ch_{2k} = sqrt2 Im x_k.
 __global__ __launch_bounds__(KT) void k_modes_to_channels(const cx<double>* __restrict__ x, double* __restrict__ ch,
-                                                          int L, size_t N, int one_part) {
-    const int C = 2 * L + 1;
+                                                          int L, size_t N) {
     const size_t i = (size_t)blockIdx.x * KT + threadIdx.x;
     if (i >= N) return;
     const double r2 = 1.4142135623730951;
-    const cx<double> x0 = x[(size_t)L * N + i];
-    ch[i] = x0.re;
-    if (!one_part) ch[(size_t)C * N + i] = x0.im;
+    ch[i] = x[(size_t)L * N + i].re;
     for (int k = 1; k <= L; ++k) {
         const cx<double> xp = x[(size_t)(L + k) * N + i];
-        if (one_part) {
-            ch[(size_t)(2 * k - 1) * N + i] = r2 * xp.re;
-            ch[(size_t)(2 * k) * N + i] = r2 * xp.im;
-        } else {
-            const cx<double> xm = x[(size_t)(L - k) * N + i];
-            ch[(size_t)(2 * k - 1) * N + i] = r2 * 0.5 * (xp.re + xm.re);
-            ch[(size_t)(2 * k) * N + i] = r2 * 0.5 * (xp.im - xm.im);
-            ch[(size_t)(C + 2 * k - 1) * N + i] = r2 * 0.5 * (xp.im + xm.im);
-            ch[(size_t)(C + 2 * k) * N + i] = r2 * 0.5 * (xm.re - xp.re);
-        }
+        ch[(size_t)(2 * k - 1) * N + i] = r2 * xp.re;
+        ch[(size_t)(2 * k) * N + i] = r2 * xp.im;
     }
 }
 
-// Inverse: y_k = P_k + i Q_k with P_k = (ch_{2k-1} + i ch_{2k})/sqrt2, P_{-k} = conj P_k, P_0 = ch0,
-// and Q likewise from the second part (absent when one_part).
+// Inverse: y_k = (ch_{2k-1} + i ch_{2k})/sqrt2, y_{-k} = conj y_k, y_0 = ch0.
 __global__ __launch_bounds__(KT) void k_channels_to_modes(const double* __restrict__ ch, cx<double>* __restrict__ y,
-                                                          int L, size_t N, int one_part) {
-    const int C = 2 * L + 1;
+                                                          int L, size_t N) {
     const size_t i = (size_t)blockIdx.x * KT + threadIdx.x;
     if (i >= N) return;
     const double r2 = 0.70710678118654752440;
-    const double q0 = one_part ? 0.0 : ch[(size_t)C * N + i];
-    y[(size_t)L * N + i] = mk(ch[i], q0);
+    y[(size_t)L * N + i] = mk(ch[i], 0.0);
     for (int k = 1; k <= L; ++k) {
         const cx<double> P = mk(r2 * ch[(size_t)(2 * k - 1) * N + i], r2 * ch[(size_t)(2 * k) * N + i]);
-        cx<double> Q = mk(0.0, 0.0);
-        if (!one_part) Q = mk(r2 * ch[(size_t)(C + 2 * k - 1) * N + i], r2 * ch[(size_t)(C + 2 * k) * N + i]);
-        y[(size_t)(L + k) * N + i] = P + mul_i(Q);
-        y[(size_t)(L - k) * N + i] = conj(P) + mul_i(conj(Q));
+        y[(size_t)(L + k) * N + i] = P;
+        y[(size_t)(L - k) * N + i] = conj(P);
     }
 }
 
-// Real-basis modes (3D spherical harmonics): channel a is Re u_a (and, for a general complex
-// vector, channel C + a is Im u_a); no mixing between modes.
+// Real-basis modes (3D spherical harmonics): channel a is u_a.
 __global__ __launch_bounds__(KT) void k_modes_to_channels_real(const cx<double>* __restrict__ x,
-                                                               double* __restrict__ ch, size_t n, int one_part) {
+                                                               double* __restrict__ ch, size_t n) {
     const size_t i = (size_t)blockIdx.x * KT + threadIdx.x;
-    if (i >= n) return;
-    const cx<double> v = x[i];
-    ch[i] = v.re;
-    if (!one_part) ch[n + i] = v.im;
+    if (i < n) ch[i] = x[i].re;
 }
 __global__ __launch_bounds__(KT) void k_channels_to_modes_real(const double* __restrict__ ch,
-                                                               cx<double>* __restrict__ y, size_t n, int one_part) {
+                                                               cx<double>* __restrict__ y, size_t n) {
     const size_t i = (size_t)blockIdx.x * KT + threadIdx.x;
-    if (i >= n) return;
-    y[i] = mk(ch[i], one_part ? 0.0 : ch[n + i]);
+    if (i < n) y[i] = mk(ch[i], 0.0);
 }
 
 // NaN/Inf scan helper: flag[0] = 1 if any entry is not finite.
@@ -483,24 +460,24 @@ void vec_fill(double* dst, double a, size_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_fill, dim3(grid_for(n, 4096)), dim3(KT), 0, st, dst, a, n);
 }
 
-void modes_to_channels(const void* x, double* ch, int L, size_t N, bool one_part, hipStream_t st) {
+void modes_to_channels(const void* x, double* ch, int L, size_t N, hipStream_t st) {
     hipLaunchKernelGGL(k_modes_to_channels, dim3((unsigned)((N + KT - 1) / KT)), dim3(KT), 0, st,
-                       (const cx<double>*)x, ch, L, N, one_part ? 1 : 0);
+                       (const cx<double>*)x, ch, L, N);
 }
 
-void channels_to_modes(const double* ch, void* y, int L, size_t N, bool one_part, hipStream_t st) {
+void channels_to_modes(const double* ch, void* y, int L, size_t N, hipStream_t st) {
     hipLaunchKernelGGL(k_channels_to_modes, dim3((unsigned)((N + KT - 1) / KT)), dim3(KT), 0, st, ch,
-                       (cx<double>*)y, L, N, one_part ? 1 : 0);
+                       (cx<double>*)y, L, N);
 }
 
-void modes_to_channels_real(const void* x, double* ch, size_t n, bool one_part, hipStream_t st) {
+void modes_to_channels_real(const void* x, double* ch, size_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_modes_to_channels_real, dim3((unsigned)((n + KT - 1) / KT)), dim3(KT), 0, st,
-                       (const cx<double>*)x, ch, n, one_part ? 1 : 0);
+                       (const cx<double>*)x, ch, n);
 }
 
-void channels_to_modes_real(const double* ch, void* y, size_t n, bool one_part, hipStream_t st) {
+void channels_to_modes_real(const double* ch, void* y, size_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_channels_to_modes_real, dim3((unsigned)((n + KT - 1) / KT)), dim3(KT), 0, st, ch,
-                       (cx<double>*)y, n, one_part ? 1 : 0);
+                       (cx<double>*)y, n);
 }
 
 void nonfinite_scan(const double* x, size_t n, int* flag, hipStream_t st) {

@@ -257,6 +257,42 @@ static Apply2DArgs<T> x_pass_args(const rte_ctx* c, int mode, int nbatch, ChanSc
     return a;
 }
 
+// The passes between the x-passes: pass B in 2D, B, C and D (y- and z-passes, one batch entry at a
+// time) in 3D; a = x_pass_args.  ev: an event after each, from ev[2] on.
+template <typename T>
+static int mid_passes(rte_ctx* c, const Apply2DArgs<T>& a, int mode, int nbatch, hipEvent_t* ev) {
+    if (c->dim == 2) {
+        if (apply2d_pass_b<T>(a, nbatch)) return set_error(RTE_EUNSUPPORTED, "pass B: unsupported size");
+        if (ev) (void)hipEventRecord(ev[2], c->stream);
+        return RTE_OK;
+    }
+    const int* v3 = sizeof(T) == 4 ? c->var3f : c->var3d;
+    Apply3DArgs<T> a3;
+    a3.nx = c->nx; a3.ny = c->ny; a3.nz = c->nz; a3.PX = c->PX; a3.PY = c->PY; a3.PZ = c->PZ;
+    a3.C = c->C;
+    a3.L = c->L;
+    a3.sc = channel_scale3(c, mode);
+    a3.stream = c->stream;
+    for (int p = 0; p < 3; ++p) a3.var[p] = v3[p + 1];
+    const size_t t1sz = (size_t)c->C * c->nz * (c->PX / 2 + 1) * c->ny;   // one batch entry
+    if constexpr (sizeof(T) == 4) {
+        a3.T1 = c->wf; a3.T2 = c->wf2; a3.Q3 = c->Q3f; a3.twy = c->twf[1]; a3.twz = c->twf[2];
+    } else {
+        a3.T1 = c->wd; a3.T2 = c->wd2; a3.Q3 = c->Q3d; a3.twy = c->twd[1]; a3.twz = c->twd[2];
+    }
+    cx<T>* T1base = a3.T1;
+    for (int bi = 0; bi < nbatch; ++bi) {
+        a3.T1 = T1base + (size_t)bi * t1sz;
+        if (apply3d_pass<T>(a3, 1)) return set_error(RTE_EUNSUPPORTED, "3D pass B: unsupported size");
+        if (ev && bi == nbatch - 1) (void)hipEventRecord(ev[2], c->stream);
+        if (apply3d_pass<T>(a3, 2)) return set_error(RTE_EUNSUPPORTED, "3D pass C: unsupported size");
+        if (ev && bi == nbatch - 1) (void)hipEventRecord(ev[3], c->stream);
+        if (apply3d_pass<T>(a3, 3)) return set_error(RTE_EUNSUPPORTED, "3D pass D: unsupported size");
+    }
+    if (ev) (void)hipEventRecord(ev[4], c->stream);
+    return RTE_OK;
+}
+
 // have_a: pass A's output is in the work buffer (x is not read then in mode APPLY_K).
 template <typename T, typename TV>
 static int apply_t(rte_ctx* c, int mode, const TV* x, const double* b, TV* y, int nbatch, hipEvent_t* ev,
@@ -268,39 +304,9 @@ static int apply_t(rte_ctx* c, int mode, const TV* x, const double* b, TV* y, in
     if (ev) (void)hipEventRecord(ev[0], c->stream);
     if (!have_a && apply2d_pass_a<T>(a, x, sc, nx_b)) return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
     if (ev) (void)hipEventRecord(ev[1], c->stream);
-    if (c->dim == 2) {
-        if (apply2d_pass_b<T>(a, nbatch)) return set_error(RTE_EUNSUPPORTED, "pass B: unsupported size");
-        if (ev) (void)hipEventRecord(ev[2], c->stream);
-        if (apply2d_pass_c<T>(a, x, b, y, cmode, nx_b)) return set_error(RTE_EUNSUPPORTED, "pass C: unsupported size");
-        if (ev) (void)hipEventRecord(ev[3], c->stream);
-    } else {
-        const int* v3 = sizeof(T) == 4 ? c->var3f : c->var3d;
-        Apply3DArgs<T> a3;
-        a3.nx = c->nx; a3.ny = c->ny; a3.nz = c->nz; a3.PX = c->PX; a3.PY = c->PY; a3.PZ = c->PZ;
-        a3.C = c->C;
-        a3.L = c->L;
-        a3.sc = channel_scale3(c, mode);
-        a3.stream = c->stream;
-        for (int p = 0; p < 3; ++p) a3.var[p] = v3[p + 1];
-        const size_t t1sz = (size_t)c->C * c->nz * (c->PX / 2 + 1) * c->ny;   // one batch entry
-        if constexpr (sizeof(T) == 4) {
-            a3.T1 = c->wf; a3.T2 = c->wf2; a3.Q3 = c->Q3f; a3.twy = c->twf[1]; a3.twz = c->twf[2];
-        } else {
-            a3.T1 = c->wd; a3.T2 = c->wd2; a3.Q3 = c->Q3d; a3.twy = c->twd[1]; a3.twz = c->twd[2];
-        }
-        cx<T>* T1base = a3.T1;
-        for (int bi = 0; bi < nbatch; ++bi) {
-            a3.T1 = T1base + (size_t)bi * t1sz;
-            if (apply3d_pass<T>(a3, 1)) return set_error(RTE_EUNSUPPORTED, "3D pass B: unsupported size");
-            if (ev && bi == nbatch - 1) (void)hipEventRecord(ev[2], c->stream);
-            if (apply3d_pass<T>(a3, 2)) return set_error(RTE_EUNSUPPORTED, "3D pass C: unsupported size");
-            if (ev && bi == nbatch - 1) (void)hipEventRecord(ev[3], c->stream);
-            if (apply3d_pass<T>(a3, 3)) return set_error(RTE_EUNSUPPORTED, "3D pass D: unsupported size");
-        }
-        if (ev) (void)hipEventRecord(ev[4], c->stream);
-        if (apply2d_pass_c<T>(a, x, b, y, cmode, nx_b)) return set_error(RTE_EUNSUPPORTED, "3D pass E: unsupported size");
-        if (ev) (void)hipEventRecord(ev[5], c->stream);
-    }
+    if (int rc = mid_passes<T>(c, a, mode, nbatch, ev)) return rc;
+    if (apply2d_pass_c<T>(a, x, b, y, cmode, nx_b)) return set_error(RTE_EUNSUPPORTED, "last pass: unsupported size");
+    if (ev) (void)hipEventRecord(ev[c->dim == 2 ? 3 : 5], c->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_hip_error(e, "apply launch", __FILE__, __LINE__);
     return RTE_OK;
@@ -1128,7 +1134,7 @@ int rte_setup(rte_ctx** out, const rte_grid* g, double mu_a, double mu_s, const 
     }
     const size_t n = c->nvec;
     if ((rc = dalloc(&c->xv, n)) || (rc = dalloc(&c->rv, n)) || (rc = dalloc(&c->bv, n)) ||
-        (rc = dalloc(&c->t0, 2 * n)) || (rc = dalloc(&c->t1, 2 * n)) || (rc = dalloc(&c->dflag, 4))) {
+        (rc = dalloc(&c->t0, n)) || (rc = dalloc(&c->t1, n)) || (rc = dalloc(&c->dflag, 4))) {
         free_ctx(c);
         return rc;
     }
@@ -1216,25 +1222,27 @@ int rte_set_solve_opts(rte_ctx* c, const rte_solve_opts* o) {
 
 }  // extern "C"
 
-// Complex modes <-> real channels: 2D pairs modes k and -k (rte.h), 3D modes are real already.
-static void to_channels(const rte_ctx* c, const void* x, double* ch, bool one_part) {
-    if (c->dim == 3) modes_to_channels_real(x, ch, c->nvec, one_part, c->stream);
-    else modes_to_channels(x, ch, c->L, c->ncell, one_part, c->stream);
+// Modes of a real field <-> channels: 2D pairs modes k and -k (rte.h), 3D modes are real already.
+static void to_channels(const rte_ctx* c, const void* x, double* ch) {
+    if (c->dim == 3) modes_to_channels_real(x, ch, c->nvec, c->stream);
+    else modes_to_channels(x, ch, c->L, c->ncell, c->stream);
 }
-static void to_modes(const rte_ctx* c, const double* ch, void* y, bool one_part) {
-    if (c->dim == 3) channels_to_modes_real(ch, y, c->nvec, one_part, c->stream);
-    else channels_to_modes(ch, y, c->L, c->ncell, one_part, c->stream);
+static void to_modes(const rte_ctx* c, const double* ch, void* y) {
+    if (c->dim == 3) channels_to_modes_real(ch, y, c->nvec, c->stream);
+    else channels_to_modes(ch, y, c->L, c->ncell, c->stream);
 }
 
-// The 2D apply on complex modes, the conversions from and to channels inside passes A and C.
+// The apply on complex modes, the conversions from and to channels inside the x-passes.
 template <typename T>
 static int apply_modes(rte_ctx* c, int mode, const void* x, void* y) {
     ChanScale sc;
     int nb;
     const Apply2DArgs<T> a = x_pass_args<T>(c, mode, 2, sc, nb);
-    if (apply2d_modes_pass<T>(a, 0, x, nullptr, mode, sc)) return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
-    if (apply2d_pass_b<T>(a, 2)) return set_error(RTE_EUNSUPPORTED, "pass B: unsupported size");
-    if (apply2d_modes_pass<T>(a, 2, x, y, mode, sc)) return set_error(RTE_EUNSUPPORTED, "pass C: unsupported size");
+    // 3D: channels are modes; the slabs of all of them
+    const int singles = c->dim == 3 ? c->C * c->nz : 0;
+    if (apply2d_modes_pass<T>(a, 0, x, nullptr, mode, sc, singles)) return set_error(RTE_EUNSUPPORTED, "pass A: unsupported size");
+    if (int rc = mid_passes<T>(c, a, mode, 2, nullptr)) return rc;
+    if (apply2d_modes_pass<T>(a, 2, x, y, mode, sc, singles)) return set_error(RTE_EUNSUPPORTED, "last pass: unsupported size");
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? RTE_OK : set_hip_error(e, "rte_apply", __FILE__, __LINE__);
 }
@@ -1251,24 +1259,18 @@ int rte_apply(rte_ctx* c, int op, int layout, int prec, const void* x, void* y) 
     if (x == y) return set_error(RTE_EINVAL, "x and y may not alias");
     const int mode = op == RTE_OP_A ? APPLY_A : APPLY_KT;
     if (layout == RTE_LAYOUT_CHANNELS) return apply_channels(c, mode, prec, (const double*)x, nullptr, (double*)y, 1);
-    if (c->dim == 2) return prec == RTE_PREC_FP32 ? apply_modes<float>(c, mode, x, y) : apply_modes<double>(c, mode, x, y);
-    to_channels(c, x, c->t0, false);
-    int rc = apply_channels(c, mode, prec, c->t0, nullptr, c->t1, 2);
-    if (rc) return rc;
-    to_modes(c, c->t1, y, false);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? RTE_OK : set_hip_error(e, "rte_apply", __FILE__, __LINE__);
+    return prec == RTE_PREC_FP32 ? apply_modes<float>(c, mode, x, y) : apply_modes<double>(c, mode, x, y);
 }
 
 int rte_modes_to_channels(rte_ctx* c, const void* modes, double* ch) {
     if (!c || !modes || !ch) return set_error(RTE_EINVAL, "NULL argument");
-    to_channels(c, modes, ch, true);
+    to_channels(c, modes, ch);
     return RTE_OK;
 }
 
 int rte_channels_to_modes(rte_ctx* c, const double* ch, void* modes) {
     if (!c || !modes || !ch) return set_error(RTE_EINVAL, "NULL argument");
-    to_modes(c, ch, modes, true);
+    to_modes(c, ch, modes);
     return RTE_OK;
 }
 
@@ -1303,7 +1305,7 @@ int rte_rhs(rte_ctx* c, const double* f, int layout, void* b) {
     if (layout == RTE_LAYOUT_CHANNELS) return rhs_channels(c, f, (double*)b);
     int rc = rhs_channels(c, f, c->bv);
     if (rc) return rc;
-    to_modes(c, c->bv, b, true);
+    to_modes(c, c->bv, b);
     return RTE_OK;
 }
 
@@ -1315,7 +1317,7 @@ int rte_solve(rte_ctx* c, const double* f, double tol, int max_iter, void* u, rt
     if (rc) return rc;
     // the modes of x are written after every true residual, while the host waits for its norm
     SolveFinish fin;
-    fin.fn = [](rte_ctx* cc, void* uu) { to_modes(cc, cc->xv, uu, true); };
+    fin.fn = [](rte_ctx* cc, void* uu) { to_modes(cc, cc->xv, uu); };
     fin.arg = u;
     rc = solve_core(c, c->bv, tol, max_iter, c->xv, info, nullptr, 0, nullptr, &fin);
     if (rc < 0) return rc;
@@ -1331,7 +1333,7 @@ int rte_solve(rte_ctx* c, const double* f, double tol, int max_iter, void* u, rt
 static int rhs_source_channels(rte_ctx* c, const void* g, int layout, double* b) {
     const double* gc = (const double*)g;
     if (layout == RTE_LAYOUT_MODES) {
-        to_channels(c, g, c->t0, true);
+        to_channels(c, g, c->t0);
         gc = c->t0;
     }
     return apply_channels(c, APPLY_KT, RTE_PREC_FP64, gc, nullptr, b, 1);
@@ -1344,7 +1346,7 @@ int rte_rhs_source(rte_ctx* c, const void* g, int layout, void* b) {
     if (layout == RTE_LAYOUT_CHANNELS) return rhs_source_channels(c, g, layout, (double*)b);
     int rc = rhs_source_channels(c, g, layout, c->bv);
     if (rc) return rc;
-    to_modes(c, c->bv, b, true);
+    to_modes(c, c->bv, b);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? RTE_OK : set_hip_error(e, "rte_rhs_source", __FILE__, __LINE__);
 }
@@ -1359,7 +1361,7 @@ int rte_solve_source(rte_ctx* c, const void* g, int layout, double tol, int max_
     SolveFinish fin;
     fin.arg = u;
     fin.fn = layout == RTE_LAYOUT_MODES
-                 ? (void (*)(rte_ctx*, void*))[](rte_ctx* cc, void* uu) { to_modes(cc, cc->xv, uu, true); }
+                 ? (void (*)(rte_ctx*, void*))[](rte_ctx* cc, void* uu) { to_modes(cc, cc->xv, uu); }
                  : (void (*)(rte_ctx*, void*))[](rte_ctx* cc, void* uu) {
                        (void)hipMemcpyAsync(uu, cc->xv, cc->nvec * sizeof(double), hipMemcpyDeviceToDevice, cc->stream);
                    };
@@ -1438,7 +1440,7 @@ int rte_solve_multi(rte_ctx* c, int nrhs, const double* const* f, double tol, in
         vec_scale(c->bm + s * nv, c->bm + s * nv, bn[s], nv, st);
     }
     if ((rc = apply_channels(c, APPLY_RESID, RTE_PREC_FP64, c->xm, c->bm, c->rm, nrhs))) return rc;
-    for (int s = 0; s < nrhs; ++s) to_modes(c, c->xm + s * nv, u[s], true);
+    for (int s = 0; s < nrhs; ++s) to_modes(c, c->xm + s * nv, u[s]);
     int worst = RTE_OK;
     for (int s = 0; s < nrhs; ++s) {
         double r2 = 0.0;
