@@ -95,7 +95,7 @@ def pmc_summary(fetch_csv: str, write_csv: str, variants) -> dict:
 
     # passes A and C: template arguments T, PX, TR, threads, vector type (and, for A, whether the
     # coarse correction is staged); the apply timing runs the unstaged form
-    for label, key, tv in (("A", "k_pass_a<float, 1024,", "double"), ("B", "k_pass_b_lds<float, 1024, 8,", None),
+    for label, key, tv in (("A", "k_pass_a<float, 1024,", "double"), ("B", "k_pass_b_wave<float, 1024, 8,", None),
                            ("C", "k_pass_c<float, 1024,", "double"), ("A_f32", "k_pass_a<float, 1024,", "float"),
                            ("C_f32", "k_pass_c<float, 1024,", "float")):
         names = [k for k in fe if key in k and (tv is None or (targs(k)[4] == tv and targs(k)[5:] in ([], ["false"])))]
@@ -654,8 +654,8 @@ def bench_sh3d(args, torch, rte, mu_s):
 
 
 def bench_modes(args, torch, rte, mu_s):
-    """2D with many modes (L = 16, 33 modes; the split pass B with the autotuner's choice of the
-    mode-axis FFT or the direct coupling), 256^2."""
+    """2D with many modes (L = 16, 33 modes; pass B in one kernel, in split form where the column
+    spectra do not fit LDS), 256^2."""
     from paper_1802_03061_amd import inputs
     w = inputs.workload("modes", seed=0, mu_s=mu_s)
     n, L = w["n"], w["L"]
@@ -664,11 +664,12 @@ def bench_modes(args, torch, rte, mu_s):
     torch.cuda.synchronize()
     r = timed_solves(ctx, fs, args.steps, args.warmup, torch)
     sols = {"gpu": seed0_solution(ctx, fs[0])}
-    pb = apply_split_bytes(n, L)
+    split = L > 16 or padded(n) > 512
+    pb = apply_split_bytes(n, L) if split else apply_pass_bytes(n, L)
     rf = roofline(ctx, rte, pb, args.apply_reps, ["A", "B", "C"])
-    coupling = {}
+    coupling = {}   # the split form's couplings
     vb, nvb = ctx.get_variant(rte.PREC_FP32, 1)
-    for v in range(nvb):
+    for v in range(nvb if split else 0):
         ctx.set_variant(rte.PREC_FP32, 1, v)
         coupling[("mode-axis FFT", "direct")[v]] = ctx.time_apply(rte.OP_A, rte.PREC_FP32, reps=args.apply_reps)[1][1]
     ctx.set_variant(rte.PREC_FP32, 1, vb)
@@ -680,7 +681,7 @@ def bench_modes(args, torch, rte, mu_s):
                    "n": n, "L": L, "mu_s": mu_s},
         "solve": r, "applies_per_s": 1000.0 / rf["ms_apply"],
         "apply_ms": {"fp32_total": rf["ms_apply"], "fp32_passes": rf["passes"]},
-        "pass_b_ms_by_coupling": coupling, "pass_b_coupling_chosen": ("mode-axis FFT", "direct")[vb],
+        "pass_b_ms_by_coupling": coupling, "pass_b_coupling_chosen": ("mode-axis FFT", "direct")[vb] if split else "in channels, one kernel",
         "apply_hbm_fraction": rf["apply_hbm_fraction"], "apply_bytes": pb, "roofline": rf["roofline"],
     }
     return out, ctx, w, sols

@@ -340,12 +340,19 @@ static void launch_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, 
 template <typename T, int PX, int TR, typename TV>
 static void launch_ua_tr(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
                          const ChanScale& sc, int nchan_total, int* nblk) {
-    dim3 grid((a.ny + TR - 1) / TR, nchan_total);
-    *nblk = (int)(grid.x * grid.y);
-    hipLaunchKernelGGL((k_update_a<T, PX, TR, 256, TV>), grid, dim3(256), 0, a.stream, w, V, ld, t, partial, a.work,
-                       a.twx, a.nx, a.ny, a.C, sc, a.pack);
+    if constexpr (TR > 2 && PassATile<PX, TR, 256>::IT > 1) {
+        launch_ua_tr<T, PX, TR / 2>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+    } else {
+        dim3 grid((a.ny + TR - 1) / TR, nchan_total);
+        *nblk = (int)(grid.x * grid.y);
+        hipLaunchKernelGGL((k_update_a<T, PX, TR, 256, TV>), grid, dim3(256), 0, a.stream, w, V, ld, t, partial, a.work,
+                           a.twx, a.nx, a.ny, a.C, sc, a.pack);
+    }
 }
-// the row tiles of pass A
+// The row tile of pass A (the tuner's), but at most one butterfly per thread: the update holds a thread's
+// inputs of several basis vectors.  Solves in FP32 with tiles of 4, 8, 16 and 32 rows: 512^2, L = 8 5.96,
+// 5.92, 6.66 and 14.4 ms; 512^2, L = 0 1.49, 1.53, 1.80, 5.65; 256^2, L = 4 1.62, 1.63, 1.68, 1.92; where
+// rows are short the tiles that pass A's stores want are better: 64^3 to degree 2 7.1, 5.4, 4.9, 4.6.
 template <typename T, int PX, typename TV>
 static void launch_ua(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
                       const ChanScale& sc, int nchan_total, int* nblk) {

@@ -38,7 +38,7 @@ struct rte_ctx {
     double* rv = nullptr;
     double* bv = nullptr;
     double* t0 = nullptr;   // one vector (with t1: inputs, tuning)
-    double* t1 = nullptr;   // 2 vectors
+    double* t1 = nullptr;
     int work_nb = 2;        // batch entries (right-hand sides) the FFT work buffers hold
     // several right-hand sides sharing the operator (rte_solve_multi): stacked x, r, b
     int multi_nb = 0;
