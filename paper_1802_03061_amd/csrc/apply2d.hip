@@ -65,8 +65,8 @@ __global__ __launch_bounds__(NTHR) void k_pass_a(const TV* __restrict__ x, cx<T>
 // Bound: HBM, the basis read once; the tiles are taken backwards, since the last lines the dots read
 // are still in the memory-side cache.  At 512^2, L = 8 in FP32 with 12 basis vectors it takes 100 us
 // (5.3 TB/s), where the update (88), the rescaling launch (6) and pass A (17) took 111, and pass C without
-// its input 18.5 instead of 21.5; a solve of 37 iterations 6.57 -> 6.06 ms.  G vectors' loads are in flight at
-// once, as many as registers hold.
+// its input 18.5 instead of 21.5; a solve of 33 iterations 6.77 -> 6.49 ms.  G vectors' loads are in flight
+// at once, as many as registers hold.
 template <typename T, int PX, int TR, int NTHR, typename TV>
 __global__ __launch_bounds__(NTHR) void k_update_a(TV* w, const TV* V, size_t ld, ArnoldiArgs t, double* partial,
                                                    cx<T>* Tb, const cx<T>* tw, int nx, int ny, int C, ChanScale sc,

@@ -10,8 +10,8 @@
 // separate conversions to channels and back were two launches and 4 (2L+1) real vectors of traffic.
 //
 // A block takes R rows of one mode pair (k, -k), 2R transforms (k = 0: R); without PAIR (3D, where every
-// mode is a channel) R rows of one slab.  Bound: latency at small
-// grids, HBM at large ones.  Applies with conversions and without, us: FP32 200x150, L = 2 32.7 and 24.0;
+// mode is a channel) R rows of one slab.  Bound: latency at small grids, HBM at large ones.  Applies
+// with conversions and without, us: FP32 200x150, L = 2 32.7 and 24.0;
 // 16^2, L = 7 25.6 and 12.8; 512^2, L = 2 63.8 and 49.3; FP64 512^2, L = 0 40.8 and 29.3;
 // 3D FP32 isotropic 32^3 33.7 and 24.9, 128^3 155 and 116, 64^3 to degree 2 177 and 155.
 #include "apply2d.h"

@@ -423,8 +423,8 @@ __global__ __launch_bounds__(NW * 64) void k_pass_b_wave(cx<T>* __restrict__ Tb,
 // wave's rows) and written once; no full-length buffer.  The quarter spectra are kept even frequencies
 // first (half_entry), so that each half reads whole lines of its own: with frequencies in order both
 // halves fetched every line.  At 512^2 in FP64 this took pass B from 98 to 88 us for L = 8 and from 73
-// to 66 for L = 6 (holding rows at L = 8 spills: 94 and 101 us for one and two); forward transforms, coupling and inverse
-// transforms through a full-length buffer (785 MB, at the HBM rate) took 150 us.
+// to 66 for L = 6 (holding rows at L = 8 spills: 94 and 101 us for one and two); forward transforms,
+// coupling and inverse transforms through a full-length buffer (785 MB, at the HBM rate) took 150 us.
 
 // All PH inputs of a transform's first stage.
 template <typename T, int P, int LN>
