@@ -57,11 +57,14 @@ __global__ __launch_bounds__(NTHR) void k_pass_a(const TV* __restrict__ x, cx<T>
                                              tid, cc, cF, cs, crow);
 }
 
-// The plain solver's Gram-Schmidt update fused with pass A of the next apply.  The basis spans the
-// Krylov space of K (A = I - K), so the apply needs its input only here; basis vector i is inv[i] times
-// the stored u_i, where inv comes from the exact |u_i|^2 that the next reduction adds up, so that
-// nothing rescales u_i and one pass reads w and writes u_{j+1} and its x-spectrum:
-//     u_{j+1} = a (w - sum_i inv_i^2 <u_i, w> u_i),  w = K u_j,  a as in arnoldi_stage0_lazy.
+// The plain solver's Gram-Schmidt update fused with pass A of the next apply.  The apply writes w = K u_j
+// alone (A = I - K), so it needs its input only here: the dots and this update, which read u_j anyway,
+// form A u_j = u_j - w.  (The Arnoldi process on K itself, the same space, loses its orthogonality in
+// diffusive media: there K v_j is nearly v_j, and what is left after the projection is small against
+// it.  64^2, mu_s h = 1.6 took 77 iterations instead of 31.)  Basis vector i is inv[i] times the stored
+// u_i, where inv comes from the exact |u_i|^2 that the next reduction adds up, so that nothing rescales
+// u_i and one pass reads w and writes u_{j+1} and its x-spectrum:
+//     u_{j+1} = a (u_j - w - sum_i inv_i^2 <u_i, u_j - w> u_i),  a as in arnoldi_stage0_lazy.
 // Bound: HBM, the basis read once; the tiles are taken backwards, since the last lines the dots read
 // are still in the memory-side cache.  At 512^2, L = 8 in FP32 with 12 basis vectors it takes 100 us
 // (5.3 TB/s), where the update (88), the rescaling launch (6) and pass A (17) took 111, and pass C without
@@ -90,7 +93,7 @@ __global__ __launch_bounds__(NTHR) void k_update_a(TV* w, const TV* V, size_t ld
 #pragma unroll
     for (int it = 0; it < IT; ++it)
 #pragma unroll
-        for (int r = 0; r < RH; ++r) { ra[it][r] = (double)la[it][r]; rb[it][r] = (double)lb[it][r]; }
+        for (int r = 0; r < RH; ++r) { ra[it][r] = -(double)la[it][r]; rb[it][r] = -(double)lb[it][r]; }
     auto subtract = [&](int i, auto gc) {
         constexpr int N = decltype(gc)::value;
         TV va[N][IT][RH], vb[N][IT][RH];

@@ -69,7 +69,6 @@ __device__ __forceinline__ void arnoldi_stage0_in_update(const ArnoldiArgs& t, c
 // on breakdown) it sets flags[3] and inv[j+1] = 1/sqrt(nu2), and the caller's rescale pass, which
 // runs only under that flag, makes the stored vector unit-norm with H[j+1, j] = sqrt(nu2)/a.
 // st layout: [0..m] h pass 1 | [m+1] |w|^2 | [m+2] |w1|^2 | [m+4..2m+4] h pass 2 | [2m+5] a
-// of_k: the columns are those of K; A v_j = v_j - K v_j makes A's column e_j - h with -H[j+1, j] below.
 // nu2, when given, stands for st[j+2].
 __device__ __forceinline__ void arnoldi_block(const ArnoldiArgs t, const double* nu2 = nullptr) {
     __shared__ double red[ARN_MAXROW];
@@ -128,10 +127,6 @@ __device__ __forceinline__ void arnoldi_block(const ArnoldiArgs t, const double*
         inv = breakdown ? 0.0 : 1.0 / hn;
     }
     hl[j + 1] = hval;
-    if (t.of_k) {
-        for (int i = 0; i <= j + 1; ++i) hl[i] = -hl[i];
-        hl[j] += 1.0;
-    }
     for (int i = 0; i < j; ++i) {
         const double x = csl[i] * hl[i] + snl[i] * hl[i + 1];
         hl[i + 1] = -snl[i] * hl[i] + csl[i] * hl[i + 1];
@@ -222,11 +217,11 @@ __device__ __forceinline__ double arnoldi_stage1_in_rescale(const ArnoldiArgs& t
     return inv_sh;
 }
 
-// Stage 0 of a column of K with lazy factors (k_update_a): the basis vectors are inv[i] times the
-// stored u_i, and raw[i] = <u_i, w> (t.st), w = K u_j.  For the update w - sum_i c_i u_i: c_i =
-// inv[i]^2 raw[i], returned negative in nc (LDS), and the factor a that makes the result near unit
-// length (fused_factor), in *a_sh.  The first block also stores H[i][j] = inv[i] inv[j] raw[i] and, for
-// stage 1, |K v_j|^2 and a / inv[j].  g: as nc.  The caller synchronises the block before it reads them.
+// Stage 0 of a column with lazy factors (k_update_a): the basis vectors are inv[i] times the stored
+// u_i, w = K u_j, and raw[i] = <u_i, u_j - w> (t.st).  For the update u_j - w - sum_i inv[i]^2 raw[i] u_i
+// it returns the coefficients of u_0 .. u_j in nc (LDS) and the factor a that makes the result near unit
+// length (fused_factor) in *a_sh.  The first block also stores H[i][j] = inv[i] inv[j] raw[i] and, for
+// stage 1, |A v_j|^2 and a / inv[j].  g: as nc.  The caller synchronises the block before it reads them.
 template <int NTHR>
 __device__ __forceinline__ void arnoldi_stage0_lazy(const ArnoldiArgs& t, bool first_block, double* nc, double* g,
                                                     double* a_sh) {
@@ -234,7 +229,7 @@ __device__ __forceinline__ void arnoldi_stage0_lazy(const ArnoldiArgs& t, bool f
     for (int i = threadIdx.x; i <= j; i += NTHR) {
         const double f = t.inv[i], gi = f * t.st[i];
         g[i] = gi;
-        nc[i] = -f * gi;
+        nc[i] = (i == j ? 1.0 : 0.0) - f * gi;
     }
     __syncthreads();
     if (threadIdx.x != 0) return;

@@ -12,7 +12,6 @@ namespace rte {
 // j of a restart length m, the Givens rotations, the residual vector g and the flags.
 struct ArnoldiArgs {
     int stage = 0, j = 0, m = 0, reorth = 0, fused = 0;
-    int of_k = 0;   // the columns are those of K, A = I - K (lazy factors, see k_update_a)
     double renorm_tol = 1e-10;
     double* st = nullptr;
     double* H = nullptr;
@@ -31,11 +30,12 @@ unsigned krylov_nblk(size_t n);
 // out[v] = <V_v, w> for v < nvec (V_v = V + v*ld); out[nvec] = <w, w> if with_norm.  With out NULL
 // only the per-block partial sums are written (row v of krylov_nblk(n) entries).
 // partial needs (nvec + 1) * RTE_KRYLOV_NBLK doubles.
-// active (device int, may be null): the kernels do nothing when *active == 0.  stage1: also stage 1
-// of that column, as arn1_run, beside the dots.
+// active (device int, may be null): the kernels do nothing when *active == 0.  of_a: w = K u for the
+// last basis vector u, and the dots (and the norm) are taken with A u = u - w.  stage1: also stage 1 of
+// that column, as arn1_run, beside the dots.
 template <typename TV>
 void krylov_dots(const TV* V, size_t ld, int nvec, const TV* w, size_t n, double* partial,
-                 double* out, bool with_norm, hipStream_t st, const int* active = nullptr,
+                 double* out, bool with_norm, hipStream_t st, const int* active = nullptr, bool of_a = false,
                  const ArnoldiArgs* stage1 = nullptr, const double* upd = nullptr, int nupd = 0);
 // w -= sum_v h[v] V_v (h on the device); *norm_out = <w, w> after the update (with norm_out NULL
 // only partial row 0 is written).  With stage0 (the fused single pass, h = stage0->st) w is also

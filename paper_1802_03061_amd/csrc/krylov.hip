@@ -51,12 +51,14 @@ __global__ __launch_bounds__(KT) void k_arn1(ArnoldiArgs t, const double* __rest
 // (v < NV, row stride ld), and norm_partial[blk] = sum of w[i]^2 over the slice when norm_partial
 // is given.  The vector count is a template parameter so that every load of a step is issued before
 // the first multiply.  With even n and ld (and 16-byte aligned V and w) each thread reads element
-// pairs as 16-byte loads.  With upd, one more block (the first to start) runs stage 1 of the column
+// pairs as 16-byte loads.  DOTS_A: w = K u, and A u = u - w takes the place of w, formed here in FP64; u
+// is the group's last vector or, with DOTS_A_SEP, read beside it.  With upd, one more block (the first to start) runs stage 1 of the column
 // before, which nothing needs until this column's update: 7 us out of the way of the step.  The slice
 // a block covers and the order of its sums do not depend on the data.
-template <int NV, bool PAIRS, typename TV>
+enum { DOTS_W = 0, DOTS_A = 1, DOTS_A_SEP = 2 };
+template <int NV, bool PAIRS, int FORM, typename TV>
 __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, size_t ld,
-                                                    const TV* __restrict__ w, size_t n,
+                                                    const TV* __restrict__ w, const TV* __restrict__ u, size_t n,
                                                     double* __restrict__ partial,
                                                     double* __restrict__ norm_partial,
                                                     const int* __restrict__ active, ArnoldiArgs t,
@@ -81,20 +83,29 @@ __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, si
         const P2* V2 = reinterpret_cast<const P2*>(V);
         for (size_t i = (size_t)blk * KT + threadIdx.x; i < np; i += stride) {
             const P2 wl = w2[i];
-            P2 al[NV > 0 ? NV : 1];
+            P2 al[NV > 0 ? NV : 1], ul = wl;
+            if constexpr (FORM == DOTS_A_SEP) ul = reinterpret_cast<const P2*>(u)[i];
 #pragma unroll
             for (int v = 0; v < NV; ++v) al[v] = V2[(size_t)v * ldp + i];
-            const double wx = (double)wl.x, wy = (double)wl.y;
+            if constexpr (FORM == DOTS_A) ul = al[NV - 1];
+            double wx = (double)wl.x, wy = (double)wl.y;
+            if constexpr (FORM != DOTS_W) {
+                wx = (double)ul.x - wx;
+                wy = (double)ul.y - wy;
+            }
             if (do_norm) nrm += wx * wx + wy * wy;
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] += (double)al[v].x * wx + (double)al[v].y * wy;
         }
     } else {
         for (size_t i = (size_t)blk * KT + threadIdx.x; i < n; i += stride) {
-            const double wi = (double)w[i];
+            double wi = (double)w[i], ui = 0.0;
+            if constexpr (FORM == DOTS_A_SEP) ui = (double)u[i];
             double a[NV > 0 ? NV : 1];
 #pragma unroll
             for (int v = 0; v < NV; ++v) a[v] = (double)V[(size_t)v * ld + i];
+            if constexpr (FORM == DOTS_A) ui = a[NV - 1];
+            if constexpr (FORM != DOTS_W) wi = ui - wi;
             if (do_norm) nrm += wi * wi;
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] += a[v] * wi;
@@ -111,16 +122,17 @@ __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, si
     }
 }
 
-template <bool PAIRS, typename TV>
-static void launch_dots(int nv, unsigned nblk, hipStream_t st, const TV* V, size_t ld, const TV* w, size_t n,
-                        double* partial, double* norm_partial, const int* active, const ArnoldiArgs& t,
+template <bool PAIRS, int FORM, typename TV>
+static void launch_dots(int nv, unsigned nblk, hipStream_t st, const TV* V, size_t ld, const TV* w, const TV* u,
+                        size_t n, double* partial, double* norm_partial, const int* active, const ArnoldiArgs& t,
                         const double* upd, int nupd) {
     const unsigned grid = nblk + (upd ? 1 : 0);
     switch (nv) {
 #define RTE_DOTS_CASE(K)                                                                                     \
     case K:                                                                                                  \
-        hipLaunchKernelGGL((k_dot_partial<K, PAIRS, TV>), dim3(grid), dim3(KT), 0, st, V, ld, w, n, partial,     \
-                           norm_partial, active, t, upd, nupd);                                                            \
+        if constexpr (K > 0 || FORM == DOTS_W)                                                               \
+            hipLaunchKernelGGL((k_dot_partial<K, PAIRS, FORM, TV>), dim3(grid), dim3(KT), 0, st, V, ld, w, u, n,   \
+                               partial, norm_partial, active, t, upd, nupd);                                 \
         break;
         RTE_DOTS_CASE(0) RTE_DOTS_CASE(1) RTE_DOTS_CASE(2) RTE_DOTS_CASE(3) RTE_DOTS_CASE(4) RTE_DOTS_CASE(5)
         RTE_DOTS_CASE(6) RTE_DOTS_CASE(7) RTE_DOTS_CASE(8) RTE_DOTS_CASE(9) RTE_DOTS_CASE(10) RTE_DOTS_CASE(11)
@@ -379,18 +391,22 @@ unsigned krylov_nblk(size_t n) { return grid_for(n, RTE_KRYLOV_NBLK); }
 
 template <typename TV>
 void krylov_dots(const TV* V, size_t ld, int nvec, const TV* w, size_t n, double* partial,
-                 double* out, bool with_norm, hipStream_t st, const int* active, const ArnoldiArgs* stage1,
-                 const double* upd, int nupd) {
+                 double* out, bool with_norm, hipStream_t st, const int* active, bool of_a,
+                 const ArnoldiArgs* stage1, const double* upd, int nupd) {
     const ArnoldiArgs none;
     const unsigned nblk = grid_for(n, RTE_KRYLOV_NBLK);
     const bool pairs = n % 2 == 0 && ld % 2 == 0 && ((uintptr_t)V % 16) == 0 && ((uintptr_t)w % 16) == 0;
+    const TV* u = V + (size_t)(nvec - 1) * ld;   // of_a only
     // groups of up to VB basis vectors; the first group also sums w^2 (into row nvec of partial)
     for (int v0 = 0; v0 < nvec || (v0 == 0 && with_norm); v0 += VB) {
         const int nv = std::min(VB, nvec - v0);
         double* np = (with_norm && v0 == 0) ? partial + (size_t)nvec * nblk : nullptr;
         const bool s1 = stage1 && v0 == 0;
-        auto launch = pairs ? launch_dots<true, TV> : launch_dots<false, TV>;
-        launch(nv, nblk, st, V + (size_t)v0 * ld, ld, w, n, partial + (size_t)v0 * nblk, np, active, s1 ? *stage1 : none,
+        const bool last = v0 + nv == nvec;
+        auto launch = !of_a ? (pairs ? launch_dots<true, DOTS_W, TV> : launch_dots<false, DOTS_W, TV>)
+                      : last ? (pairs ? launch_dots<true, DOTS_A, TV> : launch_dots<false, DOTS_A, TV>)
+                             : (pairs ? launch_dots<true, DOTS_A_SEP, TV> : launch_dots<false, DOTS_A_SEP, TV>);
+        launch(nv, nblk, st, V + (size_t)v0 * ld, ld, w, u, n, partial + (size_t)v0 * nblk, np, active, s1 ? *stage1 : none,
                s1 ? upd : nullptr, nupd);
     }
     const int nout = nvec + (with_norm ? 1 : 0);
@@ -487,7 +503,7 @@ void nonfinite_scan(const double* x, size_t n, int* flag, hipStream_t st) {
 
 #define RTE_KRYLOV_INST(TV)                                                                                     \
     template void krylov_dots<TV>(const TV*, size_t, int, const TV*, size_t, double*, double*, bool, hipStream_t, \
-                                  const int*, const ArnoldiArgs*, const double*, int);                          \
+                                  const int*, bool, const ArnoldiArgs*, const double*, int);                    \
     template void krylov_update<TV>(TV*, const TV*, size_t, int, const double*, size_t, double*, double*,       \
                                     hipStream_t, const int*, const ArnoldiArgs*);                               \
     template void vec_scale_dev<TV>(TV*, const TV*, const double*, size_t, hipStream_t);                        \

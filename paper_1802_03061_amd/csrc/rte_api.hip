@@ -627,7 +627,7 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
                        (!use_pc || (size_t)pc_update_pool_blocks(c) <= (size_t)(m + 3) * RTE_KRYLOV_NBLK);
     const bool rescale_net = fused && use_pc && pc_rescale_net_ok(c);
     const bool early_a = rescale_net && early_a_ok(c);
-    // the plain form: Arnoldi on K with lazy factors, the update fused with the next pass A
+    // the plain form: lazy factors, the update fused with the next pass A
     const bool lazy = fused && !use_pc;
     // tolerance on |v_{j+1}|^2 - 1 beyond which the stored vector is rescaled; RTE_RENORM_TOL
     // overrides it (a negative value rescales at every step, which tests use)
@@ -708,9 +708,8 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
             at.flags = dfl;
             if (lazy) {
                 // stage 1 of the last column runs beside this column's dots
-                krylov_dots(V, n, j + 1, w, n, c->partial, sd, true, st, nullptr, j > 0 ? &prev : nullptr, c->partial_u,
-                            prev_nblk);
-                at.of_k = 1;
+                krylov_dots(V, n, j + 1, w, n, c->partial, sd, true, st, nullptr, true, j > 0 ? &prev : nullptr,
+                            c->partial_u, prev_nblk);
                 at.renorm_tol = -1.0;   // H[j+1, j] and inv[j+1] from the exact norm
                 if ((rc = update_a(c, w, V, n, at, nb, &prev_nblk))) return rc;
                 at.stage = 1;
