@@ -125,21 +125,30 @@ template <bool FULL>
 __device__ __forceinline__ void chunk_dots(const KryProb& k, const Chunk& c, int j, double* red) {
     const size_t ld = k.nvec;
     const double* v = k.V + c.off;
-    double wv[CPT];
-    chunk_load<FULL>(wv, v + (j + 1) * ld, c.len);
+    double wv[CPT], s = 0.0;
+    {   // A v_j = sc[j] V_j - w, and its product with V_j
+        const double f = k.sc[j];
+        double vj[CPT];
+        chunk_load<FULL>(wv, v + (j + 1) * ld, c.len);
+        chunk_load<FULL>(vj, v + j * ld, c.len);
 #pragma unroll
-    for (int u = 0; u < CPT; ++u)
-        if (!FULL && (int)(threadIdx.x + u * BT) >= c.len) wv[u] = 0.0;
+        for (int u = 0; u < CPT; ++u) {
+            wv[u] = FULL || (int)(threadIdx.x + u * BT) < c.len ? f * vj[u] - wv[u] : 0.0;
+            s += vj[u] * wv[u];
+        }
+    }
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[j * 4 + (threadIdx.x >> 6)] = s;
     int i = 0;
     if constexpr (FULL) {
 #pragma unroll 1
-        for (; i + KG <= j + 1; i += KG) chunk_dots<FULL, KG>(v, ld, c.len, wv, i, red);
+        for (; i + KG <= j; i += KG) chunk_dots<FULL, KG>(v, ld, c.len, wv, i, red);
     }
 #pragma unroll 1
-    for (; i <= j; ++i) chunk_dots<FULL, 1>(v, ld, c.len, wv, i, red);
+    for (; i < j; ++i) chunk_dots<FULL, 1>(v, ld, c.len, wv, i, red);
 }
 
-// partial[chunk][i] = <V_i, w> over the chunk for i <= j, w = V_{j+1} (the new apply output).
+// partial[chunk][i] = <V_i, A v_j> over the chunk for i <= j; w = K v_j = V_{j+1} is the new apply output.
 __global__ __launch_bounds__(BT) void kb_dots(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
                                               const int* __restrict__ act, const int* __restrict__ dj,
                                               double* __restrict__ partial, int m) {
@@ -155,7 +164,7 @@ __global__ __launch_bounds__(BT) void kb_dots(const Chunk* __restrict__ ch, cons
         partial[(size_t)blockIdx.x * (m + 1) + i] = (red[i * 4] + red[i * 4 + 1]) + (red[i * 4 + 2] + red[i * 4 + 3]);
 }
 
-// H[0..j][j] = <v_i, K v_j>: sc[i] times the sum over the problem's chunks (in chunk order); one
+// H[0..j][j] = <v_i, A v_j>: sc[i] times the sum over the problem's chunks (in chunk order); one
 // block per problem.
 __global__ __launch_bounds__(64) void kb_hcol(const KryProb* __restrict__ kp, const int* __restrict__ act,
                                               const int* __restrict__ dj, const double* __restrict__ partial, int m) {
@@ -190,6 +199,8 @@ __device__ __forceinline__ double chunk_update(const KryProb& k, const Chunk& c,
     double* w = k.V + c.off + (j + 1) * ld;
     double wv[CPT];
     chunk_load<FULL>(wv, w, c.len);
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) wv[u] = -wv[u];
     int i = 0;
     if constexpr (FULL) {
 #pragma unroll 1
@@ -209,7 +220,7 @@ __device__ __forceinline__ double chunk_update(const KryProb& k, const Chunk& c,
     return s;
 }
 
-// w -= sum_i H[i][j] sc[i] V_i over the chunk; part2[chunk] = |w|^2 over the chunk afterwards.  The chunks are
+// w = sc[j] V_j - w - sum_i H[i][j] sc[i] V_i over the chunk; part2[chunk] = its |w|^2 afterwards.  The chunks are
 // taken backwards: the last ones the dots read are still in the memory-side cache (137 against 149 us).
 __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, const KryProb* __restrict__ kp,
                                                 const int* __restrict__ act, const int* __restrict__ dj,
@@ -222,7 +233,7 @@ __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, co
     const KryProb& k = kp[c.p];
     const int j = *dj;
     const int tid = threadIdx.x;
-    for (int i = tid; i <= j; i += BT) h[i] = k.H[(size_t)j * (m + 1) + i] * k.sc[i];
+    for (int i = tid; i <= j; i += BT) h[i] = (k.H[(size_t)j * (m + 1) + i] - (i == j ? 1.0 : 0.0)) * k.sc[i];
     __syncthreads();
     double s = c.len == CHUNK ? chunk_update<true>(k, c, j, h) : chunk_update<false>(k, c, j, h);
     s = wave_sum(s);
@@ -231,9 +242,9 @@ __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, co
     if (tid == 0) part2[blk] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// The basis spans the Krylov space of K, A = I - K: A v_j = v_j - K v_j, so column j of A's Hessenberg
-// matrix is e_j - H[.][j] with -|w| below, and the applies need not read their input again.  The basis
-// vectors are stored as the update leaves them, with their factors 1/|w| in sc: pass A, the dots, the
+// The applies write K v_j alone and need not read their input again: A = I - K, and the dots and the
+// update, which read v_j anyway, take A v_j = v_j - K v_j.  (Not K v_j itself: in diffusive media it is
+// nearly v_j, and the basis loses its orthogonality.)  The basis vectors are stored as the update leaves them, with their factors 1/|w| in sc: pass A, the dots, the
 // update and the combination multiply by those, and no pass over w normalises it.  (128 problems of
 // 64^2 to 512^2: the normalising pass took 31 us of a step of all problems, the second read 17 us.)
 //
@@ -261,9 +272,7 @@ __global__ __launch_bounds__(64) void kb_givens(const KryProb* __restrict__ kp, 
     BState& s = bs[p];
     w2 = w2 > 0.0 ? w2 : 0.0;
     const double hn = sqrt(w2);
-    for (int i = 0; i < j; ++i) Hj[i] = -Hj[i];
-    Hj[j] = 1.0 - Hj[j];
-    Hj[j + 1] = -hn;
+    Hj[j + 1] = hn;
     for (int i = 0; i < j; ++i) {
         const double t = k.cs[i] * Hj[i] + k.sn[i] * Hj[i + 1];
         Hj[i + 1] = -k.sn[i] * Hj[i] + k.cs[i] * Hj[i + 1];
