@@ -3,13 +3,18 @@
 //
 // Such a vector is two real fields p + i q, whose channels the apply handles as two batch entries
 // (channels as in apply2d.hip).  Channel by channel the two are the real and imaginary part of
-//     z_0 = u_0,   z_{2k-1} = (u_k + u_-k)/sqrt2,   z_{2k} = -i (u_k - u_-k)/sqrt2,
-// so one complex x-transform of a row of z_c carries that row of both entries (where the channel form
-// puts two rows of one real channel into it), and the same unpacking gives their spectra.  Inverse:
-// u_{+-k} = (z_{2k-1} +- i z_{2k})/sqrt2.  The modes are read and written once, in the passes themselves;
-// separate conversions to channels and back were two launches and 4 (2L+1) real vectors of traffic.
+//     z_0 = u_0,   z_{2k-1} = (u_k + u_-k)/sqrt2,   z_{2k} = -i (u_k - u_-k)/sqrt2.
+// Inverse: u_{+-k} = (z_{2k-1} +- i z_{2k})/sqrt2.  The modes are read and written once, in the passes
+// themselves; separate conversions to channels and back were two launches and 4 (2L+1) real vectors of
+// traffic.
 //
-// A block takes R rows of one mode pair (k, -k), 2R transforms (k = 0: R); without PAIR (3D, where every
+// A complex x-transform carries two rows y, y + 1 of one real field, as in the channel form, never p
+// and q together: each keeps its own accuracy however far apart they are, and a real flux
+// (conjugate-symmetric modes, q = 0) comes back exactly real.  The modes hold p and q of a row side by
+// side, so neighbouring lanes take the rows y and y + 1 and exchange halves (swap_pair): the even lane
+// goes on with both rows of p, the odd one with both rows of q, and back on the way out.
+//
+// A block takes R rows (even) of one mode pair (k, -k), 2R transforms (k = 0: R); without PAIR (3D, where every
 // mode is a channel) R rows of one slab.  Bound: latency at small grids, HBM at large ones.  Applies
 // with conversions and without, us: FP32 200x150, L = 2 32.7 and 24.0;
 // 16^2, L = 7 25.6 and 12.8; 512^2, L = 2 63.8 and 49.3; FP64 512^2, L = 0 40.8 and 29.3;
@@ -21,6 +26,29 @@
 namespace rte {
 
 constexpr double kHalfSqrt2 = 0.70710678118654752440084436210485;
+
+// The value of the neighbouring lane (2i <-> 2i + 1); both must be active.
+__device__ __forceinline__ int swap_pair(int v) { return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true); }
+__device__ __forceinline__ float swap_pair(float v) { return __int_as_float(swap_pair(__float_as_int(v))); }
+__device__ __forceinline__ double swap_pair(double v) {
+    return __hiloint2double(swap_pair(__double2hiint(v)), swap_pair(__double2loint(v)));
+}
+template <typename T>
+__device__ __forceinline__ cx<T> swap_pair(cx<T> v) { return mk(swap_pair(v.re), swap_pair(v.im)); }
+// (za + zb)/sqrt2, or u minus it (of_a).  No fused multiply-adds: modes k and -k then round alike, and
+// conjugate inputs give exactly conjugate outputs.
+__device__ __forceinline__ cx<double> join_pair(cx<double> za, cx<double> zb, bool of_a, cx<double> u) {
+#pragma clang fp contract(off)
+    const double re = kHalfSqrt2 * (za.re + zb.re), im = kHalfSqrt2 * (za.im + zb.im);
+    return of_a ? mk(u.re - re, u.im - im) : mk(re, im);
+}
+// Own (p, q) of the lane's row to (row y, row y + 1) of its part, and the reverse (the same exchange).
+template <typename E>
+__device__ __forceinline__ void exchange(E& first, E& second, int part) {
+    const E got = swap_pair(part ? first : second);
+    if (part) first = got;
+    else second = got;
+}
 
 template <typename T, int PX, int R, int NTHR, bool PAIR>
 __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restrict__ u, cx<T>* __restrict__ Tb,
@@ -39,7 +67,7 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
     cx<double> p[IT][R0 / 2], m[IT][R0 / 2];   // every load before the first use, clamped instead of guarded
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const int idx = tid + it * NTHR, row = idx / NB0, j = idx % NB0, y = y0 + row;
+        const int idx = tid + it * NTHR, j = (idx >> 1) % NB0, y = y0 + 2 * ((idx >> 1) / NB0) + (idx & 1);
 #pragma unroll
         for (int r = 0; r < R0 / 2; ++r) {
             const int x = j + r * NB0;
@@ -51,7 +79,8 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
     const double s = sc.s[k ? 2 * k : 0] * (k ? kHalfSqrt2 : 1.0);
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
-        const int idx = tid + it * NTHR, row = idx / NB0, j = idx % NB0, y = y0 + row;
+        const int idx = tid + it * NTHR, part = idx & 1, j = (idx >> 1) % NB0, rp = (idx >> 1) / NB0;
+        const int y = y0 + 2 * rp + part, row = part * (R / 2) + rp;   // row: of the transforms in buf
         if (NBT % NTHR == 0 || idx < NBT) {
             cx<T> a[R0], b[R0];
 #pragma unroll
@@ -61,6 +90,10 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
                 const cx<double> za = k ? vp + vm : vp, zb = mul_mi(vp - vm);
                 a[r] = ok ? mk((T)(s * za.re), (T)(s * za.im)) : mk((T)0, (T)0);
                 b[r] = ok ? mk((T)(s * zb.re), (T)(s * zb.im)) : mk((T)0, (T)0);
+                if (r < R0 / 2) {
+                    exchange(a[r].re, a[r].im, part);
+                    if (PAIR) exchange(b[r].re, b[r].im, part);
+                }
             }
             dft_small<T, R0, false>(a);
             if (PAIR) dft_small<T, R0, false>(b);
@@ -80,9 +113,9 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
     const int nf = NKS * R;
     for (int idx = tid; idx < (k ? 2 * nf : nf); idx += NTHR) {
         const int row = idx % R, half = idx >= nf ? 1 : 0, kx = (idx - half * nf) / R, y = y0 + row;
-        if (y >= ny) continue;
-        const cx<T>* b = buf + (half * R + row) * LD;
-        cx<T> P, Q;
+        const int part = row & 1;
+        const cx<T>* b = buf + (half * R + part * (R / 2) + row / 2) * LD;
+        cx<T> P, Q;   // rows y and y + 1 of the part, then p and q of the row
         if (pack && kx == 0) {   // (X[0], X[PX/2])
             const cx<T> z0 = b[sw(0)], zh = b[sw(H)];
             P = mk(z0.re, zh.re);
@@ -92,6 +125,8 @@ __global__ __launch_bounds__(NTHR) void k_pass_a_modes(const cx<double>* __restr
             P = scale(z + zc, (T)0.5);
             Q = scale(mul_mi(z - zc), (T)0.5);
         }
+        exchange(P, Q, part);
+        if (y >= ny) continue;
         cx<T>* out = Tb + (size_t)(PAIR ? (k ? 2 * k - 1 + half : 0) : blockIdx.y) * chan + (size_t)kx * ny + y;
         out[0] = P;
         out[entry] = Q;
@@ -127,8 +162,10 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
             const int idx = i0 + q * NTHR, row = idx % R, half = idx >= nf ? 1 : 0, kx = (idx - half * nf) / R;
             if (idx >= nl) continue;
             const bool in = y0 + row < ny;
+            const int part = row & 1;
             cx<T> P = in ? xa[q] : mk((T)0, (T)0), Q = in ? xb[q] : mk((T)0, (T)0);
-            cx<T>* b = buf + (half * R + row) * LD;
+            exchange(P, Q, part);
+            cx<T>* b = buf + (half * R + part * (R / 2) + row / 2) * LD;
             if (pack && kx == 0) {
                 b[sw(0)] = mk(P.re, Q.re);
                 b[sw(H)] = mk(P.im, Q.im);
@@ -149,7 +186,8 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
     cx<double>* vp = v + (size_t)(PAIR ? L + k : blockIdx.y) * N;
     cx<double>* vm = v + (size_t)(PAIR ? L - k : blockIdx.y) * N;
     for (int idx = tid; idx < R * NSL; idx += NTHR) {
-        const int row = idx / NSL, j = idx % NSL, y = y0 + row;
+        const int part = idx & 1, j = (idx >> 1) % NSL, rp = (idx >> 1) / NSL;
+        const int y = y0 + 2 * rp + part, row = part * (R / 2) + rp;
         cx<double> p[RL / 2], m[RL / 2];
         if (mode == APPLY_A) {
 #pragma unroll
@@ -176,6 +214,11 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
         }
         dft_small<T, RL, true>(a);
         if (k) dft_small<T, RL, true>(b);
+#pragma unroll
+        for (int r = 0; r < RL / 2; ++r) {
+            exchange(a[r].re, a[r].im, part);
+            if (k) exchange(b[r].re, b[r].im, part);
+        }
         if (y >= ny) continue;
 #pragma unroll
         for (int r = 0; r < RL / 2; ++r) {
@@ -183,18 +226,19 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
             if (x >= nx) continue;
             const size_t o = (size_t)y * nx + x;
             const cx<double> za = cvt<double>(a[r]), zb = mul_i(cvt<double>(b[r]));
-            const cx<double> yp = k ? scale(za + zb, kHalfSqrt2) : za;
-            vp[o] = mode == APPLY_A ? p[r] - yp : yp;
+            const bool of_a = mode == APPLY_A;
             if (k) {
-                const cx<double> ym = scale(za - zb, kHalfSqrt2);
-                vm[o] = mode == APPLY_A ? m[r] - ym : ym;
+                vp[o] = join_pair(za, zb, of_a, p[r]);
+                vm[o] = join_pair(za, mk(-zb.re, -zb.im), of_a, m[r]);
+            } else {
+                vp[o] = of_a ? p[r] - za : za;
             }
         }
     }
 }
 
 // ---------------------------------------------------------------------------- dispatch -------
-// Rows per block: 2R transforms in at most 70 KB (two blocks per CU), at most 8 rows (64 bytes of a
+// Rows per block (pairs): 2R transforms in at most 70 KB (two blocks per CU), at most 8 rows (64 bytes of a
 // spectrum column in FP32), and half of that where the grid would not give every CU a block.  Whole
 // applies in FP32 with R and R/2 rows: 200x150, L = 2 (57 blocks of R) 30.1 and 24.0 us; 512^2, L = 0 (128)
 // 23.2 and 20.6; 256^2, L = 4 (160) 34.2 and 29.5; 300x257, L = 3 (260) 58.2 and 65.3; 400x300, L = 8
@@ -202,7 +246,7 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
 template <typename T, int PX>
 constexpr int mode_rows() {
     int r = 8;
-    while (r > 1 && 2L * r * (padded(PX) + 1) * (long)sizeof(cx<T>) > 70 * 1024) r /= 2;
+    while (r > 2 && 2L * r * (padded(PX) + 1) * (long)sizeof(cx<T>) > 70 * 1024) r /= 2;
     return r;
 }
 template <typename T, int PX, int R, bool PAIR>
@@ -219,7 +263,7 @@ static void launch_modes_r(const Apply2DArgs<T>& a, int pass, const cx<double>* 
 template <typename T, int PX>
 static int launch_modes(const Apply2DArgs<T>& a, int pass, const cx<double>* u, cx<double>* v, int mode,
                         const ChanScale& sc, int singles) {
-    constexpr int R = mode_rows<T, PX>(), RH = R > 1 ? R / 2 : 1;
+    constexpr int R = mode_rows<T, PX>(), RH = R > 2 ? R / 2 : 2;
     const int ngroups = singles ? singles : a.L + 1;
     const bool few = (long)((a.ny + R - 1) / R) * ngroups < 256;
     if (singles) {
