@@ -340,32 +340,39 @@ static void launch_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, 
     launch_a_tr<T, PX, TR>(a, x, sc, nchan_total);
 }
 
-template <typename T, int PX, int TR, typename TV>
+template <typename T, int PX, int TR, int NTHR, typename TV>
 static void launch_ua_tr(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
                          const ChanScale& sc, int nchan_total, int* nblk) {
-    if constexpr (TR > 2 && PassATile<PX, TR, 256>::IT > 1) {
-        launch_ua_tr<T, PX, TR / 2>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+    if constexpr (TR > 2 && PassATile<PX, TR, NTHR>::IT > 1) {
+        launch_ua_tr<T, PX, TR / 2, NTHR>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
     } else {
         dim3 grid((a.ny + TR - 1) / TR, nchan_total);
         *nblk = (int)(grid.x * grid.y);
-        hipLaunchKernelGGL((k_update_a<T, PX, TR, 256, TV>), grid, dim3(256), 0, a.stream, w, V, ld, t, partial, a.work,
+        hipLaunchKernelGGL((k_update_a<T, PX, TR, NTHR, TV>), grid, dim3(NTHR), 0, a.stream, w, V, ld, t, partial, a.work,
                            a.twx, a.nx, a.ny, a.C, sc, a.pack);
     }
 }
-// The row tile of pass A (the tuner's), but at most one butterfly per thread: the update holds a thread's
-// inputs of several basis vectors.  Solves in FP32 with tiles of 4, 8, 16 and 32 rows: 512^2, L = 8 5.96,
-// 5.92, 6.66 and 14.4 ms; 512^2, L = 0 1.49, 1.53, 1.80, 5.65; 256^2, L = 4 1.62, 1.63, 1.68, 1.92; where
-// rows are short the tiles that pass A's stores want are better: 64^3 to degree 2 7.1, 5.4, 4.9, 4.6.
+// Padded x >= 256: the row tile of pass A (the tuner's), but at most one butterfly per thread: the update
+// holds a thread's inputs of several basis vectors.  Solves in FP32 with tiles of 4, 8, 16 and 32 rows:
+// 512^2, L = 8 5.96, 5.92, 6.66 and 14.4 ms; 512^2, L = 0 1.49, 1.53, 1.80, 5.65; 256^2, L = 4 1.62, 1.63,
+// 1.68, 1.92.
+// Shorter rows have 8 butterflies each (one at 16), so that those tiles leave most of 256 threads without
+// an element and too few loads in flight: there 16 rows by one wave, a butterfly per lane.  Solves with
+// pass A's tile and with these, ms: FP64 64^3 to degree 2 7.40 and 6.42, 32^3 to degree 2 1.76 and 1.50,
+// 64^3 1.72 and 1.59; FP32 64^3 to degree 2 4.77 and 4.51, 64^2, L = 4 1.03 and
+// 0.97.  32 rows by two waves 6.44, 1.53, 1.60; 4.57, 1.05.
 template <typename T, int PX, typename TV>
 static void launch_ua(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,
                       const ChanScale& sc, int nchan_total, int* nblk) {
     constexpr int TR = tile_rows<T>();
-    if constexpr (PX >= 128) {
-        if (a.var[0] == 1) return launch_ua_tr<T, PX, TR / 2>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
-        if (a.var[0] == 2) return launch_ua_tr<T, PX, TR * 2>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
-        if (a.var[0] == 3) return launch_ua_tr<T, PX, TR / 4>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+    if constexpr (PX <= 128) {
+        launch_ua_tr<T, PX, 16, 64>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+    } else {
+        if (a.var[0] == 1) launch_ua_tr<T, PX, TR / 2, 256>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+        else if (a.var[0] == 2) launch_ua_tr<T, PX, TR * 2, 256>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+        else if (a.var[0] == 3) launch_ua_tr<T, PX, TR / 4, 256>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
+        else launch_ua_tr<T, PX, TR, 256>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
     }
-    launch_ua_tr<T, PX, TR>(a, w, V, ld, t, partial, sc, nchan_total, nblk);
 }
 template <typename T, int PX, int TR, typename TV>
 static void launch_c_tr(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
