@@ -1262,12 +1262,13 @@ __global__ void k_sub(const double* __restrict__ a, const double* __restrict__ b
 }
 
 // ------------------------------------------------------------------ host dispatch ------------
+static bool conv_narrow(int W) { return W <= 16; }   // 16-pixel rows, two to a wave
+static int conv_blocks(int B, int H, int W) { return conv_narrow(W) ? B * ((H + 7) / 8) : B * ((H + 3) / 4) * ((W + 31) / 32); }
 static int conv_launch(int Cin, const float* in, const unsigned short* Wp, const float* bias, int Cout, float* out,
                        const float* mask, bool relu, const float* in_scale, int B, int H, int W,
                        hipStream_t st) {
-    const bool narrow = W <= 16;   // 16-pixel rows, two to a wave
-    const int tiles = narrow ? B * ((H + 7) / 8) : B * ((H + 3) / 4) * ((W + 31) / 32);
-    dim3 g(tiles), blk(256);
+    const bool narrow = conv_narrow(W);
+    dim3 g(conv_blocks(B, H, W)), blk(256);
     switch (Cin) {
 #define RTE_CV(CI)                                                                                                   \
     case CI:                                                                                                         \
@@ -1427,8 +1428,23 @@ static int ensure_acts(rte_nn* nn, size_t per_tensor, int B) {
     return RTE_OK;
 }
 
-// One launch for all layers where an image's activations fit LDS twice (up to about 28^2).
+// Whether one launch takes all layers (k_net_chain) or each layer has its own.  The chain's limit is LDS,
+// an image's activations twice (up to about 28^2); its time grows with the 32-pixel tiles of an image, which
+// CHAIN_WAVES waves share, while layers of their own spread an image over more blocks, and are
+// bound by latency until they fill the chip.  Forward passes of 1 to 32 images (17 channels, 32 hidden, 5
+// layers), us in one launch and layer by layer: 16^2 (8 tiles) 40 and 55, 18^2 (11) 57 and 58-61, 20^2 (13)
+// 65 and 58-61, 24^2 (18) 81 and 58-61, 28^2 (25) 104 and 59-62.  With more blocks than CUs per layer the
+// chain is ahead again: 96 images of 20^2 65 and 70, 160 67 and 112; 96 of 24^2 81 and 81, 160 81 and 113.
+// The data gradients, whose weight gradients follow in one launch either way, are behind from the second
+// round on.  Loss and gradient of 32 images with every image up to 28^2 chained and by these rules:
+// 18^2 202 and 187, 20^2 215 and 174, 24^2 273 and 179, 28^2 338 and 190 (16^2, chained in both: 122).
+static int chain_tiles(int H, int W) { return (H * W + 31) / 32; }
 static bool chain_fits(int H, int W) { return chain_lds(H, W) <= 156 * 1024; }
+static bool chain_forward(int B, int H, int W) {
+    const int tiles = chain_tiles(H, W), rounds = (tiles + CHAIN_WAVES - 1) / CHAIN_WAVES;
+    return chain_fits(H, W) && (tiles <= CHAIN_WAVES + CHAIN_WAVES / 2 || conv_blocks(B, H, W) > 256 * (rounds - 1));
+}
+static bool chain_backward(int H, int W) { return chain_fits(H, W) && chain_tiles(H, W) <= CHAIN_WAVES; }
 static void chain_launch(const ChainArgs& a, int B, int H, int W, hipStream_t st) {
     const int nw = std::min(CHAIN_WAVES, std::max(4, (H * W + 31) / 32));   // one wave per tile
     hipLaunchKernelGGL(k_net_chain, dim3(B), dim3(64 * nw), chain_lds(H, W), st, a, H, W);
@@ -1438,7 +1454,7 @@ static void chain_launch(const ChainArgs& a, int B, int H, int W, hipStream_t st
 static int net_forward(const NetShape& sh, const unsigned short* wf, const float* params_bias_base,
                        const std::vector<size_t>& boff, const float* x, float* const* act, bool keep, int B,
                        int H, int W, hipStream_t st) {
-    if (chain_fits(H, W)) {
+    if (chain_forward(B, H, W)) {
         ChainArgs c{};
         c.in = x;
         c.layers = sh.layers;
@@ -1998,7 +2014,7 @@ int rte_nn_loss_grad(rte_nn* nn, const float* x, const float* t, const float* w,
     };
     // backward: gy[l] holds dLoss/d(output of layer l); a data gradient is masked by the ReLU of the
     // layer before (its output is positive where its pre-activation is)
-    const bool chain = together && L > 1 && chain_fits(H, W);
+    const bool chain = together && L > 1 && chain_backward(H, W);
     if (chain) {
         ChainArgs c{};
         c.in = wa.gy[L - 1];
