@@ -24,8 +24,8 @@ Other workloads (same JSON shape):
            throughout, tol 1e-10 (latency-bound)
   sh3d     one step = one solve of the 3D anisotropic problem in real spherical harmonics to
            degree 2 (9 modes), 64^3, HG g = 0.5, mu_a = 0.05, mu_s = 10, tol 1e-8
-  modes    one step = one solve of a 2D problem with many modes (L = 16, 33 modes; the split
-           pass B with the mode-axis FFT or the direct coupling, as tuned), 256^2, HG g = 0.9,
+  modes    one step = one solve of a 2D problem with many modes (L = 16, 33 modes; pass B in one
+           kernel in the FP32 apply, in split form in the FP64 one), 256^2, HG g = 0.9,
            mu_a = 0.05, mu_s = 10, tol 1e-8
   multi    one step = one rte_solve_multi call for 16 sources sharing one 256^2, L = 4 medium
            (HG g = 0.5, mu_a = 0.1, mu_s = 10), tol 1e-8 per source; value counts sources solved
@@ -57,8 +57,8 @@ METRIC = "solve time to rel-res 1e-8 (512^2, L=8 HG), learned-PC vs plain; appli
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "hbm_traffic_hg512_L8.json")
 # sources of the 2D apply kernels: counter readings are only reported while these are unchanged
 APPLY_SOURCES = ["paper_1802_03061_amd/csrc/" + f for f in
-                 ("apply2d.hip", "apply2d_b.hip", "apply2d.h", "apply2d_b.h", "apply2d_tile.h", "passb_split.h", "fft.h",
-                  "common.h")]
+                 ("apply2d.hip", "apply2d_b.hip", "apply2d.h", "apply2d_b.h", "apply2d_tile.h", "passb_wave.h",
+                  "fft_wave.h", "fft.h", "common.h")]
 
 
 def sources_digest() -> str:

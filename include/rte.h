@@ -232,8 +232,9 @@ int rte_solve_batched(int count, rte_ctx* const* ctxs, const double* const* f_de
  * the FP32 apply (padded x 128..1024) each Arnoldi step runs the next apply's x-transforms beside
  * the network and adds the correction's x-spectrum in the y-pass instead (the same z up to FP32
  * rounding); environment RTE_PC_EARLY_A=0 keeps the correction in the x-pass.  Environment
- * RTE_RENORM_TOL overrides the tolerance on |v_{j+1}|^2 - 1 beyond which a solve rescales the new
- * Krylov vector (default 1e-8 with the FP32 apply, 1e-10 with FP64; negative: every step). */
+ * RTE_RENORM_TOL overrides the tolerance on |v_{j+1}|^2 - 1 beyond which a solve with a preconditioner
+ * (also after it has been dropped) rescales the new Krylov vector (default 1e-8 with the FP32 apply,
+ * 1e-10 with FP64; negative: every step); plain solves carry the exact norms and rescale nothing. */
 int rte_pc_attach(rte_ctx* ctx, const float* weights_dev, int hidden, int layers, int factor);
 
 /* Time `reps` back-to-back applies (op, RTE_LAYOUT_CHANNELS, prec) on the context stream with
@@ -275,13 +276,14 @@ int rte_set_batched_variant(int pass, int variant);
  * 1 = B, 2 = C; 3D: pass 0 = A (x-FFT), 1 = B (y-FFT), 2 = C (z-FFT with the spectrum or the mode
  * coupling), 3 = D (inverse y-FFT), 4 = E (inverse x-FFT).  Variants differ only in tiling (row
  * tiles, z-rows or columns per block, the coupling method for more than 17 modes): the
- * same arithmetic, equal results up to rounding.  Pass B with up to 17 modes in 2D has one kernel per
- * shape, which every variant number of its range selects.  rte_setup of a 2D
+ * same arithmetic, equal results up to rounding.  Pass B in 2D with up to 17 modes, and in FP32 with up to
+ * 33 at padded y <= 512, has one kernel per shape, which every variant number of its range selects.
+ * rte_setup of a 2D
  * context with n_x or n_y >= 128, or of a 3D context with a side >= 64, picks the fastest variant of
  * every pass by timing them on the context's buffers, once per (precision, L, grid) per process
  * (environment RTE_AUTOTUNE=0: keep variant 0).  rte_autotune re-times them (`reps` launches each;
  * synchronises the stream); rte_set_variant forces one (RTE_EINVAL if the pass or variant is out of
- * range); rte_get_variant reports the current one and how many exist. */
+ * range); rte_get_variant reports the current one and how many numbers are taken. */
 int rte_autotune(rte_ctx* ctx, int reps);
 int rte_set_variant(rte_ctx* ctx, int prec, int pass, int variant);
 int rte_get_variant(const rte_ctx* ctx, int prec, int pass, int* variant, int* count);

@@ -353,9 +353,11 @@ static void launch_ua_tr(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld,
     }
 }
 // Padded x >= 256: the row tile of pass A (the tuner's), but at most one butterfly per thread: the update
-// holds a thread's inputs of several basis vectors.  Solves in FP32 with tiles of 4, 8, 16 and 32 rows:
-// 512^2, L = 8 5.96, 5.92, 6.66 and 14.4 ms; 512^2, L = 0 1.49, 1.53, 1.80, 5.65; 256^2, L = 4 1.62, 1.63,
-// 1.68, 1.92.
+// holds a thread's inputs of several basis vectors (with two and four, 16 and 32 rows at padded x = 1024, a
+// solve of 29 iterations at 512^2, L = 8 in FP32 took 6.66 and 14.4 ms instead of 5.92).  What the tiles
+// below that differ by, solves to 1e-10 in ms: FP32, 4 and 8 rows, 512^2, L = 8 6.59 and 6.54, 512^2, L = 0
+// 1.36 and 1.41, 256^2, L = 4 1.67 and 1.67; FP64, 2, 4 and 8 rows, 512^2, L = 8 10.43, 9.26 and 9.40, 256^2,
+// L = 4 1.86, 1.72 and 1.75 (pass A's choice: 4 rows).
 // Shorter rows have 8 butterflies each (one at 16), so that those tiles leave most of 256 threads without
 // an element and too few loads in flight: there 16 rows by one wave, a butterfly per lane.  Solves with
 // pass A's tile and with these, ms: FP64 64^3 to degree 2 7.40 and 6.42, 32^3 to degree 2 1.76 and 1.50,
@@ -405,20 +407,12 @@ static void launch_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* 
         default: return -1;                       \
     }
 
-// Pass-B variant numbers that rte_set_variant takes for L <= 8: those of the tilings that existed
-// before the wave-private form replaced them all (default, 1024 and 256 threads, register-resident,
-// radix 32, one FFT group; in FP64 beyond LDS: split, halves, fused inverse), which now select it.
+// How many pass-B variant numbers rte_set_variant takes for L <= 8.  One kernel serves each shape; the
+// numbers are kept so that programs which set one go on working.
 static int pass_b_numbers(bool f64, int L, int PY) {
-    const int C = 2 * L + 1, ncol = C >= 4 ? 1 : (C == 3 ? 2 : 4), nf = ncol * C, n8 = nf * PY / 8;
-    const int nthr = n8 >= 512 ? 512 : (n8 >= 256 ? 256 : (n8 >= 128 ? 128 : 64));
-    const int group = std::max(1, std::min(nf, 3 * nthr * 8 / PY));
-    const long es = f64 ? 16 : 8, budget = 160 * 1024;
-    if ((nf * (long)padded(PY) + PY + 2 * C) * es <= budget && (!f64 || L <= 4)) {
-        const int base = PY < 128 ? 1 : (!f64 && L >= 2 ? 4 : (!f64 && n8 >= 1024 ? 3 : 2));
-        return base + (PY >= 256 ? 1 : 0) + (group < nf ? 1 : 0);
-    }
-    const bool half = PY >= 64 && (C * (long)padded(PY / 2) + PY / 2) * es <= budget;
-    return (half ? 2 : 1) + (L >= 1 ? 1 : 0);
+    if (f64 && L > 4) return PY < 64 ? 2 : 3;
+    if (PY < 128) return 1;
+    return (f64 || L < 2 ? 2 : 4) + (PY >= 256 ? 1 : 0) + (!f64 && L >= 6 && PY == 1024 ? 1 : 0);
 }
 template <typename T>
 int apply2d_variant_count(int pass, int L, int PX, int PY) {

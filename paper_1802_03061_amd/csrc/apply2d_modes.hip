@@ -16,9 +16,10 @@
 //
 // A block takes R rows (even) of one mode pair (k, -k), 2R transforms (k = 0: R); without PAIR (3D, where every
 // mode is a channel) R rows of one slab.  Bound: latency at small grids, HBM at large ones.  Applies
-// with conversions and without, us: FP32 200x150, L = 2 32.7 and 24.0;
-// 16^2, L = 7 25.6 and 12.8; 512^2, L = 2 63.8 and 49.3; FP64 512^2, L = 0 40.8 and 29.3;
-// 3D FP32 isotropic 32^3 33.7 and 24.9, 128^3 155 and 116, 64^3 to degree 2 177 and 155.
+// with conversions and with these passes, us: FP32 200x150, L = 2 33.0 and 24.5; 16^2, L = 7 25.3 and 14.7;
+// 512^2, L = 2 63.6 and 50.3; FP64 512^2, L = 0 40.4 and 28.2; 3D FP32 isotropic 32^3 35.8 and 31.9, 128^3
+// 154 and 119, 64^3 to degree 2 181 and 157.  (Without the exchange, p and q in one transform: 512^2, L = 2
+// 48.8, 128^3 117.)
 #include "apply2d.h"
 #include "apply2d_tile.h"
 #include "fft.h"
@@ -240,9 +241,9 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
 // ---------------------------------------------------------------------------- dispatch -------
 // Rows per block (pairs): 2R transforms in at most 70 KB (two blocks per CU), at most 8 rows (64 bytes of a
 // spectrum column in FP32), and half of that where the grid would not give every CU a block.  Whole
-// applies in FP32 with R and R/2 rows: 200x150, L = 2 (57 blocks of R) 30.1 and 24.0 us; 512^2, L = 0 (128)
-// 23.2 and 20.6; 256^2, L = 4 (160) 34.2 and 29.5; 300x257, L = 3 (260) 58.2 and 65.3; 400x300, L = 8
-// (675) 131 and 161.
+// applies in FP32 with R and R/2 rows: 200x150, L = 2 (57 blocks of R) 31.6 and 24.4 us; 512^2, L = 0 (128)
+// 24.2 and 21.1; 256^2, L = 4 (160) 35.7 and 30.0; 300x257, L = 3 (260) 59.9 and 65.7; 400x300, L = 8 (675)
+// 133 and 163.
 template <typename T, int PX>
 constexpr int mode_rows() {
     int r = 8;

@@ -143,8 +143,10 @@ static void launch_dots(int nv, unsigned nblk, hipStream_t st, const TV* V, size
 }
 
 // out[v] = sum_b partial[v * nblk + b] in a fixed order, v the block.
-__device__ __forceinline__ void reduce_row(const double* __restrict__ partial, int nblk, double* __restrict__ out,
-                                           double* sh) {
+__global__ __launch_bounds__(KT) void k_reduce_partials(const double* __restrict__ partial, int nblk,
+                                                        double* __restrict__ out, const int* __restrict__ active) {
+    __shared__ double sh[KT / 64];
+    if (active && *active == 0) return;
     const int v = blockIdx.x;
     const double* __restrict__ p = partial + (size_t)v * nblk;
     double s = 0.0;
@@ -156,12 +158,6 @@ __device__ __forceinline__ void reduce_row(const double* __restrict__ partial, i
     for (; b < nblk; b += KT) s += p[b];
     s = block_sum(s, sh);
     if (threadIdx.x == 0) out[v] = s;
-}
-__global__ __launch_bounds__(KT) void k_reduce_partials(const double* __restrict__ partial, int nblk,
-                                                        double* __restrict__ out, const int* __restrict__ active) {
-    __shared__ double sh[KT / 64];
-    if (active && *active == 0) return;
-    reduce_row(partial, nblk, out, sh);
 }
 
 // A thread's last index below n (n: none); a step of stride down from its first wraps to above n.

@@ -1,6 +1,6 @@
 // Pass B with wave-private y-FFTs and the mode coupling in real arithmetic.
 //
-// A block holds the spectra of NCOL columns x C channels in LDS, as the other fused form does, but
+// A block holds the spectra of NCOL columns x C channels in LDS, and
 // every sequence is transformed by one wave (or part of one) from its loads to its spectrum and
 // back, so a transform's stages are ordered by the wave alone and the block meets at two barriers
 // per column group: before and after the coupling.  Waves drift apart between them, and one wave's

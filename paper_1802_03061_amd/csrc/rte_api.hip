@@ -233,7 +233,7 @@ Apply2DArgs<double> args2d<double>(const rte_ctx* c) {
     return a;
 }
 
-// The arguments of the x-passes on nbatch channel vectors: nchan "channels" of them with factors sc.
+// The arguments of the x-passes on nbatch channel vectors: nb batch entries of them, with factors sc.
 // In 3D every z-slab of every channel of every batch entry counts as one channel of a 2D apply; the
 // factor of D is applied per channel when pass B loads it.
 template <typename T>
@@ -629,7 +629,8 @@ static int solve_core_t(rte_ctx* c, const double* b, double tol, int max_iter, d
     const bool early_a = rescale_net && early_a_ok(c);
     // the plain form: lazy factors, the update fused with the next pass A
     const bool lazy = fused && !use_pc;
-    // tolerance on |v_{j+1}|^2 - 1 beyond which the stored vector is rescaled; RTE_RENORM_TOL
+    // tolerance on |v_{j+1}|^2 - 1 beyond which a preconditioned step (and the step after the
+    // preconditioner has been dropped) rescales the stored vector; RTE_RENORM_TOL
     // overrides it (a negative value rescales at every step, which tests use)
     const char* renorm_env = std::getenv("RTE_RENORM_TOL");
     const double renorm_tol = renorm_env ? std::atof(renorm_env) : (mixed ? 1e-8 : 1e-10);

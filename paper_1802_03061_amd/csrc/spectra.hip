@@ -141,9 +141,10 @@ static void unit_root(int q, int S, double& cr, double& ci) {
     }
 }
 
-// The twiddle table of the length-P LDS FFT (fft.h), in its per-stage layout: for every Stockham stage after the first (sub-transform length NS, radix R), the factors
-// exp(-2 pi i k r / (NS R)) for k < NS, r = 1..R-1 at stage_tw_offset(P, NS) + k (R - 1) + (r - 1).  The angle is computed in long double from the exact integer fraction (k r mod NS R) / (NS R), rounded to FP64, with
-// the quarter points exact.
+// The twiddle table of the length-P LDS FFT (fft.h), in its per-stage layout: for every Stockham stage
+// after the first (sub-transform length NS, radix R), the factors exp(-2 pi i k r / (NS R)) for k < NS,
+// r = 1..R-1 at stage_tw_offset(P, NS) + k (R - 1) + (r - 1).  The angle is computed in long double from the
+// exact integer fraction (k r mod NS R) / (NS R), rounded to FP64, with the quarter points exact.
 void twiddles(int P, std::vector<double>& re, std::vector<double>& im) {
     re.assign(P, 0.0);
     im.assign(P, 0.0);
