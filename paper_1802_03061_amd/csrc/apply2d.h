@@ -137,6 +137,13 @@ bool apply2d_split(int L, int PY);
 // Whether pass B runs the y-transforms in two halves (twyh needed).
 template <typename T>
 bool apply2d_b_halves(int L, int PY);
+// Where pass B would run in halves, but on so few columns (over nbatch batch entries) that a block per
+// column leaves most CUs idle: it takes the split form too (pack = 0, work2; not for single_in, whose
+// halves are faster).  FP64 applies in halves and in split form, us: L = 5, 8x512 (8 columns) 37.1 and 23.5,
+// 16x512 (16) 34.8 and 22.9, 32x512 (32) 36.0 and 28.0, 64x512 (64) 39.9 and 37.1, 128x512 (128) 46.4 and 48.5;
+// L = 8 55.2 and 29.0, 50.3 and 27.0, 52.6 and 36.6, 58.0 and 43.0, 64.8 and 67.6.
+template <typename T>
+bool apply2d_few_columns(int L, int PX, int PY, int nbatch);
 template <typename T, typename TV>
 int apply2d_pass_c(const Apply2DArgs<T>& a, const TV* x, const double* b, TV* y, int mode,
                    int nbatch);

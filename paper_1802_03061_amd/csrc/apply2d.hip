@@ -443,6 +443,12 @@ bool apply2d_b_halves(int L, int PY) {
 }
 template bool apply2d_b_halves<float>(int, int);
 template bool apply2d_b_halves<double>(int, int);
+template <typename T>
+bool apply2d_few_columns(int L, int PX, int PY, int nbatch) {
+    return apply2d_b_halves<T>(L, PY) && (long)(PX / 2) * nbatch <= PASSB_FEW_COLUMNS;
+}
+template bool apply2d_few_columns<float>(int, int, int, int);
+template bool apply2d_few_columns<double>(int, int, int, int);
 
 template <typename T, typename TV>
 int apply2d_pass_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, int nbatch) {
@@ -451,6 +457,7 @@ int apply2d_pass_a(const Apply2DArgs<T>& a, const TV* x, const ChanScale& sc, in
 }
 template <typename T>
 int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch) {
+    if (!a.pack) return pass_b_large<T>(a, nbatch);
     switch (a.L) {
         case 0: return pass_b_L0<T>(a, nbatch);
         case 1: return pass_b_L1<T>(a, nbatch);
@@ -463,20 +470,18 @@ int apply2d_pass_b(const Apply2DArgs<T>& a, int nbatch) {
         case 8: return pass_b_L8<T>(a, nbatch);
     }
     if constexpr (sizeof(T) == 4) {
-        if (!apply2d_split<T>(a.L, a.PY)) {
-            switch (a.L) {
-                case 9: return pass_b_L9<T>(a, nbatch);
-                case 10: return pass_b_L10<T>(a, nbatch);
-                case 11: return pass_b_L11<T>(a, nbatch);
-                case 12: return pass_b_L12<T>(a, nbatch);
-                case 13: return pass_b_L13<T>(a, nbatch);
-                case 14: return pass_b_L14<T>(a, nbatch);
-                case 15: return pass_b_L15<T>(a, nbatch);
-                case 16: return pass_b_L16<T>(a, nbatch);
-            }
+        switch (a.L) {
+            case 9: return pass_b_L9<T>(a, nbatch);
+            case 10: return pass_b_L10<T>(a, nbatch);
+            case 11: return pass_b_L11<T>(a, nbatch);
+            case 12: return pass_b_L12<T>(a, nbatch);
+            case 13: return pass_b_L13<T>(a, nbatch);
+            case 14: return pass_b_L14<T>(a, nbatch);
+            case 15: return pass_b_L15<T>(a, nbatch);
+            case 16: return pass_b_L16<T>(a, nbatch);
         }
     }
-    return pass_b_large<T>(a, nbatch);
+    return -1;
 }
 template <typename T, typename TV>
 int apply2d_update_a(const Apply2DArgs<T>& a, TV* w, const TV* V, size_t ld, const ArnoldiArgs& t, double* partial,

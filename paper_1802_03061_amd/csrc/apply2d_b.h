@@ -11,12 +11,13 @@ RTE_DECL_PASSB(9) RTE_DECL_PASSB(10) RTE_DECL_PASSB(11) RTE_DECL_PASSB(12)     /
 RTE_DECL_PASSB(13) RTE_DECL_PASSB(14) RTE_DECL_PASSB(15) RTE_DECL_PASSB(16)
 #undef RTE_DECL_PASSB
 
-// Pass B in split form (apply2d_split: unpacked work buffer, work2 required; apply2d_bm.hip): variant 0
-// couples the modes by an FFT along the mode axis (twm: twiddles of length mode_fft_len(L)),
-// variant 1 by the direct Toeplitz sum.
+// Pass B in split form (apply2d_split, apply2d_few_columns: unpacked work buffer, work2 required;
+// apply2d_bm.hip).  More than 17 modes: variant 0 couples the modes by an FFT along the mode axis (twm:
+// twiddles of length mode_fft_len(L)), variant 1 by the direct Toeplitz sum.  Up to 17: k_couple_regs.
 constexpr int PASSB_FUSED_MAX_L = 8;      // in both precisions at every size
 constexpr int PASSB_FUSED_MAX_L_F32 = 16;  // in FP32 up to padded y = PASSB_FUSED_MAX_PY
 constexpr int PASSB_FUSED_MAX_PY = 512;
+constexpr int PASSB_FEW_COLUMNS = 64;      // FP64, 11 to 17 modes, padded y = 1024: apply2d_few_columns
 inline int mode_fft_len(int L) { int p = 1; while (p < 4 * L + 1) p <<= 1; return p; }
 template <typename T> int pass_b_large(const Apply2DArgs<T>& a, int nbatch);
 }  // namespace rte

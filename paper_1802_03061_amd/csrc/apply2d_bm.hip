@@ -1,4 +1,5 @@
-// Pass B of the 2D apply for many modes (L > 8, up to 2L+1 = 65 channels): the split form
+// Pass B of the 2D apply for many modes (L > 8, up to 2L+1 = 65 channels; 11 to 17 in FP64 on few
+// columns, with a coupling of their own, k_couple_regs): the split form
 // (forward y-FFT of every (channel, column) sequence to a full-length buffer, the mode coupling per
 // frequency, inverse y-FFT) with the coupling done by an FFT along the mode axis.
 //
@@ -18,6 +19,7 @@
 #include "apply2d_b.h"
 #include "fft.h"
 #include "passb_split.h"
+#include "passb_wave.h"
 
 #include <algorithm>
 
@@ -293,12 +295,58 @@ static void launch_modefft(const Apply2DArgs<T>& a, int nbatch, int PY, int nkx,
                        PY, a.L, a.single_in);
 }
 
+// 11 to 17 modes in FP64 on few columns (apply2d_few_columns): a frequency per thread, its channels in
+// registers and the coupling in real arithmetic (passb_wave.h), with the kernel table as the halves keep
+// it.  Bound: latency (at most 65 columns of 16 waves).
+template <typename T, int PY, int L>
+__global__ __launch_bounds__(64) void k_couple_regs(cx<T>* __restrict__ T2, const cx<T>* __restrict__ Q, int nkx,
+                                                    int nkq) {
+    constexpr int C = 2 * L + 1, KH = PY / 2 + 1;
+    const int f = blockIdx.x * 64 + threadIdx.x, kx = blockIdx.y;
+    const size_t cstride = (size_t)nkx * PY;
+    cx<T>* p = T2 + (size_t)blockIdx.z * C * cstride + (size_t)kx * PY + f;
+    const bool flip = f > PY / 2;
+    T c[2 * L + 1], s[2 * L + 1];
+    load_entries<T, L>(Q + (size_t)kx * KH, (size_t)nkq * KH, half_entry(flip ? PY - f : f, PY), c, s);
+    cx<T> a[L + 1], b[L + 1];
+    a[0] = p[0];
+#pragma unroll
+    for (int k = 1; k <= L; ++k) {
+        a[k] = phase_in(p[(2 * k - 1) * cstride], k);
+        b[k] = phase_in(p[2 * k * cstride], k);
+    }
+    const T sg = flip ? (T)-1 : (T)1;
+#pragma unroll
+    for (int m = 0; m <= 2 * L; ++m) s[m] *= sg;
+    couple_rows<T, L>(a, b, c, s, [&](int ch, cx<T> z) { p[ch * cstride] = z; });
+}
+template <typename T, int PY, int L>
+static void launch_regs(const Apply2DArgs<T>& a, int nbatch, int nkx) {
+    hipLaunchKernelGGL((k_couple_regs<T, PY, L>), dim3(PY / 64, nkx, nbatch), dim3(64), 0, a.stream, a.work2, a.Q, nkx,
+                       nkx);
+}
+
 template <typename T, int PY>
 static int launch_large(const Apply2DArgs<T>& a, int nbatch) {
     const int nkq = a.PX / 2 + 1;
     const int nkx = nkq;                      // unpacked
     if (a.single_in && nbatch != 1) return -3;
     const size_t nseq = (size_t)nbatch * a.C * nkx;
+    if (a.L <= PASSB_FUSED_MAX_L) {
+        if constexpr (sizeof(T) == 8 && PY == 1024) {   // the only shapes with halves
+            if (a.single_in || a.L < 5) return -1;
+            split_fft<T, PY, false>(a.work, a.work2, a.twy, a.ny, nseq, a.stream);
+            switch (a.L) {
+                case 5: launch_regs<T, PY, 5>(a, nbatch, nkx); break;
+                case 6: launch_regs<T, PY, 6>(a, nbatch, nkx); break;
+                case 7: launch_regs<T, PY, 7>(a, nbatch, nkx); break;
+                case 8: launch_regs<T, PY, 8>(a, nbatch, nkx); break;
+            }
+            split_fft<T, PY, true>(a.work, a.work2, a.twy, a.ny, nseq, a.stream);
+            return 0;
+        }
+        return -1;
+    }
     split_fft<T, PY, false>(a.work, a.work2, a.twy, a.ny, a.single_in ? (size_t)nkx : nseq, a.stream);
     const int PM = mode_fft_len(a.L);
     if (a.var[1] == 1) {
@@ -316,7 +364,7 @@ static int launch_large(const Apply2DArgs<T>& a, int nbatch) {
 
 template <typename T>
 int pass_b_large(const Apply2DArgs<T>& a, int nbatch) {
-    if (a.pack || !a.work2 || !a.twm || a.L <= PASSB_FUSED_MAX_L || a.L > RTE_MAX_L) return -1;
+    if (a.pack || !a.work2 || (!a.twm && a.L > PASSB_FUSED_MAX_L) || a.L > RTE_MAX_L) return -1;
     switch (a.PY) {
         case 16: return launch_large<T, 16>(a, nbatch);
         case 32: return launch_large<T, 32>(a, nbatch);

@@ -159,6 +159,12 @@ int ensure_krylov(rte_ctx* c, int m, bool need_z, size_t vbytes, size_t nlen) {
     return RTE_OK;
 }
 
+// Whether some apply of the context in precision T takes the split form (work2).
+template <typename T>
+static bool needs_work2(const rte_ctx* c) {
+    return apply2d_split<T>(c->L, c->PY) || apply2d_few_columns<T>(c->L, c->PX, c->PY, 1);
+}
+
 // FFT work buffers for nb batch entries (right-hand sides); grown on demand, never shrunk.
 static int ensure_work(rte_ctx* c, int nb) {
     if (nb <= c->work_nb) return RTE_OK;
@@ -174,10 +180,10 @@ static int ensure_work(rte_ctx* c, int nb) {
         const size_t nt = (size_t)nb * c->C * NK * c->ny;
         const size_t nt2 = (size_t)nb * c->C * NK * c->PY;
         if ((rc = dalloc(&c->wd, nt))) return rc;
-        if (apply2d_split<double>(c->L, c->PY) && (rc = dalloc(&c->wd2, nt2))) return rc;
+        if (needs_work2<double>(c) && (rc = dalloc(&c->wd2, nt2))) return rc;
         if (f32) {
             if ((rc = dalloc(&c->wf, nt))) return rc;
-            if (apply2d_split<float>(c->L, c->PY) && (rc = dalloc(&c->wf2, nt2))) return rc;
+            if (needs_work2<float>(c) && (rc = dalloc(&c->wf2, nt2))) return rc;
         }
     } else {
         const size_t n1 = (size_t)nb * c->C * c->nz * NK * c->ny;
@@ -211,9 +217,11 @@ static ChanScale3 channel_scale3(const rte_ctx* c, int mode) {
 }
 
 // Column 0 of the 2D work buffer packs the x-frequencies 0 and PX/2 (two real sequences) except in
-// pass B's split form.
+// pass B's split form.  single: an apply of channel 0 alone (single_in).
 template <typename T>
-static int pack_for(const Apply2DArgs<T>& a) { return apply2d_split<T>(a.L, a.PY) ? 0 : 1; }
+static int pack_for(const Apply2DArgs<T>& a, int nbatch = 1, bool single = false) {
+    return apply2d_split<T>(a.L, a.PY) || (!single && apply2d_few_columns<T>(a.L, a.PX, a.PY, nbatch)) ? 0 : 1;
+}
 
 template <typename T>
 static Apply2DArgs<T> args2d(const rte_ctx* c);
@@ -240,7 +248,7 @@ template <typename T>
 static Apply2DArgs<T> x_pass_args(const rte_ctx* c, int mode, int nbatch, ChanScale& sc, int& nb) {
     Apply2DArgs<T> a = args2d<T>(c);
     if (c->dim == 2) {
-        a.pack = pack_for(a);
+        a.pack = pack_for(a, nbatch);
         sc = channel_scale(c, mode);
         nb = nbatch;
         return a;
@@ -1121,10 +1129,10 @@ int rte_setup(rte_ctx** out, const rte_grid* g, double mu_a, double mu_s, const 
         const size_t nt = (size_t)nb * c->C * NK * c->ny;
         const size_t nt2 = (size_t)nb * c->C * NK * c->PY;
         if ((rc = dalloc(&c->wd, nt))) { free_ctx(c); return rc; }
-        if (apply2d_split<double>(c->L, c->PY) && (rc = dalloc(&c->wd2, nt2))) { free_ctx(c); return rc; }
+        if (needs_work2<double>(c) && (rc = dalloc(&c->wd2, nt2))) { free_ctx(c); return rc; }
         if (f32) {
             if ((rc = dalloc(&c->wf, nt))) { free_ctx(c); return rc; }
-            if (apply2d_split<float>(c->L, c->PY) && (rc = dalloc(&c->wf2, nt2))) { free_ctx(c); return rc; }
+            if (needs_work2<float>(c) && (rc = dalloc(&c->wf2, nt2))) { free_ctx(c); return rc; }
         }
     } else {
         const size_t n1 = (size_t)nb * c->C * c->nz * NK * c->ny;
@@ -1280,7 +1288,7 @@ static int rhs_channels(rte_ctx* c, const double* f, double* b) {
         // b = K~ (f, 0, ..., 0): pass A for channel 0 only, pass B reading channel 0 only (its
         // coupling writes every channel); inverse y-FFTs and pass C as usual
         Apply2DArgs<double> a = args2d<double>(c);
-        a.pack = pack_for(a);
+        a.pack = pack_for(a, 1, true);
         const ChanScale sc = channel_scale(c, APPLY_KT);
         Apply2DArgs<double> a1 = a;
         a1.C = 1;
