@@ -244,21 +244,28 @@ __global__ __launch_bounds__(NTHR) void k_pass_c_modes(const cx<T>* __restrict__
 // applies in FP32 with R and R/2 rows: 200x150, L = 2 (57 blocks of R) 31.6 and 24.4 us; 512^2, L = 0 (128)
 // 24.2 and 21.1; 256^2, L = 4 (160) 35.7 and 30.0; 300x257, L = 3 (260) 59.9 and 65.7; 400x300, L = 8 (675)
 // 133 and 163.
+// FP64 at padded x = 1024: one block per CU either way (two rows and the twiddles take 86 KB), so four rows
+// (156 KB, whole 64-byte pieces of a spectrum column) by 512 threads, and two only where their blocks
+// still run at once.  Two rows by 256 threads, four by 256 and by 512, us: 512^2, L = 8 316, 301, 283; 300^2,
+// L = 16 1326, 1249, 1236 (separate conversions 1262); 512x16, L = 4 (two rows by either) 25.5 and 24.2.
+template <typename T, int PX>
+constexpr bool modes_wide() { return sizeof(T) == 8 && PX == 1024; }
 template <typename T, int PX>
 constexpr int mode_rows() {
-    int r = 8;
-    while (r > 2 && 2L * r * (padded(PX) + 1) * (long)sizeof(cx<T>) > 70 * 1024) r /= 2;
+    int r = modes_wide<T, PX>() ? 4 : 8;
+    while (!modes_wide<T, PX>() && r > 2 && 2L * r * (padded(PX) + 1) * (long)sizeof(cx<T>) > 70 * 1024) r /= 2;
     return r;
 }
 template <typename T, int PX, int R, bool PAIR>
 static void launch_modes_r(const Apply2DArgs<T>& a, int pass, const cx<double>* u, cx<double>* v, int mode,
                            const ChanScale& sc, int ngroups) {
+    constexpr int NT = modes_wide<T, PX>() ? 512 : 256;
     dim3 grid((a.ny + R - 1) / R, ngroups);
     if (pass == 0)
-        hipLaunchKernelGGL((k_pass_a_modes<T, PX, R, 256, PAIR>), grid, dim3(256), 0, a.stream, u, a.work, a.twx, a.nx, a.ny,
+        hipLaunchKernelGGL((k_pass_a_modes<T, PX, R, NT, PAIR>), grid, dim3(NT), 0, a.stream, u, a.work, a.twx, a.nx, a.ny,
                            a.L, sc, a.pack);
     else
-        hipLaunchKernelGGL((k_pass_c_modes<T, PX, R, 256, PAIR>), grid, dim3(256), 0, a.stream, a.work, u, v, a.twx, a.nx,
+        hipLaunchKernelGGL((k_pass_c_modes<T, PX, R, NT, PAIR>), grid, dim3(NT), 0, a.stream, a.work, u, v, a.twx, a.nx,
                            a.ny, a.L, mode, a.pack);
 }
 template <typename T, int PX>
@@ -266,7 +273,8 @@ static int launch_modes(const Apply2DArgs<T>& a, int pass, const cx<double>* u, 
                         const ChanScale& sc, int singles) {
     constexpr int R = mode_rows<T, PX>(), RH = R > 2 ? R / 2 : 2;
     const int ngroups = singles ? singles : a.L + 1;
-    const bool few = (long)((a.ny + R - 1) / R) * ngroups < 256;
+    const long most = modes_wide<T, PX>() ? 256 : 512;   // blocks of RH rows
+    const bool few = (long)((a.ny + R - 1) / R) * ngroups < 256 && (long)((a.ny + RH - 1) / RH) * ngroups <= most;
     if (singles) {
         if (few) launch_modes_r<T, PX, RH, false>(a, pass, u, v, mode, sc, ngroups);
         else launch_modes_r<T, PX, R, false>(a, pass, u, v, mode, sc, ngroups);
