@@ -277,7 +277,7 @@ int rte_set_batched_variant(int pass, int variant);
  * coupling), 3 = D (inverse y-FFT), 4 = E (inverse x-FFT).  Variants differ only in tiling (row
  * tiles, z-rows or columns per block, the coupling method for more than 17 modes): the
  * same arithmetic, equal results up to rounding.  Pass B in 2D with up to 17 modes, and in FP32 with up to
- * 33 at padded y <= 512, has one kernel per shape, which every variant number of its range selects.
+ * 33 at padded y <= 512, has one form per shape, which every variant number of its range selects.
  * rte_setup of a 2D
  * context with n_x or n_y >= 128, or of a 3D context with a side >= 64, picks the fastest variant of
  * every pass by timing them on the context's buffers, once per (precision, L, grid) per process

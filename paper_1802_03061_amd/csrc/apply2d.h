@@ -57,7 +57,7 @@ struct Apply2DArgs {
 
 // Kernel variants (same arithmetic, different tiling; results agree up to rounding):
 //   passes A and C (PX >= 128): row tiles of 16, 8, 32 or 4 rows (FP32) / 8, 4, 16 or 2 rows (FP64)
-//   pass B: one kernel per shape (passb_wave.h).  The variant numbers of the forms it replaced stay
+//   pass B: one form per shape (passb_wave.h).  The variant numbers of the forms it replaced stay
 //   valid and select it.
 //   pass B in split form: the coupling as a mode-axis FFT or as a register-blocked direct sum
 // Number of variants of `pass` (0 = A, 1 = B, 2 = C) for this shape and precision, and how many of

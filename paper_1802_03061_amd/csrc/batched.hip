@@ -244,9 +244,10 @@ __global__ __launch_bounds__(BT) void kb_update(const Chunk* __restrict__ ch, co
 
 // The applies write K v_j alone and need not read their input again: A = I - K, and the dots and the
 // update, which read v_j anyway, take A v_j = v_j - K v_j.  (Not K v_j itself: in diffusive media it is
-// nearly v_j, and the basis loses its orthogonality.)  The basis vectors are stored as the update leaves them, with their factors 1/|w| in sc: pass A, the dots, the
-// update and the combination multiply by those, and no pass over w normalises it.  (128 problems of
-// 64^2 to 512^2: the normalising pass took 31 us of a step of all problems, the second read 17 us.)
+// nearly v_j, and the basis loses its orthogonality.)  The basis vectors are stored as the update
+// leaves them, with their factors 1/|w| in sc: pass A, the dots, the update and the combination multiply
+// by those, and no pass over w normalises it.  (128 problems of 64^2 to 512^2: the normalising pass took
+// 31 us of a step of all problems, the second read 17 us.)
 //
 // H[j+1][j] = |w|, the previous Givens rotations and a new one on column j, the residual vector
 // g and the estimate |g[j+1]|; decides whether the problem keeps iterating.  One 64-lane block per

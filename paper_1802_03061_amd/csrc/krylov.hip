@@ -52,9 +52,9 @@ __global__ __launch_bounds__(KT) void k_arn1(ArnoldiArgs t, const double* __rest
 // is given.  The vector count is a template parameter so that every load of a step is issued before
 // the first multiply.  With even n and ld (and 16-byte aligned V and w) each thread reads element
 // pairs as 16-byte loads.  DOTS_A: w = K u, and A u = u - w takes the place of w, formed here in FP64; u
-// is the group's last vector or, with DOTS_A_SEP, read beside it.  With upd, one more block (the first to start) runs stage 1 of the column
-// before, which nothing needs until this column's update: 7 us out of the way of the step.  The slice
-// a block covers and the order of its sums do not depend on the data.
+// is the group's last vector or, with DOTS_A_SEP, read beside it.  With upd, one more block (the first
+// to start) runs stage 1 of the column before, which nothing needs until this column's update: 7 us out
+// of the way of the step.  The slice a block covers and the order of its sums do not depend on the data.
 enum { DOTS_W = 0, DOTS_A = 1, DOTS_A_SEP = 2 };
 template <int NV, bool PAIRS, int FORM, typename TV>
 __global__ __launch_bounds__(KT) void k_dot_partial(const TV* __restrict__ V, size_t ld,

@@ -1,10 +1,10 @@
 // Pass B with wave-private y-FFTs and the mode coupling in real arithmetic.
 //
-// A block holds the spectra of NCOL columns x C channels in LDS, and
-// every sequence is transformed by one wave (or part of one) from its loads to its spectrum and
-// back, so a transform's stages are ordered by the wave alone and the block meets at two barriers
-// per column group: before and after the coupling.  Waves drift apart between them, and one wave's
-// LDS latency hides behind another's arithmetic.
+// A block holds the spectra of NCOL columns x C channels in LDS, and every sequence is transformed by
+// one wave (or part of one) from its loads to its spectrum and back, so a transform's stages are ordered
+// by the wave alone and the block meets at two barriers per column group: before and after the
+// coupling.  Waves drift apart between them, and one wave's LDS latency hides behind another's
+// arithmetic.
 //
 // Coupling.  In the real-channel basis the operator's (c, c') kernel is kappa(r) times a product of
 // cos k theta, sin k theta: with Khat_m = C_m + i S_m (the spectra of kappa cos m theta and kappa
@@ -17,12 +17,12 @@
 //
 // Bound and measured (512^2, L = 8, FP32, MI355X): vector arithmetic.  The form this replaces (stages
 // by the whole block, complex coupling) took 57-60 us with 21.3M vector instructions and its vector
-// units busy 58 % of the time; this one takes 39 us with 15.9M (the column traffic alone: 13 us).
-// Of a column's time at a CU about 40 % is the coupling and 40 % the transforms.  Twiddles are read
-// from memory (L1-resident): staging them in LDS cost each block a memory latency and took 0.5 us
-// longer at 256^2.  At 256^2, L = 8 the FP64 apply went from 72 to 42 us.  With 33 modes at
-// 256^2 in FP32 pass B takes 31 us, where forward transforms, a register-blocked complex coupling and
-// inverse transforms through a full-length buffer took 83 us.
+// units busy 58 % of the time; this one takes 39 us with 16.4M (the column traffic alone: 14 us).
+// Without the coupling it takes 29.6 us, without the transforms but for their first and last stages
+// 29.5, without both 19.8.  Twiddles are read from memory (L1-resident): staging them in LDS cost each
+// block a memory latency and took 0.5 us longer at 256^2.  At 256^2, L = 8 the FP64 apply went from 72 to
+// 42 us.  With 33 modes at 256^2 in FP32 pass B takes 31 us, where forward transforms, a register-blocked
+// complex coupling and inverse transforms through a full-length buffer took 83 us.
 #pragma once
 #include "apply2d.h"
 #include "fft_wave.h"
