@@ -139,7 +139,7 @@ int ensure_krylov(rte_ctx* c, int m, bool need_z, size_t vbytes, size_t nlen) {
     if ((rc = dalloc(&c->partial_u, n / c->nx))) return rc;
     if ((rc = dalloc(&c->dsmall, (size_t)(2 * m + 16)))) return rc;
     // device Arnoldi state: H [(m+1) x m] | cs [m] | sn [m] | g [m+1] | est [m] | inv [m+1]
-    if ((rc = dalloc(&c->arn, (size_t)(m + 1) * m + 4 * (size_t)m + 2))) return rc;
+    if ((rc = dalloc(&c->arn, (size_t)(m + 1) * m + 5 * (size_t)m + 2))) return rc;
     if ((rc = dalloc(&c->arn_flags, 4))) return rc;
     hipError_t e = hipSuccess;
     // per-iteration pinned slots: estimate; (breakdown, non-finite) flags
